@@ -22,8 +22,8 @@
 //   - block -> (slice, row run) is XCD-aware: blocks are dispatched round-robin
 //     over the 8 XCDs, and every block of a slice runs on the same XCD, so its
 //     L2 serves the repeated slice staging.
-// When the slice of every chunk does not fit in LDS (many chunks, ell >= 2, bf16 at
-// large N) the worker-group layout below takes over.
+// Where the slice of every chunk does not fit in LDS or rows start off 16-byte boundaries, the
+// matrix-core encode (encode_mx.hip) or the worker-group layout below takes over.
 #include "common.h"
 #include "encode_mx.h"
 
@@ -239,18 +239,15 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(EncodeArgs a) {
 // and are broadcast with readlane; the LDS offset of each term's slice comes from
 // a per-group table the same way.  The blocks of a slice run back to back on one
 // XCD, so its L2 serves the groups' overlapping chunk slices.
-// Shapes with many terms per output normally take the bf16 matrix-core encode
-// (encode_mx.hip); where its staged rows do not fit, with a full 32-pattern tile per call
-// and delta*ell >= 32 terms per output (a dense contraction [32 patterns][terms] x
+// Shapes with up to 176-192 terms per output normally take the bf16 matrix-core encode
+// (encode_mx.hip), whatever the alignment of the rows.  Past that, with a full 32-pattern tile
+// per call and delta*ell >= 32 terms per output (a dense contraction [32 patterns][terms] x
 // [terms][128 positions] per worker), a block whose group's chunks are all staged runs its
 // items on the fp32 matrix cores instead (v_mfma_f32_32x32x2f32; coefficients past a
 // pattern's prefix enter as zeros, so the gradient values must be finite).  With fewer
 // patterns, the tile rows are 16 (pattern, worker) pairs and its K the group's staged
 // chunk blocks (v_mfma_f32_16x16x4f32).
-// fp32 chunk gradients take the bf16 matrix-core encode from this many terms per output
-// (measured at m = 100, d = 2^20: at delta*ell = 10 the vector path writes 7% faster; at 20
-// the two are within a few percent either way, at 80 the matrix cores win by far)
-constexpr int kMxF32Terms = 32;
+constexpr int kGrpFewPatterns = 4, kGrpFewTerms = 24;  // fp32 calls that keep the vector units
 constexpr int kGrpThreads = 512;
 constexpr int kGrpWaves = kGrpThreads / kWave;
 constexpr size_t kGrpLds = 72 * 1024;     // per block: two blocks per CU
@@ -919,8 +916,9 @@ int launch_encode_group(EncodeArgs a, int64_t P, hipStream_t st) {
   return pb4 ? launch_group<GT, 1, 1, 4>(a, g, lds, st) : launch_group<GT, 1, 1, 2>(a, g, lds, st);
 }
 
-template <typename GT, int VEC>
+template <typename GT>
 int launch_encode(EncodeArgs a, hipStream_t st) {
+  constexpr int VEC = 4;
   constexpr int W = kWave * VEC;
   a.nslices = int(ceil_div(a.L, W));
   a.term_stride = (a.delta * a.ell + 3) & ~3;
@@ -952,10 +950,7 @@ int launch_encode(EncodeArgs a, hipStream_t st) {
 }
 
 template <typename GT>
-int dispatch_encode(const EncodeArgs &a, int64_t P, int vec, bool all_chunks, hipStream_t st) {
-  if (all_chunks)
-    return vec == 4 ? launch_encode<GT, 4>(a, st)
-                    : (vec == 2 ? launch_encode<GT, 2>(a, st) : launch_encode<GT, 1>(a, st));
+int dispatch_group(const EncodeArgs &a, int64_t P, int vec, hipStream_t st) {
   return vec == 4 ? launch_encode_group<GT, 4>(a, P, st)
                   : (vec == 2 ? launch_encode_group<GT, 2>(a, P, st) : launch_encode_group<GT, 1>(a, P, st));
 }
@@ -990,23 +985,31 @@ extern "C" int gc_encode(const void *G, int32_t g_dtype, int32_t N, int64_t d, c
   a.delta = delta;
   a.ell = ell;
   a.T = T;
-  // widest vector the row length and the alignment of T allow; the all-chunk layout
-  // when the slice of every chunk fits in LDS at that width, else the worker groups
   const size_t esize = g_dtype == GC_F32 ? 4 : 2;
   const uintptr_t ta = reinterpret_cast<uintptr_t>(T), ga = reinterpret_cast<uintptr_t>(G);
   const int64_t sv = int64_t(16 / esize);
   a.stage16 = d % sv == 0 && a.L % sv == 0 && (ga & 15) == 0;
+  // widest vector the row length and the alignment of T allow
   const int vec = (a.L % 4 == 0 && (ta & 15) == 0) ? 4 : ((a.L % 2 == 0 && (ta & 7) == 0) ? 2 : 1);
-  const bool all_chunks = size_t(N) * ell * kWave * vec * esize <= kEncSliceLds;
   (void)hipGetLastError();
-  // beyond the all-chunk layout, the bf16 matrix cores where they fit: always for bf16 chunk
-  // gradients; for fp32 ones from kMxF32Terms terms per output on
-  if (!all_chunks && (g_dtype == GC_BF16 || delta * ell >= kMxF32Terms)) {
-    const int st = encode_mx(G, g_dtype == GC_F32, N, d, psi, order, Bc, P, m, delta, ell, T, stream);
-    if (st != kEncodeMxNotApplicable) return st != GC_OK ? st : launch_status();
+  // The all-chunk layout where the rows of G and T are 16-byte aligned and the slice of every
+  // chunk fits in LDS (m = 50, ell = 1: 1.85 ms for 5000 patterns against 1.94 on the matrix
+  // cores; on rows that start anywhere its scalar accesses lose: m = 37, ell = 3, d = 100003
+  // 2.1 ms against 0.62).  Else the matrix cores up to 176 (fp32) or 192 (bf16) terms per output,
+  // and past that the worker groups.
+  if (vec == 4 && a.stage16 && size_t(N) * ell * kWave * 4 * esize <= kEncSliceLds) {
+    const int st = g_dtype == GC_F32 ? launch_encode<float>(a, stream) : launch_encode<uint16_t>(a, stream);
+    return st != GC_OK ? st : launch_status();
   }
-  const int st = g_dtype == GC_F32 ? dispatch_encode<float>(a, P, vec, all_chunks, stream)
-                                   : dispatch_encode<uint16_t>(a, P, vec, all_chunks, stream);
+  // A few patterns with few terms stay there too: one pattern, m = 200, delta = 8, d = 65536 on a
+  // random regular order, where no two workers share chunks, 0.10 ms against 0.15 (ell = 1) and
+  // 0.13 against 0.16 (ell = 3); on cyclic orders the two are equal (m = 100, delta = 10, ell = 2, d
+  // = 2^18: 0.069 ms both).
+  int st = kEncodeMxNotApplicable;
+  if (!(g_dtype == GC_F32 && vec == 4 && P <= kGrpFewPatterns && delta * ell <= kGrpFewTerms))
+    st = encode_mx(G, g_dtype == GC_F32, N, d, psi, order, Bc, P, m, delta, ell, T, stream);
+  if (st == kEncodeMxNotApplicable)
+    st = g_dtype == GC_F32 ? dispatch_group<float>(a, P, vec, stream) : dispatch_group<uint16_t>(a, P, vec, stream);
   if (st != GC_OK) return st;
   return launch_status();
 }

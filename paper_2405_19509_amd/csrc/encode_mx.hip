@@ -1,12 +1,12 @@
 // gc_encode on the bf16 matrix cores (Sec. 2, worker encode):
 //   T[p][j][x] = sum_{t < psi[p][j]} sum_{k < ell} Bc[p][j][t][k] * g_{order[j][t]}[k*L + x]
 //
-// Why matrix cores: every output value of the encode takes psi*ell multiply-adds, 4-5 per
-// byte of T at delta = 20, ell = 1 and 4x that at ell = 4, which the vector units cannot
-// sustain at the HBM write rate.  Per worker group the encode is a dense contraction
-//   T[(pattern, worker)][x] = sum_kk A[(pattern, worker)][kk] * Gs[kk][x]
-// over kk = (chunk slot s of the group's union, block k), with A the coefficients of the
-// row's worker (zero where the worker does not hold the chunk or has not processed it).
+// Per window of (pattern, worker) rows the encode is a dense contraction
+//   T[row][x] = sum_kk A[row][kk] * B[kk][x]
+// over kk = (chunk slot s of the window's workers, block k): A the coefficients of the
+// transmitting rows (zero where the worker does not hold the chunk or has not processed it),
+// B the chunk gradients.  The vector units cannot sustain its 2 psi ell flops per 4 bytes of T
+// at the HBM write rate past a few terms per output; the bf16 matrix cores can.
 //
 // Arithmetic: each fp32 coefficient a is split into three bf16 parts a = a1 + a2 + a3 + r
 // with |r| <= 2^-24 |a| (each part the bf16 rounding of what the previous ones leave).
@@ -14,33 +14,32 @@
 // g is split exactly into three bf16 parts by truncation (g1 its top 16 bits, g2 the top 16
 // bits of g - g1, g3 the rest), and the six products a_i g_j with i + j <= 4 are kept: the
 // dropped ones stay below 2^-21 |a g|.  Every product of two bf16 values is exact in fp32;
-// v_mfma_f32_32x32x16_bf16 accumulates them in fp32.
+// v_mfma_f32_32x32x16_bf16 accumulates them in fp32.  Against 64 bits the error is at or
+// below that of the fp32 vector sum (m = 37, ell = 3: 7.3e-8 against 8.2e-8 relative).
+// A zero coefficient times a non-finite gradient is not zero, so tiles whose gradients are
+// not all finite are computed term by term over each row's processed prefix instead.
 //
-// Layout: a block owns a group of J consecutive workers, a window of PB patterns
-// (J * PB = 64 or 128 candidate rows (pattern, worker), candidate r = pb * J + jb) and a
-// range of at most 32 slices of x walked in turn.  The window's transmitting rows (psi > 0) are
-// compacted into full 32-row tiles (stragglers cost nothing), whose coefficients, split
-// into three bf16 planes, are built once per block.  Per slice the block stages the slices
-// of the group's union of chunks (J + delta - 1 chunks under the cyclic order), one row per
-// (slot, block), and every row tile is computed against them:
-//   bf16: 512-wide slices staged straight from memory to LDS (1 KB rows); each of the 8
-//         waves takes two 32 x 32 output tiles per row tile, per 16-deep K step three bf16x8
-//         coefficient loads, eight 16-bit gathers of the staged column per tile, six MFMAs.
-//         Where the group's rows need 3+ K steps, 128-candidate windows with 256-wide
-//         slices: the union of twice the workers is not much larger, so the rows staged per
-//         row written nearly halve; each wave takes one 32-wide column, gathered once per K
-//         step for all (up to four) row tiles.  From 4 K steps on a block fills a CU's LDS
-//         and the K loop is unrolled into the registers that frees;
-//   fp32: 512-wide slices (256-wide from 4 K steps on) staged through registers with the
-//         staged rows fastest, so that a lane's eight K values of one position are two
-//         16-byte reads, split once per slice for both row tiles; each wave takes one
-//         32-position tile, six MFMAs per row tile and K step.
-// Stores are 4 bytes per lane, two 128-byte row segments per instruction, non-temporal;
-// rows of workers that transmit nothing (psi = 0) are not written.  Blocks of a slice range
-// run back to back on one XCD (round-robin dispatch), so its L2 serves the groups'
-// overlapping chunk slices.  If a block's union exceeds its slots (orders other than the
-// cyclic one), it walks its workers one at a time (a pass per worker, each staging only
-// that worker's chunks).
+// Layout: a window is up to CW candidate rows, PB patterns x J workers, its transmitting rows
+// compacted into 32-row tiles; their coefficient planes are built in LDS once per block.  A
+// wave then walks tiles of W = 32 PW positions: it loads B straight into registers in the
+// matrix operand's layout (lane (h, li): positions x0 + PW li .. + PW - 1 of the rows kk
+// with kk % 2 = h; PW positions per lane are PW separate 32-wide tiles, so loads and stores
+// stay contiguous across the lanes), splits it once, multiplies every row tile by it and
+// stores each.  The gradients are thus read and split once per window instead of passing
+// through LDS, no barrier separates the phases, and nothing orders one wave's stores with
+// another's loads.  Measured against LDS slices with barriers between staging, products and
+// stores (time per call, MI355X): m = 100, d = 2^20 fp32, ell = 2, 64 patterns 3.2 -> 2.5
+// ms (vector path before), ell = 8, 256 patterns 6.3 -> 3.8 ms; m = 200 bf16, d = 2^22, ell =
+// 4, half the workers lost 2.8 -> 2.05 ms, d = 2^24, ell = 2, one pattern 3.8 -> 2.6 ms.
+// What bounds it: the T stores alone take 1.85 / 2.1 / 1.2 ms of the first three, the products
+// 0.6 / 1.6 / 0.7 ms, and the two barely overlap (the clock falls to 1.7 GHz under both); the
+// last runs at the rate of a plain copy of its 6.7 GB in and 6 GB out.
+//
+// Rows of workers that transmit nothing (psi = 0) are not written.  The blocks of a position
+// range run back to back on one XCD (round-robin dispatch), so its L2 serves the windows'
+// overlapping chunks.  If a window's workers hold more distinct chunks than its slots (orders
+// other than the cyclic one), the block takes as many of its workers at a time as fit.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -49,22 +48,30 @@
 namespace gcx {
 namespace {
 
-constexpr int kMxThreads = 512;              // bf16, and fp32 with more than 3 K steps
-constexpr int kMxW = 512;                    // positions per slice (1 KB of bf16 per staged row)
-constexpr int kMxfMaxWideKS = 3;             // fp32: 512-wide slices (1024 threads) up to 3 K steps
-static_assert(kMxW == (kMxThreads / 64) * 64 && kMxW * 2 == 64 * 16, "bf16: two 32-wide tiles per wave, 16 bytes per lane and staged row");
-constexpr int kMxMaxKS = 6;                  // K steps of 16 (at most 96 staged rows)
-// slices a block walks at most: runs of 32 wrote T up to 8% faster than the 128-373-slice
-// runs that about 16 blocks per CU gave at d = 2^20 and 2^24 (a store-only kernel with
-// this grid showed the same: its write rate rose with the number of shorter blocks)
-constexpr int64_t kMxSliceRun = 32;
-// bf16: 128-candidate windows (256-wide slices, one tile per wave) where a 64-candidate
-// window would need this many K steps
-constexpr int kMxWinKS = 3;
-constexpr size_t kMxLds = 152 * 1024;
+constexpr int kMxThreads = 512;         // threads per block, at most
+constexpr int kMxMaxCW = 256;           // candidate rows per window, at most
+// K steps of 16 rows of B, as the registers allow
+constexpr int kMxMaxKSF32 = 11, kMxMaxKSBF16 = 12;
+constexpr int kMxMapChunks = 4096;      // chunks up to which groups of workers are formed
+constexpr size_t kMxLds = 144 * 1024;   // dynamic LDS of a block, at most
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+// PW neighbouring positions of a gradient or of T, at element alignment: rows start anywhere
+template <int N>
+struct __attribute__((packed, aligned(2))) HalfPairs {
+  uint32_t v[N];
+};
+template <int N>
+struct Floats;
+template <>
+struct Floats<1> { typedef float T; };
+template <>
+struct Floats<2> { typedef float T __attribute__((ext_vector_type(2), aligned(4))); };
+template <>
+struct Floats<4> { typedef float T __attribute__((ext_vector_type(4), aligned(4))); };
 
 // round-to-nearest-even bf16 bits of a finite fp32 value
 __device__ __forceinline__ uint32_t bf16_rne(float v) {
@@ -72,14 +79,17 @@ __device__ __forceinline__ uint32_t bf16_rne(float v) {
   return (b + 0x7fffu + ((b >> 16) & 1u)) >> 16;
 }
 
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+// chk + 0 * (either bf16 half of pair): a NaN once a half is infinite or a NaN
+__device__ __forceinline__ float times_zero(uint32_t pair, float chk) {
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(v2bf, pair), __builtin_bit_cast(v2bf, 0u), chk, false);
+}
 
 // Exact split of eight finite fp32 values into three bf16 parts each, g = g1 + g2 + g3:
 // g1 keeps the top 16 bits of g (sign, exponent, 7 fraction bits), g - g1 is exact with at
 // most 16 significant bits, g2 its top 16 bits, and what remains has at most 8 significant
-// bits, a bf16 value (|g2| < 2^-7 |g|, |g3| < 2^-15 |g|; exact for |g| >= 2^-100).
-__device__ __forceinline__ void split3(float4 u0, float4 u1, v8bf &g1, v8bf &g2, v8bf &g3) {
-  const float v[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+// bits, a bf16 value (|g2| < 2^-7 |g|, |g3| < 2^-15 |g|; exact for |g| >= 2^-100).  The
+// top half of an infinity or a NaN is an infinity or a NaN too.
+__device__ __forceinline__ void split3(const float (&v)[8], v8bf (&g)[3]) {
   uint32_t h1[8], h2[8], h3[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -95,474 +105,458 @@ __device__ __forceinline__ void split3(float4 u0, float4 u1, v8bf &g1, v8bf &g2,
     p2[j] = __builtin_amdgcn_perm(h2[2 * j + 1], h2[2 * j], 0x07060302u);
     p3[j] = __builtin_amdgcn_perm(h3[2 * j + 1], h3[2 * j], 0x07060302u);
   }
-  g1 = __builtin_bit_cast(v8bf, p1);
-  g2 = __builtin_bit_cast(v8bf, p2);
-  g3 = __builtin_bit_cast(v8bf, p3);
+  g[0] = __builtin_bit_cast(v8bf, p1);
+  g[1] = __builtin_bit_cast(v8bf, p2);
+  g[2] = __builtin_bit_cast(v8bf, p3);
 }
 
 struct MxArgs {
   const void *G;
   int N;
   int64_t d, L;
+  int64_t lmin;  // positions valid in every block: max(0, d - (ell - 1) L)
   const int32_t *psi;
   const int32_t *order;
   const float *Bc;
   int64_t P;
   int m, delta, ell;
   float *T;
-  bool stage16;   // bf16: G 16-byte aligned and d, L multiples of 8; fp32: 8-byte, multiples of 2
-  int J;          // workers per window
-  int PB;         // patterns per window (J * PB = 64 or 128 candidate rows, at most)
+  bool nt;       // rows of T on 64-byte boundaries
+  int J, PB;     // workers and patterns per window
+  int CW;        // candidate rows J * PB, rounded up to 32
   int ngroups;
-  int64_t ntp;    // pattern windows
-  int slots;      // union slots staged per block
-  int nslices;
-  int64_t spb;    // slices per range
-  int64_t nsr;    // slice ranges (a multiple of 8)
+  int64_t ntp;   // pattern windows
+  int slots;     // chunk slots (rows of B / ell)
+  int64_t ntiles, tpb, nsr;  // position tiles, per block, ranges (a multiple of 8)
 };
 
-// Slice region of the LDS, by chunk-gradient type:
-//   bf16: Kp staged rows x RB bytes, position fastest (filled straight from memory)
-//   fp32: W positions x (Kp + 4) floats, staged row fastest (a lane's eight K values of
-//         one position are two 16-byte reads)
-template <typename GT, int KS, int CW>
+// dynamic LDS of a block, as laid out at the kernel
+size_t mx_lds(const MxArgs &a, int KS) {
+  const size_t Kp = 16 * size_t(KS);
+  return size_t(a.CW) * 3 * (Kp + 8) * 2 + 2 * sizeof(int64_t) * Kp + sizeof(int64_t) * a.CW +
+         sizeof(int32_t) * (size_t(a.J) * a.delta + a.slots + (a.J > 1 ? a.N : 0)) + 2 * sizeof(int16_t) * a.CW;
+}
+
+template <typename GT, int KS, int PW>
 struct MxLayout {
   static constexpr bool F32 = sizeof(GT) == 4;
+  static constexpr int NP = F32 ? 3 : 1;  // parts of a gradient value
   static constexpr int Kp = 16 * KS;
-  static_assert(CW == 64 || (CW == 128 && !F32), "64 candidates, or 128 with bf16 chunk gradients");
-  static constexpr bool WIN = CW == 128;  // 256-wide slices, one 32-wide tile per wave
-  static constexpr int NT = CW / 32;      // row tiles at most
-  // fp32: one 32-wide tile per wave, 2 KB row segments of T per slice (16 waves) while the
-  // staged rows fit, else 256 positions (8 waves); bf16: two tiles per wave, 512 positions
-  // (128-candidate windows: one tile per wave, 256 positions)
-  static constexpr int THREADS = F32 && KS <= kMxfMaxWideKS ? 1024 : kMxThreads;
-  static constexpr int WAVES = THREADS / 64;
-  static constexpr int W = F32 || WIN ? 32 * WAVES : kMxW;  // positions per slice
-  static constexpr int RB = W * 2 + 16;  // bf16: staged row stride in bytes, padded so rows 8 apart differ in bank
-  static constexpr int BS = Kp + 4;                  // fp32: floats per staged position
-  static constexpr size_t slice_bytes = F32 ? size_t(W) * BS * 4 : size_t(Kp) * RB;
-  // bf16 from 4 K steps on the staged rows allow one block per CU: registers for the K loop
-  // unrolled, so the LDS reads of one step overlap the products of the previous one
-  static constexpr int WPE = !F32 && KS >= 4 ? 2 : 4;
-  static constexpr int UNR = !F32 && KS >= 4 ? KS : 1;
-  static_assert(!F32 || (W / 2) % 128 == 0, "fp32 staging: two positions per thread, whole waves per row group");
+  static constexpr int AP = Kp + 8;       // plane row stride (bf16): 16-byte rows, staggered banks
+  static constexpr int W = 32 * PW;       // positions per tile
+  // registers: B (4 NP PW KS; fp32 splits take some more), accumulators (16 PW), one K step
+  // of A (12), addresses
+  static constexpr int REGS = (F32 ? 15 : 4) * PW * KS + 16 * PW + 12 + 40;
+  static constexpr int WPE = REGS <= 128 ? 4 : (REGS <= 168 ? 3 : 2);
 };
 
-// LDS: [ slice region ][ Ap: CW/32 tiles x 3 planes x 32 rows x AP bf16 ]
-//      [ rdesc: 2 int64 per row ][ map: N int32 ][ slotc: slots int32 ][ code: J*delta int32 ]
-// The coefficient rows are first assembled in fp32 over the slice region, then split into Ap.
-template <typename GT, int KS, int CW>
-__global__ __launch_bounds__((MxLayout<GT, KS, CW>::THREADS)) __attribute__((amdgpu_waves_per_eu(MxLayout<GT, KS, CW>::WPE))) void encode_mx_kernel(
-    MxArgs a) {
-  using Lay = MxLayout<GT, KS, CW>;
-  constexpr int NTH = Lay::THREADS;
-  constexpr bool F32 = Lay::F32;
-  constexpr int Kp = Lay::Kp;
-  constexpr int AP = Kp + 8;  // plane row stride (bf16): 16-byte aligned rows, staggered banks
-  extern __shared__ __align__(16) unsigned char lds[];
-  unsigned char *Gs = lds;
-  uint16_t *Ap = reinterpret_cast<uint16_t *>(lds + Lay::slice_bytes);
-  int64_t *rdesc = reinterpret_cast<int64_t *>(Ap + Lay::NT * 3 * 32 * AP);
-  int32_t *map = reinterpret_cast<int32_t *>(rdesc + 2 * Kp);
-  int32_t *slotc = map + a.N;
-  int32_t *code = slotc + a.slots;
-  float *Af = reinterpret_cast<float *>(Gs);  // [CW][Kp] fp32, before the slices are staged
-  static_assert(size_t(CW) * Kp * 4 <= Lay::slice_bytes, "coefficient rows fit the slice region");
-  __shared__ int nslot_s, nuni_s, nsend_s;
-  __shared__ int8_t ccomp_s[CW];    // compacted row of each candidate, or -1
-  // each compacted row's element offset in T from the window's first row (pattern p0,
-  // worker j0): (pb * m + jb) * L; read two at a time by the stores
-  __shared__ __align__(16) int64_t rowoff_s[CW];
+// The window's rows at the positions of one tile, term by term over the processed prefix in
+// order, on the vector units: what a row has not processed does not enter it.  For tiles whose
+// gradients are not all finite only.
+template <typename GT>
+__device__ __forceinline__ void mx_tile_terms(const MxArgs &a, int64_t p0, int j0, int nsend,
+                                              const int16_t *crow, const int16_t *cnp, int64_t x0, int64_t x1) {
+  const GT *G = static_cast<const GT *>(a.G);
+  for (int c = 0; c < nsend; ++c) {
+    const int r = __builtin_amdgcn_readfirstlane(crow[c]), np = __builtin_amdgcn_readfirstlane(cnp[c]);
+    const int pb = r / a.J, j = j0 + r - pb * a.J;
+    const int64_t row = (p0 + pb) * a.m + j;
+    const int32_t *ord = a.order + int64_t(j) * a.delta;
+    const float *coef = a.Bc + row * a.delta * a.ell;
+    for (int64_t x = x0 + threadIdx.x % kWave; x < x1; x += kWave) {
+      float acc = 0.f;
+      for (int k = 0; k < a.ell; ++k) {  // block k of a gradient, zero from d on
+        const int64_t col = int64_t(k) * a.L + x;
+        const bool in = col < a.d;
+        const GT *gx = G + (in ? col : 0);
+#pragma unroll 4
+        for (int t = 0; t < np; ++t) {  // loads unconditional, so that several are in flight
+          const int ch = ord[t];
+          const bool ok = ch >= 0 && ch < a.N;
+          const GT v = gx[int64_t(ok ? ch : 0) * a.d];
+          float g;
+          if constexpr (sizeof(GT) == 4) g = v;
+          else g = bf16_to_f32(v);
+          const float w = coef[t * a.ell + k];
+          acc = fmaf(ok ? w : 0.f, ok && in ? g : 0.f, acc);
+        }
+      }
+      a.T[row * a.L + x] = acc;
+    }
+  }
+}
 
-  // block -> (slice range, unit = (group, pattern tile)); XCD x takes ranges x, x + 8, ...
+// LDS: [ planes: CW/32 tiles x 3 x 32 rows x AP bf16 ][ base, lim: Kp int64 each ]
+//      [ rowoff: CW int64 ][ code: J*delta int32 ][ slotc: slots int32 ][ map: N int32 (J > 1) ]
+//      [ crow, cnp: CW int16 each ]
+template <typename GT, int KS, int PW>
+__global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(MxLayout<GT, KS, PW>::WPE))) void
+encode_mx_kernel(MxArgs a) {
+  using Lay = MxLayout<GT, KS, PW>;
+  constexpr bool F32 = Lay::F32;
+  constexpr int NP = Lay::NP, Kp = Lay::Kp, AP = Lay::AP, W = Lay::W;
+  using VT = typename Floats<PW>::T;
+  extern __shared__ __align__(16) unsigned char lds[];
+  uint16_t *Ap = reinterpret_cast<uint16_t *>(lds);
+  int64_t *base = reinterpret_cast<int64_t *>(lds + size_t(a.CW) * 3 * AP * 2);  // [2][Kp / 2]
+  int64_t *lim = base + Kp;
+  int64_t *rowoff = lim + Kp;
+  int32_t *code = reinterpret_cast<int32_t *>(rowoff + a.CW);
+  int32_t *slotc = code + a.J * a.delta;
+  int32_t *map = slotc + a.slots;
+  int16_t *crow = reinterpret_cast<int16_t *>(map + (a.J > 1 ? a.N : 0));
+  int16_t *cnp = crow + a.CW;
+  __shared__ int wcnt[kMxThreads / kWave];
+  __shared__ int nuni_s, jn_s;
+
+  // block -> (position range, unit = (group, pattern window)); XCD x takes ranges x, x + 8, ...
+  const int nth = blockDim.x;
   const int64_t b = blockIdx.x;
   const int64_t units = int64_t(a.ngroups) * a.ntp;
   const int64_t sr = (b & 7) + 8 * ((b >> 3) / units);
   const int64_t unit = (b >> 3) % units;
-  const int64_t s_begin = sr * a.spb;
-  const int64_t s_end = s_begin + a.spb < a.nslices ? s_begin + a.spb : a.nslices;
-  if (s_begin >= s_end) return;  // the whole block: an empty range at the end
-  const int gi = int(unit % a.ngroups);
+  const int64_t t_begin = sr * a.tpb;
+  const int64_t t_end = t_begin + a.tpb < a.ntiles ? t_begin + a.tpb : a.ntiles;
+  if (t_begin >= t_end) return;  // the whole block: an empty range at the end
   const int64_t p0 = (unit / a.ngroups) * a.PB;
-  const int j0 = gi * a.J;
+  const int j0 = int(unit % a.ngroups) * a.J;
   const int nj = a.m - j0 < a.J ? a.m - j0 : a.J;
   const int ell = a.ell;
   float *const Tw = a.T + (p0 * a.m + j0) * a.L;  // row (pattern p0, worker j0) of T
   const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), nw = nth / kWave;
   const int lane = tid % kWave, h = lane >> 5, li = lane & 31;
 
-  // which chunks the whole group uses; if they exceed the slots, one worker per pass
-  for (int c = tid; c < a.N; c += NTH) map[c] = 0;
-  __syncthreads();
-  for (int e = tid; e < nj * a.delta; e += NTH) {
-    const int c = a.order[int64_t(j0) * a.delta + e];
-    if (c >= 0 && c < a.N) map[c] = 1;
-  }
-  __syncthreads();
-  if (tid < kWave) {
-    int cnt = 0;
-    for (int base = 0; base < a.N; base += kWave) {
-      const int c = base + tid;
-      const unsigned long long mk = __ballot(c < a.N && map[c] != 0);
-      cnt += __popcll(mk);
-    }
-    if (tid == 0) nuni_s = cnt;
-  }
-  __syncthreads();
-  const bool split = nuni_s > a.slots;
-  const int npass = split ? nj : 1;
-
-  for (int pass = 0; pass < npass; ++pass) {
-    // active workers of this pass: all nj, or worker jb = pass
-    const int ja = split ? pass : 0, jn = split ? pass + 1 : nj;
-    __syncthreads();  // the previous pass is done with every table
-    for (int c = tid; c < a.N; c += NTH) map[c] = 0;
+  // Passes over the group's workers, each with the slots of its workers' distinct chunks.  One
+  // worker: slot t = position t.  Else one pass where every worker's chunks together fit the
+  // slots (slots in ascending chunk order; the cyclic order always does), and as many
+  // consecutive workers per pass as fit elsewhere.
+  int nuni = a.slots + 1;
+  if (a.J > 1) {
+    for (int c = tid; c < a.N; c += nth) map[c] = -1;
     __syncthreads();
-    for (int e = tid; e < (jn - ja) * a.delta; e += NTH) {
-      const int c = a.order[int64_t(j0 + ja) * a.delta + e];
-      if (c >= 0 && c < a.N) map[c] = 1;
+    for (int e = tid; e < nj * a.delta; e += nth) {
+      const int c = a.order[int64_t(j0) * a.delta + e];
+      if (c >= 0 && c < a.N) map[c] = 0;
     }
     __syncthreads();
-    // slots in ascending chunk order
     if (tid < kWave) {
       int cnt = 0;
-      for (int base = 0; base < a.N; base += kWave) {
-        const int c = base + tid;
-        const bool on = c < a.N && map[c] != 0;
+      for (int c0 = 0; c0 < a.N; c0 += kWave) {
+        const int c = c0 + tid;
+        const bool on = c < a.N && map[c] == 0;
         const unsigned long long mk = __ballot(on);
+        const int s = cnt + __popcll(mk & ((1ull << tid) - 1));
         if (on) {
-          const int s = cnt + __popcll(mk & ((1ull << tid) - 1));
-          map[c] = s;  // < slots: the active set fits by construction
-          slotc[s] = c;
-        } else if (c < a.N) {
-          map[c] = -1;
+          map[c] = s;
+          if (s < a.slots) slotc[s] = c;
         }
         cnt += __popcll(mk);
       }
-      if (tid == 0) nslot_s = cnt;
+      if (tid == 0) nuni_s = cnt;
     }
     __syncthreads();
-    const int nslot = nslot_s;
-    const int K = nslot * ell;
-    // per (worker, position): the slot of the chunk there, or -1
-    for (int e = tid; e < nj * a.delta; e += NTH) {
-      const int jb = e / a.delta;
-      const int c = a.order[int64_t(j0 + jb) * a.delta + e % a.delta];
-      code[e] = (jb >= ja && jb < jn && c >= 0 && c < a.N) ? map[c] : -1;
-    }
-    // the transmitting candidates of the pass, compacted in candidate order
-    if (tid < kWave) {
-      int cnt = 0;
-      for (int r0 = 0; r0 < CW; r0 += kWave) {
-        const int r = r0 + tid, pb = r / a.J, jb = r % a.J;
-        const int64_t p = p0 + pb;
-        const bool on = pb < a.PB && p < a.P && jb >= ja && jb < jn && a.psi[p * a.m + j0 + jb] > 0;
-        const unsigned long long mk = __ballot(on);
-        const int c = cnt + __popcll(mk & ((1ull << tid) - 1));
-        ccomp_s[r] = on ? int8_t(c) : int8_t(-1);
-        if (on) rowoff_s[c] = (int64_t(pb) * a.m + jb) * a.L;
-        cnt += __popcll(mk);
+    nuni = nuni_s;
+  }
+  for (int ja = 0, jn = nj; ja < nj; ja = jn) {  // workers ja .. jn - 1 of the group
+    int nslot = nuni;
+    __syncthreads();  // the previous pass is done with every table
+    if (nuni > a.slots) {
+      jn = ja + 1;
+      nslot = a.delta;
+      if (a.J > 1) {
+        for (int c = tid; c < a.N; c += nth) map[c] = -1;
+        for (int e = ja * a.delta + tid; e < nj * a.delta; e += nth) code[e] = a.order[int64_t(j0) * a.delta + e];
+        __syncthreads();
+        if (tid < kWave) {
+          int cnt = 0, j = ja;
+          for (; j < nj; ++j) {
+            const int c = lane < a.delta ? code[j * a.delta + lane] : -1;  // delta <= 64
+            const bool fresh = c >= 0 && c < a.N && map[c] < 0;
+            const unsigned long long mk = __ballot(fresh);
+            if (cnt + __popcll(mk) > a.slots) break;  // never at j = ja: delta <= slots
+            const int s = cnt + __popcll(mk & ((1ull << lane) - 1));
+            if (fresh) {
+              map[c] = s;
+              slotc[s] = c;
+            }
+            cnt += __popcll(mk);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+          }
+          if (tid == 0) {
+            nuni_s = cnt;
+            jn_s = j;
+          }
+        }
+        __syncthreads();
+        nslot = nuni_s;
+        jn = jn_s;
       }
-      if (tid == 0) nsend_s = cnt;
     }
-    for (int e = tid; e < CW * Kp; e += NTH) Af[e] = 0.f;
+    for (int e = tid; e < nj * a.delta; e += nth) {  // the slot at each (worker, position), or -1
+      const int jb = e / a.delta, t = e - jb * a.delta;
+      const int c = a.order[int64_t(j0) * a.delta + e];
+      const bool ok = jb >= ja && jb < jn && c >= 0 && c < a.N;
+      code[e] = !ok ? -1 : (a.J == 1 ? t : map[c]);
+      if (a.J == 1) slotc[t] = ok ? c : 0;
+    }
+    const int K = nslot * ell;  // rows of B
+    // the transmitting candidates (pattern p0 + r / J, worker j0 + r % J), compacted in order
+    bool on = false;
+    int np = 0, pb = 0, jb = 0;
+    if (tid < a.CW) {
+      pb = tid / a.J;
+      jb = tid - pb * a.J;
+      if (pb < a.PB && p0 + pb < a.P && jb >= ja && jb < jn) np = a.psi[(p0 + pb) * a.m + j0 + jb];
+      np = np < 0 ? 0 : (np > a.delta ? a.delta : np);
+      on = np > 0;
+    }
+    const unsigned long long mk = __ballot(on);
+    if (lane == 0) wcnt[wave] = __popcll(mk);
     __syncthreads();
-    const int nsend = nsend_s;
-    const int ntile = (nsend + 31) / 32;
-    // compacted row c (candidate (pattern p0 + r / J, worker j0 + r % J)), column s*ell + k:
-    // zero past the row's processed prefix
-    for (int e = tid; e < CW * a.delta; e += NTH) {
-      const int r = e / a.delta, t = e % a.delta;
-      const int c = ccomp_s[r];
-      if (c < 0) continue;
-      const int jb = r % a.J;
-      const int64_t p = p0 + r / a.J;
-      const int s = code[jb * a.delta + t];
-      if (s < 0) continue;
-      int v = a.psi[p * a.m + j0 + jb];
-      v = v < 0 ? 0 : (v > a.delta ? a.delta : v);
-      if (t >= v) continue;
-      const float *src = a.Bc + ((p * a.m + j0 + jb) * a.delta + t) * ell;
-      for (int k = 0; k < ell; ++k) Af[c * Kp + s * ell + k] = src[k];
+    int c0 = 0, nsend = 0;
+    for (int w = 0; w < nw; ++w) {
+      if (w < wave) c0 += wcnt[w];
+      nsend += wcnt[w];
     }
+    if (on) {
+      const int c = c0 + __popcll(mk & ((1ull << lane) - 1));
+      crow[c] = int16_t(tid);
+      cnp[c] = int16_t(np);
+      rowoff[c] = (int64_t(pb) * a.m + jb) * a.L;
+    }
+    // row kk of B: half kk % 2, place kk / 2 (a place past K repeats row 0, with zero
+    // coefficients): its element offset in G and the end of its valid positions
+    for (int e = tid; e < Kp; e += nth) {
+      const int kk = e < K ? e : 0;
+      const int s = kk / ell, k = kk - s * ell;
+      const int64_t rem = a.d - int64_t(k) * a.L;
+      const int q = (e & 1) * (Kp / 2) + (e >> 1);
+      base[q] = int64_t(K > 0 ? slotc[s] : 0) * a.d + (rem > 0 ? int64_t(k) * a.L : 0);
+      lim[q] = rem < a.L ? rem : a.L;
+    }
+    const int ntile = (nsend + 31) / 32;
+    for (int e = tid; e < ntile * (3 * 32 * AP / 8); e += nth)
+      reinterpret_cast<uint4 *>(Ap)[e] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     // three bf16 planes per row tile: a1 = bf16(a), a2 = bf16(a - a1), a3 = bf16(a - a1 - a2),
-    // all exact steps
-    for (int e = tid; e < 32 * ntile * Kp; e += NTH) {
-      const int c = e / Kp, kk = e % Kp;
-      const int rt = c / 32, r = c % 32;
-      const float v = Af[e];
-      const uint32_t b1 = bf16_rne(v);
-      const float r1 = v - __uint_as_float(b1 << 16);
-      const uint32_t b2 = bf16_rne(r1);
-      const float r2 = r1 - __uint_as_float(b2 << 16);
-      const uint32_t b3 = bf16_rne(r2);
-      uint16_t *tp = Ap + rt * 3 * 32 * AP;
-      tp[(0 * 32 + r) * AP + kk] = uint16_t(b1);
-      tp[(1 * 32 + r) * AP + kk] = uint16_t(b2);
-      tp[(2 * 32 + r) * AP + kk] = uint16_t(b3);
-    }
-    // staged rows: element offset of block k of slot s's chunk, and the end of its valid
-    // positions min(L, d - k L)
-    for (int row = tid; row < K; row += NTH) {
-      const int s = row / ell, k = row % ell;
-      rdesc[2 * row] = int64_t(slotc[s]) * a.d + int64_t(k) * a.L;
-      const int64_t rem = a.d - int64_t(k) * a.L;
-      rdesc[2 * row + 1] = rem < a.L ? rem : a.L;
-    }
-    __syncthreads();  // Af consumed: the slice region is free
-    // bf16: rows K .. Kp of the slice region stay zero for the whole pass (fp32: the
-    // staging writes them)
-    if constexpr (!F32)
-      for (int e = tid; e < (Kp - K) * (Lay::RB / 16); e += NTH)
-        reinterpret_cast<uint4 *>(Gs + size_t(K) * Lay::RB)[e] = make_uint4(0u, 0u, 0u, 0u);
-    if (ntile == 0) continue;  // nothing transmitted in this window: no slice to stage
-
-    for (int64_t slice = s_begin; slice < s_end; ++slice) {
-      const int64_t x0 = slice * Lay::W;
-      __syncthreads();  // the previous slice is consumed
-      if constexpr (F32) {
-        // stage: a thread takes positions xp, xp + 1 and groups of 8 staged rows, and writes
-        // each position's 8 values as two 16-byte words (zero past L, d or K)
-        float *Bf = reinterpret_cast<float *>(Gs);
-        const float *Gf = static_cast<const float *>(a.G);
-        const int xp = 2 * (tid % (Lay::W / 2));
-        const int64_t x = x0 + xp;
-#pragma unroll 1
-        for (int g = tid / (Lay::W / 2); g < Kp / 8; g += (NTH / (Lay::W / 2))) {
-          float v0[8], v1[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const int kk = 8 * g + i;
-            v0[i] = 0.f;
-            v1[i] = 0.f;
-            if (kk < K) {
-              const int64_t base = rdesc[2 * kk], lim = rdesc[2 * kk + 1];
-              if (a.stage16 && x + 2 <= lim) {
-                const float2 u = *reinterpret_cast<const float2 *>(Gf + base + x);
-                v0[i] = u.x;
-                v1[i] = u.y;
-              } else {
-                if (x < lim) v0[i] = Gf[base + x];
-                if (x + 1 < lim) v1[i] = Gf[base + x + 1];
-              }
-            }
-          }
-          float *d0 = Bf + xp * Lay::BS + 8 * g, *d1 = d0 + Lay::BS;
-          *reinterpret_cast<float4 *>(d0) = make_float4(v0[0], v0[1], v0[2], v0[3]);
-          *reinterpret_cast<float4 *>(d0 + 4) = make_float4(v0[4], v0[5], v0[6], v0[7]);
-          *reinterpret_cast<float4 *>(d1) = make_float4(v1[0], v1[1], v1[2], v1[3]);
-          *reinterpret_cast<float4 *>(d1 + 4) = make_float4(v1[4], v1[5], v1[6], v1[7]);
-        }
-      } else {
-        // stage: staged row `row` <- W positions of its block from x0 (zero past L or d),
-        // straight from memory to LDS: one wave instruction per row, lane i filling bytes
-        // 16i .. 16i + 15 (256-wide slices: lanes 0 .. 31)
-        const uint16_t *Gh = static_cast<const uint16_t *>(a.G);
-        for (int row = wave; row < K && (!Lay::WIN || lane < 32); row += Lay::WAVES) {
-          const int64_t base = rdesc[2 * row], lim = rdesc[2 * row + 1];
-          const int64_t x = x0 + 8 * lane;
-          unsigned char *dst = Gs + size_t(row) * Lay::RB;
-          if (a.stage16 && x0 + Lay::W <= lim) {
-            __builtin_amdgcn_global_load_lds(Gh + base + x, dst, 16, 0, 0);
-          } else {
-            uint32_t w[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const uint32_t lo = x + 2 * q < lim ? Gh[base + x + 2 * q] : 0u;
-              const uint32_t hi = x + 2 * q + 1 < lim ? Gh[base + x + 2 * q + 1] : 0u;
-              w[q] = lo | (hi << 16);
-            }
-            *reinterpret_cast<uint4 *>(dst + 16 * lane) = make_uint4(w[0], w[1], w[2], w[3]);
-          }
-        }
-        __builtin_amdgcn_s_waitcnt(0);  // this wave's direct-to-LDS loads have landed
+    // all exact steps; row kk at column 16 (kk / 16) + 8 (kk % 2) + (kk % 16) / 2
+    for (int e = tid; e < nsend * a.delta; e += nth) {
+      const int c = e / a.delta, t = e - c * a.delta;
+      if (t >= cnp[c]) continue;
+      const int rpb = crow[c] / a.J, rjb = crow[c] - rpb * a.J;
+      const int s = code[rjb * a.delta + t];
+      if (s < 0) continue;
+      const float *src = a.Bc + (((p0 + rpb) * a.m + j0 + rjb) * a.delta + t) * ell;
+      uint16_t *tp = Ap + (c / 32) * (3 * 32 * AP) + (c % 32) * AP;
+      for (int k = 0; k < ell; ++k) {
+        const int kk = s * ell + k;
+        const int col = (kk & ~15) + 8 * (kk & 1) + ((kk & 15) >> 1);
+        const float v = src[k];
+        const uint32_t b1 = bf16_rne(v);
+        const float r1 = v - __uint_as_float(b1 << 16);
+        const uint32_t b2 = bf16_rne(r1);
+        const float r2 = r1 - __uint_as_float(b2 << 16);
+        tp[col] = uint16_t(b1);
+        tp[32 * AP + col] = uint16_t(b2);
+        tp[64 * AP + col] = uint16_t(bf16_rne(r2));
       }
-      __syncthreads();  // the slice is staged
+    }
+    __syncthreads();
 
-      if constexpr (F32) {
-        // one 32-position tile per wave (x0 + 32 wave + li), every row tile in one K loop so
-        // that each staged value is split once
-        const float *Bw = reinterpret_cast<const float *>(Gs) + (32 * wave + li) * Lay::BS + 8 * h;
-        auto tiles = [&](auto ntc) {
-          constexpr int NT = decltype(ntc)::value;
-          v16f acc[NT];
+    const int64_t *bh = base + h * (Kp / 2), *lh = lim + h * (Kp / 2);
+    unsigned long long terms = 0;  // this wave's tiles left to the term-by-term sums (the last bit: and all after)
+    int step = 0;
+    for (int64_t tl = t_begin + wave; tl < t_end; tl += nw, ++step) {
+      const int64_t x0 = tl * W, x = x0 + li * PW;  // this lane's positions x .. x + PW - 1
+      v8bf bf[KS][PW][NP];
+      // every load of the tile in flight before the first is used; past a row's valid
+      // positions (EDGE: the last tiles) zeros, loaded from the row's start
+      auto load = [&](auto edge_c) {
+        constexpr bool EDGE = decltype(edge_c)::value;
+        if constexpr (F32) {
+          const float *G = static_cast<const float *>(a.G);
+          float raw[KS][PW][8];
 #pragma unroll
-          for (int t = 0; t < NT; ++t) acc[t] = v16f{};
-#pragma unroll 1
-          for (int q = 0; q < KS; ++q) {
-            const float4 u0 = *reinterpret_cast<const float4 *>(Bw + 16 * q);
-            const float4 u1 = *reinterpret_cast<const float4 *>(Bw + 16 * q + 4);
-            v8bf g1, g2, g3;
-            split3(u0, u1, g1, g2, g3);
-            const int kb = 16 * q + 8 * h;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-              const uint16_t *At = Ap + t * 3 * 32 * AP;
-              const v8bf a1 = *reinterpret_cast<const v8bf *>(At + (0 * 32 + li) * AP + kb);
-              const v8bf a2 = *reinterpret_cast<const v8bf *>(At + (1 * 32 + li) * AP + kb);
-              const v8bf a3 = *reinterpret_cast<const v8bf *>(At + (2 * 32 + li) * AP + kb);
-              // the six products of parts above 2^-24 relative, smallest first
-              acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3, g1, acc[t], 0, 0, 0);
-              acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, g2, acc[t], 0, 0, 0);
-              acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, g3, acc[t], 0, 0, 0);
-              acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, g1, acc[t], 0, 0, 0);
-              acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, g2, acc[t], 0, 0, 0);
-              acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, g1, acc[t], 0, 0, 0);
-            }
-          }
-          const int64_t xa = x0 + 32 * wave + li;
-          if (xa >= a.L) return;
-          // lane (h, li) holds D[8(v/4) + 4h + v%4][li]: rows 32t + 8g + 4h + i, their
-          // offsets read four at a time (two 16-byte reads)
-          float *Tx = Tw + xa;
-#pragma unroll
-          for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              const int cb = 32 * t + 8 * g + 4 * h;
-              const longlong2 o0 = *reinterpret_cast<const longlong2 *>(rowoff_s + cb);
-              const longlong2 o1 = *reinterpret_cast<const longlong2 *>(rowoff_s + cb + 2);
-              const int64_t off[4] = {o0.x, o0.y, o1.x, o1.y};
-#pragma unroll
-              for (int i = 0; i < 4; ++i)
-                if (cb + i < nsend) __builtin_nontemporal_store(acc[t][4 * g + i], Tx + off[i]);
-            }
-        };
-        if (ntile == 2)
-          tiles(std::integral_constant<int, 2>{});
-        else
-          tiles(std::integral_constant<int, 1>{});
-      } else if constexpr (Lay::WIN) {
-        // one 32-position tile per wave (x0 + 32 wave + li), every row tile in one K loop so
-        // that each gathered column feeds all of them
-        const uint16_t *Gc = reinterpret_cast<const uint16_t *>(Gs) + 32 * wave + li;
-        constexpr int GR = Lay::RB / 2;  // staged row stride in bf16
-        auto tiles = [&](auto ntc) {
-          constexpr int NT = decltype(ntc)::value;
-          v16f acc[NT];
-#pragma unroll
-          for (int t = 0; t < NT; ++t) acc[t] = v16f{};
-#pragma unroll Lay::UNR
-          for (int q = 0; q < KS; ++q) {
-            const int kb = 16 * q + 8 * h;
-            v8bf bq;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) bq[i] = __builtin_bit_cast(__bf16, Gc[(kb + i) * GR]);
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-              const uint16_t *At = Ap + t * 3 * 32 * AP;
-              const v8bf a1 = *reinterpret_cast<const v8bf *>(At + (0 * 32 + li) * AP + kb);
-              const v8bf a2 = *reinterpret_cast<const v8bf *>(At + (1 * 32 + li) * AP + kb);
-              const v8bf a3 = *reinterpret_cast<const v8bf *>(At + (2 * 32 + li) * AP + kb);
-              acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3, bq, acc[t], 0, 0, 0);
-              acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, bq, acc[t], 0, 0, 0);
-              acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, bq, acc[t], 0, 0, 0);
-            }
-          }
-          const int64_t xa = x0 + 32 * wave + li;
-          if (xa >= a.L) return;
-          // lane (h, li) holds D[8(v/4) + 4h + v%4][li]: rows 32t + 8g + 4h + i, their
-          // offsets read four at a time (two 16-byte reads)
-          float *Tx = Tw + xa;
-#pragma unroll
-          for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              const int cb = 32 * t + 8 * g + 4 * h;
-              const longlong2 o0 = *reinterpret_cast<const longlong2 *>(rowoff_s + cb);
-              const longlong2 o1 = *reinterpret_cast<const longlong2 *>(rowoff_s + cb + 2);
-              const int64_t off[4] = {o0.x, o0.y, o1.x, o1.y};
-#pragma unroll
-              for (int i = 0; i < 4; ++i)
-                if (cb + i < nsend) __builtin_nontemporal_store(acc[t][4 * g + i], Tx + off[i]);
-            }
-        };
-        if (ntile == 1)
-          tiles(std::integral_constant<int, 1>{});
-        else if (ntile == 2)
-          tiles(std::integral_constant<int, 2>{});
-        else if (ntile == 3)
-          tiles(std::integral_constant<int, 3>{});
-        else
-          tiles(std::integral_constant<int, Lay::NT>{});
-      } else {
-        // per row tile, two 32 x 32 tiles per wave: positions x0 + 64 wave + 32 c + li
-        const uint16_t *Gc = reinterpret_cast<const uint16_t *>(Gs) + 64 * wave + li;
-        constexpr int GR = Lay::RB / 2;  // staged row stride in bf16
-        for (int rt = 0; rt < ntile; ++rt) {
-          const uint16_t *At = Ap + rt * 3 * 32 * AP;
-          v16f acc0 = {}, acc1 = {};
-#pragma unroll Lay::UNR
-          for (int q = 0; q < KS; ++q) {
-            const int kb = 16 * q + 8 * h;
-            const v8bf a1 = *reinterpret_cast<const v8bf *>(At + (0 * 32 + li) * AP + kb);
-            const v8bf a2 = *reinterpret_cast<const v8bf *>(At + (1 * 32 + li) * AP + kb);
-            const v8bf a3 = *reinterpret_cast<const v8bf *>(At + (2 * 32 + li) * AP + kb);
-            v8bf b0, b1;
+          for (int q = 0; q < KS; ++q)
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-              b0[i] = __builtin_bit_cast(__bf16, Gc[(kb + i) * GR]);
-              b1[i] = __builtin_bit_cast(__bf16, Gc[(kb + i) * GR + 32]);
+              const float *src = G + bh[8 * q + i];
+              if constexpr (EDGE) {
+                const int64_t lm = lh[8 * q + i];
+#pragma unroll
+                for (int w = 0; w < PW; ++w) {
+                  const float v = src[x + w < lm ? x + w : 0];
+                  raw[q][w][i] = x + w < lm ? v : 0.f;
+                }
+              } else {
+                const VT v = *reinterpret_cast<const VT *>(src + x);
+                if constexpr (PW == 1) {
+                  raw[q][0][i] = v;
+                } else {
+#pragma unroll
+                  for (int w = 0; w < PW; ++w) raw[q][w][i] = v[w];
+                }
+              }
             }
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3, b0, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3, b1, acc1, 0, 0, 0);
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b0, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b1, acc1, 0, 0, 0);
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b0, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, acc1, 0, 0, 0);
+#pragma unroll
+          for (int q = 0; q < KS; ++q)
+#pragma unroll
+            for (int w = 0; w < PW; ++w) split3(raw[q][w], bf[q][w]);
+        } else {
+          static_assert(F32 || PW % 2 == 0, "bf16: pairs of positions");
+          constexpr int PP = F32 ? 1 : PW / 2;
+          const uint16_t *G = static_cast<const uint16_t *>(a.G);
+          uint32_t raw[KS][8][PP];
+#pragma unroll
+          for (int q = 0; q < KS; ++q)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+              const uint16_t *src = G + bh[8 * q + i];
+              if constexpr (EDGE) {
+                const int64_t lm = lh[8 * q + i];
+#pragma unroll
+                for (int w = 0; w < PP; ++w) {
+                  const int64_t y = x + 2 * w;
+                  const uint32_t lo = src[y < lm ? y : 0], hi = src[y + 1 < lm ? y + 1 : 0];
+                  raw[q][i][w] = (y < lm ? lo : 0u) | (y + 1 < lm ? hi << 16 : 0u);
+                }
+              } else {
+                const auto v = *reinterpret_cast<const HalfPairs<PP> *>(src + x);
+#pragma unroll
+                for (int w = 0; w < PP; ++w) raw[q][i][w] = v.v[w];
+              }
+            }
+#pragma unroll
+          for (int q = 0; q < KS; ++q)
+#pragma unroll
+            for (int w = 0; w < PP; ++w) {
+              v4u e, o;  // the pair's even and odd position
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                e[j] = __builtin_amdgcn_perm(raw[q][2 * j + 1][w], raw[q][2 * j][w], 0x05040100u);
+                o[j] = __builtin_amdgcn_perm(raw[q][2 * j + 1][w], raw[q][2 * j][w], 0x07060302u);
+              }
+              bf[q][2 * w][0] = __builtin_bit_cast(v8bf, e);
+              bf[q][2 * w + 1][0] = __builtin_bit_cast(v8bf, o);
+            }
+        }
+      };
+      if (x0 + W <= a.lmin) load(std::false_type{});
+      else load(std::true_type{});
+      // a sum that is a NaN once a value loaded is not finite
+      float chk[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int q = 0; q < KS; ++q)
+#pragma unroll
+        for (int w = 0; w < PW; ++w) {
+          const v4u top = __builtin_bit_cast(v4u, bf[q][w][0]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) chk[j] = times_zero(top[j], chk[j]);
+        }
+      const float nan_if_bad = (chk[0] + chk[1]) + (chk[2] + chk[3]);
+      if (__any(nan_if_bad != nan_if_bad)) {
+        terms |= 1ull << (step < 63 ? step : 63);
+        continue;
+      }
+      const bool inside = x0 + W <= a.L;
+      float *Tx = Tw + x;
+#pragma unroll 1
+      for (int rt = 0; rt < ntile; ++rt) {
+        const uint16_t *At = Ap + rt * (3 * 32 * AP) + li * AP + 8 * h;
+        v16f acc[PW];
+#pragma unroll
+        for (int w = 0; w < PW; ++w) acc[w] = v16f{};
+        auto mm = [&](const uint16_t *plane, int q, int part) {
+          const v8bf av = *reinterpret_cast<const v8bf *>(plane + 16 * q);
+#pragma unroll
+          for (int w = 0; w < PW; ++w)
+            acc[w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bf[q][w][part], acc[w], 0, 0, 0);
+        };
+        // the products of parts above 2^-24 relative; those below 2^-7 of the whole first, over
+        // all of K, so that only the last KS sums round at the result's own size
+#pragma unroll
+        for (int q = 0; q < KS; ++q) {
+          mm(At + 64 * AP, q, 0);
+          if constexpr (F32) {
+            mm(At + 32 * AP, q, 1);
+            mm(At, q, 2);
           }
-          // lane (h, li) holds D[8(v/4) + 4h + v%4][li] of each tile: rows 32 rt + 8g + 4h +
-          // i, their offsets read four at a time (two 16-byte reads)
-          const int64_t xa = x0 + 64 * wave + li, xb = xa + 32;
+          mm(At + 32 * AP, q, 0);
+          if constexpr (F32) mm(At, q, 1);
+        }
+#pragma unroll
+        for (int q = 0; q < KS; ++q) mm(At, q, 0);
+        // lane (h, li) holds D[8(v/4) + 4h + v%4][li] of each 32-wide tile: rows 32 rt + 8g + 4h
+        // + i, PW neighbouring positions each.  Non-temporal where rows start on 64-byte
+        // boundaries; elsewhere the pieces of a row meet inside a memory line, which plain
+        // stores let L2 put together (m = 37, L = 33335: 0.62 ms against 0.70)
+        auto value = [&](int v) {
+          VT o;
+          if constexpr (PW == 1) {
+            o = acc[0][v];
+          } else {
+#pragma unroll
+            for (int w = 0; w < PW; ++w) o[w] = acc[w][v];
+          }
+          return o;
+        };
+        const int64_t *ro = rowoff + 32 * rt + 4 * h;
+        auto full = [&](auto nt_c) {
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
-            const int cb = 32 * rt + 8 * g + 4 * h;
-            const longlong2 o0 = *reinterpret_cast<const longlong2 *>(rowoff_s + cb);
-            const longlong2 o1 = *reinterpret_cast<const longlong2 *>(rowoff_s + cb + 2);
+            const longlong2 o0 = *reinterpret_cast<const longlong2 *>(ro + 8 * g);
+            const longlong2 o1 = *reinterpret_cast<const longlong2 *>(ro + 8 * g + 2);
             const int64_t off[4] = {o0.x, o0.y, o1.x, o1.y};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              if (cb + i >= nsend) continue;
-              float *row = Tw + off[i];
-              if (xa < a.L) __builtin_nontemporal_store(acc0[4 * g + i], row + xa);
-              if (xb < a.L) __builtin_nontemporal_store(acc1[4 * g + i], row + xb);
+              VT *dst = reinterpret_cast<VT *>(Tx + off[i]);
+              if constexpr (decltype(nt_c)::value) __builtin_nontemporal_store(value(4 * g + i), dst);
+              else *dst = value(4 * g + i);
+            }
+          }
+        };
+        if (inside && 32 * rt + 32 <= nsend) {
+          if (a.nt) full(std::true_type{});
+          else full(std::false_type{});
+        } else {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const int c = 8 * (v >> 2) + (v & 3);
+            if (32 * rt + 4 * h + c >= nsend) continue;
+            float *dst = Tx + ro[c];
+            if (inside) {
+              *reinterpret_cast<VT *>(dst) = value(v);
+            } else {
+#pragma unroll
+              for (int w = 0; w < PW; ++w)
+                if (x + w < a.L) dst[w] = acc[w][v];
             }
           }
         }
       }
     }
+    for (int s = 0; terms >> (s < 63 ? s : 63); ++s) {
+      const int64_t x0 = (t_begin + wave + int64_t(s) * nw) * W;
+      if (x0 >= a.L || t_begin + wave + int64_t(s) * nw >= t_end) break;
+      if ((terms >> (s < 63 ? s : 63)) & 1)
+        mx_tile_terms<GT>(a, p0, j0, nsend, crow, cnp, x0, x0 + W < a.L ? x0 + W : a.L);
+    }
   }
 }
 
-template <typename GT, int KS, int CW>
-int launch_mx_ks(const MxArgs &m, size_t lds, hipStream_t st) {
-  if constexpr (CW == 128 && KS < kMxWinKS) {
-    return kEncodeMxNotApplicable;  // never planned: a 128-candidate window has as many K steps
-  } else {                          // as a 64-candidate one, or more
-    const int64_t blocks = m.nsr * m.ngroups * m.ntp;
-    constexpr int NTH = MxLayout<GT, KS, CW>::THREADS;
-    if (!grid_ok(blocks, NTH)) return GC_EINVAL;
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&encode_mx_kernel<GT, KS, CW>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
-      return GC_ELAUNCH;
-    hipLaunchKernelGGL((encode_mx_kernel<GT, KS, CW>), dim3(unsigned(blocks)), dim3(NTH), lds, st, m);
-    return GC_OK;
-  }
-}
-
-template <typename GT, int CW>
-int launch_mx(const MxArgs &a, int KS, size_t lds, hipStream_t st) {
-  switch (KS) {
-    case 1: return launch_mx_ks<GT, 1, CW>(a, lds, st);
-    case 2: return launch_mx_ks<GT, 2, CW>(a, lds, st);
-    case 3: return launch_mx_ks<GT, 3, CW>(a, lds, st);
-    case 4: return launch_mx_ks<GT, 4, CW>(a, lds, st);
-    case 5: return launch_mx_ks<GT, 5, CW>(a, lds, st);
-    case 6: return launch_mx_ks<GT, 6, CW>(a, lds, st);
-    default: return kEncodeMxNotApplicable;
-  }
+template <typename GT, int KS, int PW>
+int launch_mx(const MxArgs &a, int threads, hipStream_t st) {
+  const size_t lds = mx_lds(a, KS);
+  const int64_t blocks = a.nsr * a.ngroups * a.ntp;
+  if (!grid_ok(blocks, threads)) return GC_EINVAL;
+  if (hipFuncSetAttribute(reinterpret_cast<const void *>(&encode_mx_kernel<GT, KS, PW>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
+    return GC_ELAUNCH;
+  hipLaunchKernelGGL((encode_mx_kernel<GT, KS, PW>), dim3(unsigned(blocks)), dim3(threads), lds, st, a);
+  return GC_OK;
 }
 
 }  // namespace
@@ -574,6 +568,7 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
   a.N = N;
   a.d = d;
   a.L = ceil_div(d, ell);
+  a.lmin = std::max<int64_t>(0, d - int64_t(ell - 1) * a.L);
   a.psi = psi;
   a.order = order;
   a.Bc = Bc;
@@ -582,71 +577,82 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
   a.delta = delta;
   a.ell = ell;
   a.T = T;
-  const uintptr_t ga = reinterpret_cast<uintptr_t>(G);
-  a.stage16 = f32 ? (d % 2 == 0 && a.L % 2 == 0 && (ga & 7) == 0) : (d % 8 == 0 && a.L % 8 == 0 && (ga & 15) == 0);
-  // slots for the cyclic union of a group; a block whose union is larger walks its workers
-  // one at a time, each needing delta slots
-  auto union_slots = [&](int64_t J) {
-    int64_t sl = J + delta - 1;
-    if (sl > N) sl = N;
-    return sl < delta ? int64_t(delta) : sl;
-  };
-  // a window of cw candidate rows: PB patterns (a power of two covering the call, at most
-  // cw) x J workers, J halved while the group's cyclic union would need more than kMxMaxKS
-  // K steps
-  struct Plan {
-    int pb, J, KS, W;
-    int64_t slots;
-    size_t lds;
-  };
-  auto plan = [&](int cw, Plan &q) {
-    q.pb = 1;
-    while (q.pb < cw && q.pb < P) q.pb *= 2;
-    int64_t J = cw / q.pb;
-    if (J > m) J = m;
-    while (J > 1 && ceil_div(union_slots(J) * ell, 16) > kMxMaxKS) J /= 2;
-    q.J = int(J);
-    q.slots = union_slots(J);
-    const int64_t KS = ceil_div(q.slots * ell, 16);
-    if (KS > kMxMaxKS) return false;
-    q.KS = int(KS);
-    const int Kp = 16 * q.KS;
-    q.W = f32 ? (q.KS <= kMxfMaxWideKS ? 512 : 256) : (cw == 128 ? 256 : kMxW);
-    const size_t slice = f32 ? size_t(q.W) * (Kp + 4) * sizeof(float) : size_t(Kp) * (q.W * 2 + 16);
-    q.lds = slice + sizeof(uint16_t) * (cw / 32) * 3 * 32 * (Kp + 8) + 2 * sizeof(int64_t) * size_t(Kp) +
-            sizeof(int32_t) * (size_t(N) + q.slots + size_t(q.J) * delta);
-    return q.lds <= kMxLds;
-  };
-  Plan q{}, q2{};
-  const bool ok64 = plan(64, q);
-  // bf16: 128-candidate windows, which stage the group's chunks once for up to twice the
-  // rows, where a 64-candidate window would need kMxWinKS or more K steps and the larger
-  // window holds more candidates
-  const bool win = !f32 && (!ok64 || q.KS >= kMxWinKS) && plan(128, q2) &&
-                   (!ok64 || int64_t(q2.pb) * q2.J > int64_t(q.pb) * q.J);
-  if (win) q = q2;
-  else if (!ok64) return kEncodeMxNotApplicable;
-  a.PB = q.pb;
-  a.J = q.J;
-  a.ngroups = int(ceil_div(m, a.J));
-  a.ntp = ceil_div(P, q.pb);
-  a.slots = int(q.slots);
-  const int KS = q.KS, W = q.W;
-  const size_t lds = q.lds;
-  a.nslices = int(ceil_div(a.L, W));
-  // slice ranges: a multiple of 8 (one share per XCD), at least about 16 blocks per CU in
-  // all, and at most kMxSliceRun slices each
+  a.nt = a.L % 16 == 0 && (reinterpret_cast<uintptr_t>(T) & 63) == 0;
+  auto steps = [&](int64_t slots) { return ceil_div(slots * ell, 16); };
+  const int64_t max_steps = f32 ? kMxMaxKSF32 : kMxMaxKSBF16;
+  if (steps(delta) > max_steps) return kEncodeMxNotApplicable;
+  // Candidate rows per window: as many as the LDS allows, so that B is loaded and split
+  // for more rows (fp32, ell = 8: 64 / 128 / 256 rows 4.5 / 4.1 / 3.8 ms; bf16, ell = 4: 64 /
+  // 128 / 192 rows 2.4 / 2.1 / 2.05 ms).  With few K steps on rows that start anywhere 128 rows
+  // and four positions per lane (0.62 ms against 0.65 with 256 rows, 0.68 with two positions).
+  const bool small_odd = f32 && !a.nt && steps(delta) <= 2;
+  int KS = 0;
+  for (int cw = small_odd ? 128 : (f32 ? kMxMaxCW : 192);; cw -= 32) {
+    // one pattern window where P allows, else balanced ones; then workers while there is
+    // room.  J workers share J + delta - 1 chunks under the cyclic order, so for each count of
+    // K steps the most workers it holds, and of these the one with the least work per row: KS
+    // products per row tile, and for each K step loads and splits that cost about as much as
+    // 2.5 row tiles' products
+    a.PB = int(ceil_div(P, ceil_div(P, cw)));
+    a.ntp = ceil_div(P, a.PB);
+    const int64_t most = N <= kMxMapChunks ? std::min<int64_t>(cw / a.PB, m) : 1;
+    double best = 0;
+    for (int64_t k = steps(delta); k <= max_steps; ++k) {
+      int64_t J = std::max<int64_t>(1, std::min<int64_t>(16 * k / ell - delta + 1, most));
+      const int64_t groups = ceil_div(m, J);
+      J = ceil_div(m, groups);  // balanced groups
+      const int64_t ks = std::min<int64_t>(k, steps(std::min<int64_t>(J + delta - 1, std::max(N, delta))));
+      const double cost = double(ks) * double(2 * ceil_div(J * a.PB, 32) + 5) / double(J * a.PB);
+      if (best == 0 || cost < best) {
+        best = cost;
+        a.J = int(J);
+        a.ngroups = int(groups);
+        KS = int(ks);
+      }
+      if (J >= most || J >= m) break;
+    }
+    a.slots = a.J == 1 ? delta : std::min<int>(16 * KS / ell, std::max(N, delta));
+    a.CW = (a.J * a.PB + 31) & ~31;
+    if (mx_lds(a, KS) <= kMxLds || cw == 32) break;  // 32 rows always fit
+  }
+  // positions per lane, as registers allow (fp32: 12 PW per K step, bf16 4 PW; 16 PW sums)
+  const int pw = f32 ? (KS <= 2 ? (small_odd ? 4 : 2) : (KS <= 5 ? 2 : 1)) : (KS <= 8 ? 4 : 2);
+  const int threads = KS <= (f32 ? 2 : 3) ? 256 : 512;
+  const int nw = threads / kWave;
+  a.ntiles = ceil_div(a.L, int64_t(32) * pw);
+  // tiles per wave: the planes cost more to build with more K steps (2 up to 3 steps, else 8;
+  // m = 200 bf16 at ell = 1 2.67 ms against 2.77 with 4, at ell = 4 2.05 against 2.31 with 2),
+  // fewer while the grid is short of four blocks per CU
   const int64_t units = int64_t(a.ngroups) * a.ntp;
-  const int64_t want = 16 * int64_t(cu_count());
-  int64_t nsr = ceil_div(ceil_div(want, units), 8) * 8;
-  if (nsr > ceil_div(a.nslices, 8) * 8) nsr = ceil_div(a.nslices, 8) * 8;
-  a.spb = ceil_div(a.nslices, nsr);
-  // shorter runs while the grid stays within the launch limits (1024 threads per block at most)
-  if (a.spb > kMxSliceRun && ceil_div(ceil_div(a.nslices, kMxSliceRun), 8) * 8 * units <= 0xffffffffLL / 1024)
-    a.spb = kMxSliceRun;
-  a.nsr = ceil_div(ceil_div(a.nslices, a.spb), 8) * 8;
-  if (f32) return launch_mx<float, 64>(a, KS, lds, stream);
-  return win ? launch_mx<uint16_t, 128>(a, KS, lds, stream) : launch_mx<uint16_t, 64>(a, KS, lds, stream);
+  a.tpb = int64_t(nw) * (KS <= 3 ? 2 : 8);
+  while (a.tpb > nw && ceil_div(a.ntiles, a.tpb) * units < 4 * int64_t(cu_count())) a.tpb -= nw;
+  a.nsr = ceil_div(ceil_div(a.ntiles, a.tpb), 8) * 8;
+  while (a.nsr > 8 && a.nsr * units > 0xffffffffLL / kMxThreads) {  // the launch limits
+    a.tpb *= 2;
+    a.nsr = ceil_div(ceil_div(a.ntiles, a.tpb), 8) * 8;
+  }
+#define GC_BF16_CASE(K, PWN) \
+  case K: return launch_mx<uint16_t, K, PWN>(a, threads, stream);
+#define GC_F32_CASE(K, PWN) \
+  case K: return launch_mx<float, K, PWN>(a, threads, stream);
+  if (!f32) {
+    switch (KS) {
+      GC_BF16_CASE(1, 4) GC_BF16_CASE(2, 4) GC_BF16_CASE(3, 4) GC_BF16_CASE(4, 4) GC_BF16_CASE(5, 4)
+      GC_BF16_CASE(6, 4) GC_BF16_CASE(7, 4) GC_BF16_CASE(8, 4) GC_BF16_CASE(9, 2) GC_BF16_CASE(10, 2)
+      GC_BF16_CASE(11, 2) GC_BF16_CASE(12, 2)
+    }
+  } else if (pw == 4) {
+    switch (KS) { GC_F32_CASE(1, 4) GC_F32_CASE(2, 4) }
+  } else {
+    switch (KS) {
+      GC_F32_CASE(1, 2) GC_F32_CASE(2, 2) GC_F32_CASE(3, 2) GC_F32_CASE(4, 2) GC_F32_CASE(5, 2)
+      GC_F32_CASE(6, 1) GC_F32_CASE(7, 1) GC_F32_CASE(8, 1) GC_F32_CASE(9, 1) GC_F32_CASE(10, 1)
+      GC_F32_CASE(11, 1)
+    }
+  }
+#undef GC_BF16_CASE
+#undef GC_F32_CASE
+  return kEncodeMxNotApplicable;
 }
 
 }  // namespace gcx

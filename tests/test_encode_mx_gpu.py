@@ -1,0 +1,109 @@
+"""The matrix-core encode against the oracle at the edges of its plan: every count of K steps
+(16 rows of chunk blocks) of both storage types, rows of T on and off 16-byte and 64-byte
+boundaries, last blocks shorter than the others, fewer positions than a tile, one pattern
+(groups of workers), several (fewer workers per group) and more than a window; orders whose
+workers share no chunks; gradients that are not finite."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle.protocol as OP
+import oracle_runs as R_
+import test_parity_gpu as TP
+from workloads import gen
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+from paper_2405_19509_amd import gcx  # noqa: E402
+
+
+def problem(m, delta, d, P, g_dtype, seed=0, cyclic=True):
+    rng = np.random.default_rng([seed, m, delta, d, P])
+    if cyclic:
+        O, order, _, _ = gcx.gc_assign(gcx.GC_ASSIGN_CYCLIC, m, m, delta - 1)
+    else:
+        A = np.zeros((m, m), dtype=np.int32)
+        for j in range(m):
+            A[rng.permutation(m)[:delta], j] = rng.permutation(delta) + 1
+        O, order, _, _ = gcx.gc_assign(gcx.GC_ASSIGN_ORDER, m, m, O=A)
+    G = rng.standard_normal((m, d)).astype(np.float32)
+    if g_dtype == "bf16":
+        G = gen.f32_to_bf16_bits(G)
+    psi = rng.integers(0, delta + 1, size=(P, m)).astype(np.int32)
+    psi[:, rng.permutation(m)[: m // 6]] = 0
+    return O.astype(np.int64), order, G, psi
+
+
+# (m, delta, ell): 1 .. 12 K steps of the smallest window; the last of each type goes past them
+STEPS = [(100, 4, 1), (50, 16, 2), (34, 14, 3), (34, 14, 4), (26, 16, 5), (26, 16, 6), (26, 16, 7), (26, 16, 8),
+         (26, 18, 8), (26, 20, 8), (26, 22, 8), (26, 24, 8), (28, 25, 8)]
+
+
+@pytest.mark.parametrize("g_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,delta,ell", STEPS)
+def test_k_steps(m, delta, ell, g_dtype):
+    # 64-byte rows; odd rows with a short last block; rows on 16 but not on 64 bytes
+    for d, P in ((ell * 160, 3), (ell * 203 - 1, 7), (ell * 36, 33)):
+        O, order, G, psi = problem(m, delta, d, P, g_dtype)
+        TP._encode_against_oracle(O, order, psi, gen.shared_R(m, ell), G, g_dtype, ell, d)
+
+
+@pytest.mark.parametrize("g_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,delta,ell,d,P", [
+    (7, 3, 2, 9, 1), (7, 3, 8, 5, 2),        # blocks of a few positions, some of them empty
+    (12, 5, 1, 129, 260), (12, 5, 2, 257, 193),  # one row more than a window's
+    (110, 2, 1, 131, 5), (110, 2, 1, 128, 64),   # K steps that hold more workers than a window
+])
+def test_windows(m, delta, ell, d, P, g_dtype):
+    O, order, G, psi = problem(m, delta, d, P, g_dtype, seed=1)
+    TP._encode_against_oracle(O, order, psi, gen.shared_R(m, ell), G, g_dtype, ell, d)
+
+
+@pytest.mark.parametrize("g_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("P", [1, 6, 40])
+@pytest.mark.parametrize("ell", [1, 3])
+def test_orders_without_shared_chunks(ell, P, g_dtype):
+    m, delta, d = 120, 9, 301
+    O, order, G, psi = problem(m, delta, d, P, g_dtype, seed=2, cyclic=False)
+    TP._encode_against_oracle(O, order, psi, gen.shared_R(m, ell), G, g_dtype, ell, d)
+
+
+@pytest.mark.parametrize("g_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_not_finite_gradients(value, g_dtype):
+    """A chunk's value that is not finite enters the rows that have processed the chunk, at its
+    position, and no other row."""
+    m, delta, ell, d, P = 40, 12, 2, 1203, 20
+    L = -(-d // ell)
+    O, order, G, psi = problem(m, delta, d, P, "f32", seed=3)
+    where = [(5, 17), (23, L + 44), (23, d - 1)]
+    for c, x in where:
+        G[c, x] = 0.0
+    bits = np.float32(value).view(np.uint32)
+    if g_dtype == "bf16":
+        G = gen.f32_to_bf16_bits(G)
+        bits = bits >> 16
+    Gbad = G.copy()
+    for c, x in where:
+        Gbad.view(np.uint16 if g_dtype == "bf16" else np.uint32)[c, x] = bits
+    wide = OP.widen(G, g_dtype)
+    R = gen.shared_R(m, ell)
+    Bc, _ = R_.coefficients(O, psi, R)
+    Bc32 = Bc.astype(np.float32)
+    Gt = TP.dev(Gbad.view(np.int16)).view(torch.bfloat16) if g_dtype == "bf16" else TP.dev(Gbad)
+    T = torch.zeros((P, m, L), dtype=torch.float32, device="cuda")
+    T = TP.host(gcx.gc_encode(Gt, TP.dev(psi), TP.dev(order), TP.dev(Bc32), T=T))
+    ref, M, nterm = R_.encode_ref(Bc32.astype(np.float64), psi, order, wide, ell)
+    bound = R_.encode_bound(nterm, M, g_dtype)
+    bad = np.zeros(T.shape, dtype=bool)
+    for p in range(P):
+        for j in range(m):
+            for c, x in where:
+                if c in order[j, : psi[p, j]]:
+                    bad[p, j, x % L] = True
+    assert bad.any() and not np.isfinite(T[bad]).any()
+    ok = ~bad & (psi > 0)[:, :, None]
+    diff = np.where(ok, np.abs(np.where(ok, T, 0).astype(np.float64) - np.where(ok, ref, 0)), 0)
+    assert (diff <= np.where(ok, bound, np.inf)).all()
