@@ -22,8 +22,8 @@
 //   - block -> (slice, row run) is XCD-aware: blocks are dispatched round-robin
 //     over the 8 XCDs, and every block of a slice runs on the same XCD, so its
 //     L2 serves the repeated slice staging.
-// Where the slice of every chunk does not fit in LDS or rows start off 16-byte boundaries, the
-// matrix-core encode (encode_mx.hip) or the worker-group layout below takes over.
+// Where the slice of every chunk does not fit in LDS, and for most calls on rows off 16-byte
+// boundaries, the matrix-core encode (encode_mx.hip) or the worker-group layout below takes over.
 #include "common.h"
 #include "encode_mx.h"
 
@@ -36,6 +36,7 @@ constexpr size_t kEncSliceLds = 96 * 1024;   // G slice budget
 constexpr size_t kEncMetaLds = 24 * 1024;    // row metadata budget
 constexpr int kEncGroup = 256;               // rows of metadata staged per step, at most
 constexpr int kEncGroupsPerBlock = 2;        // rows per block = 2 groups
+constexpr int64_t kEncFewRows = 128, kEncFewOutputs = int64_t(1) << 22;  // small calls keep this layout
 
 template <typename GT>
 __device__ __forceinline__ float to_f32(GT v);
@@ -916,9 +917,8 @@ int launch_encode_group(EncodeArgs a, int64_t P, hipStream_t st) {
   return pb4 ? launch_group<GT, 1, 1, 4>(a, g, lds, st) : launch_group<GT, 1, 1, 2>(a, g, lds, st);
 }
 
-template <typename GT>
+template <typename GT, int VEC>
 int launch_encode(EncodeArgs a, hipStream_t st) {
-  constexpr int VEC = 4;
   constexpr int W = kWave * VEC;
   a.nslices = int(ceil_div(a.L, W));
   a.term_stride = (a.delta * a.ell + 3) & ~3;
@@ -947,6 +947,12 @@ int launch_encode(EncodeArgs a, hipStream_t st) {
     return GC_ELAUNCH;
   hipLaunchKernelGGL((encode_kernel<GT, VEC>), dim3(unsigned(blocks)), dim3(kEncThreads), lds, st, a);
   return GC_OK;
+}
+
+template <typename GT>
+int dispatch_all_chunks(const EncodeArgs &a, int vec, hipStream_t st) {
+  return vec == 4 ? launch_encode<GT, 4>(a, st)
+                  : (vec == 2 ? launch_encode<GT, 2>(a, st) : launch_encode<GT, 1>(a, st));
 }
 
 template <typename GT>
@@ -992,13 +998,18 @@ extern "C" int gc_encode(const void *G, int32_t g_dtype, int32_t N, int64_t d, c
   // widest vector the row length and the alignment of T allow
   const int vec = (a.L % 4 == 0 && (ta & 15) == 0) ? 4 : ((a.L % 2 == 0 && (ta & 7) == 0) ? 2 : 1);
   (void)hipGetLastError();
-  // The all-chunk layout where the rows of G and T are 16-byte aligned and the slice of every
-  // chunk fits in LDS (m = 50, ell = 1: 1.85 ms for 5000 patterns against 1.94 on the matrix
-  // cores; on rows that start anywhere its scalar accesses lose: m = 37, ell = 3, d = 100003
-  // 2.1 ms against 0.62).  Else the matrix cores up to 176 (fp32) or 192 (bf16) terms per output,
-  // and past that the worker groups.
-  if (vec == 4 && a.stage16 && size_t(N) * ell * kWave * 4 * esize <= kEncSliceLds) {
-    const int st = g_dtype == GC_F32 ? launch_encode<float>(a, stream) : launch_encode<uint16_t>(a, stream);
+  // The all-chunk layout, where the slice of every chunk fits in LDS at that width, for rows of G
+  // and T on 16-byte boundaries (m = 50, ell = 1: 1.85 ms for 5000 patterns against 1.94 on the
+  // matrix cores; on rows that start anywhere its narrow accesses lose: m = 37, ell = 3, d = 100003
+  // 2.1 ms against 0.62), and on any rows for calls that are over in a few microseconds, where
+  // its shorter setup counts (m = 20, ell = 3, d = 131075, 4 patterns 12 us against 17; m = 60, d =
+  // 32770, one pattern 11 against 13; m = 20, d = 131075, 32 patterns 45 against 26).  Else the
+  // matrix cores up to 176 (fp32) or 192 (bf16) terms per output, and past that the worker
+  // groups.
+  const bool few = a.rows <= kEncFewRows && a.rows * a.L <= kEncFewOutputs;
+  if (((vec == 4 && a.stage16) || few) && size_t(N) * ell * kWave * vec * esize <= kEncSliceLds) {
+    const int st = g_dtype == GC_F32 ? dispatch_all_chunks<float>(a, vec, stream)
+                                     : dispatch_all_chunks<uint16_t>(a, vec, stream);
     return st != GC_OK ? st : launch_status();
   }
   // A few patterns with few terms stay there too: one pattern, m = 200, delta = 8, d = 65536 on a

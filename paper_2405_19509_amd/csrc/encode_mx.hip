@@ -227,6 +227,17 @@ encode_mx_kernel(MxArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), nw = nth / kWave;
   const int lane = tid % kWave, h = lane >> 5, li = lane & 31;
 
+  // every load that waits for nothing: the chunks at each (worker, position), and the counts of
+  // the candidates (pattern p0 + r / J, worker j0 + r % J)
+  for (int e = tid; e < nj * a.delta; e += nth) {
+    const int c = a.order[int64_t(j0) * a.delta + e];
+    code[e] = c >= 0 && c < a.N ? c : -1;
+  }
+  const int rpb = tid / a.J, rjb = tid - rpb * a.J;
+  int npr = 0;
+  if (tid < a.CW && rpb < a.PB && p0 + rpb < a.P && rjb < nj) npr = a.psi[(p0 + rpb) * a.m + j0 + rjb];
+  npr = npr < 0 ? 0 : (npr > a.delta ? a.delta : npr);
+
   // Passes over the group's workers, each with the slots of its workers' distinct chunks.  One
   // worker: slot t = position t.  Else one pass where every worker's chunks together fit the
   // slots (slots in ascending chunk order; the cyclic order always does), and as many
@@ -235,10 +246,8 @@ encode_mx_kernel(MxArgs a) {
   if (a.J > 1) {
     for (int c = tid; c < a.N; c += nth) map[c] = -1;
     __syncthreads();
-    for (int e = tid; e < nj * a.delta; e += nth) {
-      const int c = a.order[int64_t(j0) * a.delta + e];
-      if (c >= 0 && c < a.N) map[c] = 0;
-    }
+    for (int e = tid; e < nj * a.delta; e += nth)
+      if (code[e] >= 0) map[code[e]] = 0;
     __syncthreads();
     if (tid < kWave) {
       int cnt = 0;
@@ -261,58 +270,43 @@ encode_mx_kernel(MxArgs a) {
   for (int ja = 0, jn = nj; ja < nj; ja = jn) {  // workers ja .. jn - 1 of the group
     int nslot = nuni;
     __syncthreads();  // the previous pass is done with every table
-    if (nuni > a.slots) {
-      jn = ja + 1;
+    if (a.J == 1) {
       nslot = a.delta;
-      if (a.J > 1) {
-        for (int c = tid; c < a.N; c += nth) map[c] = -1;
-        for (int e = ja * a.delta + tid; e < nj * a.delta; e += nth) code[e] = a.order[int64_t(j0) * a.delta + e];
-        __syncthreads();
-        if (tid < kWave) {
-          int cnt = 0, j = ja;
-          for (; j < nj; ++j) {
-            const int c = lane < a.delta ? code[j * a.delta + lane] : -1;  // delta <= 64
-            const bool fresh = c >= 0 && c < a.N && map[c] < 0;
-            const unsigned long long mk = __ballot(fresh);
-            if (cnt + __popcll(mk) > a.slots) break;  // never at j = ja: delta <= slots
-            const int s = cnt + __popcll(mk & ((1ull << lane) - 1));
-            if (fresh) {
-              map[c] = s;
-              slotc[s] = c;
-            }
-            cnt += __popcll(mk);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      for (int t = tid; t < a.delta; t += nth) slotc[t] = code[t] >= 0 ? code[t] : 0;
+    } else if (nuni > a.slots) {
+      for (int c = tid; c < a.N; c += nth) map[c] = -1;
+      __syncthreads();
+      if (tid < kWave) {
+        int cnt = 0, j = ja;
+        for (; j < nj; ++j) {
+          const int c = lane < a.delta ? code[j * a.delta + lane] : -1;  // delta <= 64
+          const bool fresh = c >= 0 && map[c] < 0;
+          const unsigned long long mk = __ballot(fresh);
+          if (cnt + __popcll(mk) > a.slots) break;  // never at j = ja: delta <= slots
+          const int s = cnt + __popcll(mk & ((1ull << lane) - 1));
+          if (fresh) {
+            map[c] = s;
+            slotc[s] = c;
           }
-          if (tid == 0) {
-            nuni_s = cnt;
-            jn_s = j;
-          }
+          cnt += __popcll(mk);
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
-        __syncthreads();
-        nslot = nuni_s;
-        jn = jn_s;
+        if (tid == 0) {
+          nuni_s = cnt;
+          jn_s = j;
+        }
       }
-    }
-    for (int e = tid; e < nj * a.delta; e += nth) {  // the slot at each (worker, position), or -1
-      const int jb = e / a.delta, t = e - jb * a.delta;
-      const int c = a.order[int64_t(j0) * a.delta + e];
-      const bool ok = jb >= ja && jb < jn && c >= 0 && c < a.N;
-      code[e] = !ok ? -1 : (a.J == 1 ? t : map[c]);
-      if (a.J == 1) slotc[t] = ok ? c : 0;
+      __syncthreads();
+      nslot = nuni_s;
+      jn = jn_s;
     }
     const int K = nslot * ell;  // rows of B
-    // the transmitting candidates (pattern p0 + r / J, worker j0 + r % J), compacted in order
-    bool on = false;
-    int np = 0, pb = 0, jb = 0;
-    if (tid < a.CW) {
-      pb = tid / a.J;
-      jb = tid - pb * a.J;
-      if (pb < a.PB && p0 + pb < a.P && jb >= ja && jb < jn) np = a.psi[(p0 + pb) * a.m + j0 + jb];
-      np = np < 0 ? 0 : (np > a.delta ? a.delta : np);
-      on = np > 0;
-    }
+    for (int e = tid; e < (a.CW / 32) * (3 * 32 * AP / 8); e += nth)
+      reinterpret_cast<uint4 *>(Ap)[e] = make_uint4(0u, 0u, 0u, 0u);
+    // the transmitting candidates, compacted in order
+    const bool on = npr > 0 && rjb >= ja && rjb < jn;
     const unsigned long long mk = __ballot(on);
     if (lane == 0) wcnt[wave] = __popcll(mk);
     __syncthreads();
@@ -324,9 +318,10 @@ encode_mx_kernel(MxArgs a) {
     if (on) {
       const int c = c0 + __popcll(mk & ((1ull << lane) - 1));
       crow[c] = int16_t(tid);
-      cnp[c] = int16_t(np);
-      rowoff[c] = (int64_t(pb) * a.m + jb) * a.L;
+      cnp[c] = int16_t(npr);
+      rowoff[c] = (int64_t(rpb) * a.m + rjb) * a.L;
     }
+    const int ntile = (nsend + 31) / 32;
     // row kk of B: half kk % 2, place kk / 2 (a place past K repeats row 0, with zero
     // coefficients): its element offset in G and the end of its valid positions
     for (int e = tid; e < Kp; e += nth) {
@@ -337,19 +332,17 @@ encode_mx_kernel(MxArgs a) {
       base[q] = int64_t(K > 0 ? slotc[s] : 0) * a.d + (rem > 0 ? int64_t(k) * a.L : 0);
       lim[q] = rem < a.L ? rem : a.L;
     }
-    const int ntile = (nsend + 31) / 32;
-    for (int e = tid; e < ntile * (3 * 32 * AP / 8); e += nth)
-      reinterpret_cast<uint4 *>(Ap)[e] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     // three bf16 planes per row tile: a1 = bf16(a), a2 = bf16(a - a1), a3 = bf16(a - a1 - a2),
     // all exact steps; row kk at column 16 (kk / 16) + 8 (kk % 2) + (kk % 16) / 2
     for (int e = tid; e < nsend * a.delta; e += nth) {
       const int c = e / a.delta, t = e - c * a.delta;
       if (t >= cnp[c]) continue;
-      const int rpb = crow[c] / a.J, rjb = crow[c] - rpb * a.J;
-      const int s = code[rjb * a.delta + t];
-      if (s < 0) continue;
-      const float *src = a.Bc + (((p0 + rpb) * a.m + j0 + rjb) * a.delta + t) * ell;
+      const int pb = crow[c] / a.J, jb = crow[c] - pb * a.J;
+      const int ch = code[jb * a.delta + t];
+      if (ch < 0) continue;
+      const int s = a.J == 1 ? t : map[ch];
+      const float *src = a.Bc + (((p0 + pb) * a.m + j0 + jb) * a.delta + t) * ell;
       uint16_t *tp = Ap + (c / 32) * (3 * 32 * AP) + (c % 32) * AP;
       for (int k = 0; k < ell; ++k) {
         const int kk = s * ell + k;
