@@ -31,46 +31,36 @@
 namespace gcx {
 namespace {
 
-constexpr int kRecThreads = 1024;
-constexpr int kRecNV = 1;            // float4 (or 4 scalars) per thread and row
-constexpr int kRecV = 4 * kRecNV;    // x positions per thread
-constexpr int64_t kRecPiece = int64_t(kRecThreads) * kRecV;  // x positions per block
+constexpr int kRecThreads = 1024;    // threads per block, kRecSmall while a row fits its positions
+constexpr int kRecSmall = 256;
+constexpr int kRecV = 4;             // x positions per thread
+constexpr int64_t kRecPiece = int64_t(kRecThreads) * kRecV;  // x positions per item
 constexpr int kRecUnroll = 8;        // rows of T loads in flight per thread
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));  // rows may start anywhere
 
 int64_t rec_pieces(int64_t L) { return ceil_div(L, kRecPiece); }
 
-// VEC = 4: thread t owns x = piece*kRecPiece + 4(t + kRecThreads v) + e, v < kRecNV, e < 4
-// (needs L % 4 == 0 and aligned T); VEC = 1: x = piece*kRecPiece + t + kRecThreads i,
-// i < kRecV (any L).  Either way each load instruction of a block reads consecutive bytes.
-template <int VEC>
-__device__ __forceinline__ int64_t rec_x(int64_t q, int i) {
-  return VEC == 4 ? q * kRecPiece + (int64_t(threadIdx.x) + int64_t(kRecThreads) * (i / 4)) * 4 + i % 4
-                  : q * kRecPiece + threadIdx.x + int64_t(kRecThreads) * i;
-}
-
-template <int VEC>
-__device__ __forceinline__ void rec_load(const float *__restrict__ row, int64_t q, int64_t L,
-                                         float (&v)[kRecV]) {
-  if constexpr (VEC == 4) {
+// Thread t owns x0 = q*kRecPiece + 4t .. x0 + 3: each load instruction of a block reads
+// consecutive bytes, 16 per lane.  AL: rows of T, of the estimate and gsum on 16-byte
+// boundaries; else rows start anywhere, loaded 16 bytes per lane all the same (at L = 33335, ell
+// = 3 0.47 ms for 500 patterns against 0.48 with 4-byte loads), and the last one to three
+// positions of a row one by one.  Each load is issued as its row's offset is read, rather than
+// eight in a burst: the block's waves then ask for the same row's 16 KB together (a burst of
+// eight, with waits that count the loads needed only, read T 6-12% slower).
+template <bool AL>
+__device__ __forceinline__ v4f rec_load(const float *__restrict__ row, int64_t x0, int64_t L) {
+  v4f v = {0.f, 0.f, 0.f, 0.f};
+  if (AL ? x0 < L : x0 + 4 <= L) {
+    v = AL ? __builtin_nontemporal_load(reinterpret_cast<const v4f *>(row + x0))
+           : v4f(__builtin_nontemporal_load(reinterpret_cast<const v4fu *>(row + x0)));
+  } else if (!AL && x0 < L) {
 #pragma unroll
-    for (int u = 0; u < kRecNV; ++u) {
-      const int64_t x = rec_x<4>(q, 4 * u);
-      if (x < L) {
-        const v4f t = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(row + x));
-        v[4 * u] = t.x; v[4 * u + 1] = t.y; v[4 * u + 2] = t.z; v[4 * u + 3] = t.w;
-      } else {
-        v[4 * u] = v[4 * u + 1] = v[4 * u + 2] = v[4 * u + 3] = 0.f;
-      }
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < kRecV; ++i) {
-      const int64_t x = rec_x<1>(q, i);
-      v[i] = x < L ? __builtin_nontemporal_load(row + x) : 0.f;
-    }
+    for (int i = 0; i < 3; ++i)
+      if (x0 + i < L) v[i] = row[x0 + i];
   }
+  return v;
 }
 
 // Items per block when the estimate is written: K consecutive (pattern, piece) items,
@@ -80,29 +70,23 @@ __device__ __forceinline__ void rec_load(const float *__restrict__ row, int64_t 
 template <int ELL>
 constexpr int rec_items() { return ELL == 1 ? 8 : (ELL == 2 ? 4 : (ELL <= 4 ? 2 : 1)); }
 
-// the estimate's stores of one item (positions as rec_x; the whole float4 where it lies
-// inside the gradient, else element by element)
-template <int ELL, int VEC>
-__device__ __forceinline__ void rec_store(float *__restrict__ ghat, int64_t p, int64_t q, int64_t d,
-                                          int64_t L, const float (&acc)[ELL][kRecV]) {
+// the estimate's stores of one item (the whole float4 where it lies inside the gradient, else
+// element by element); plain where rows start anywhere, so that L2 puts together the pieces of
+// a line
+template <int ELL, bool AL>
+__device__ __forceinline__ void rec_store(float *__restrict__ ghat, int64_t p, int64_t x0, int64_t d,
+                                          int64_t L, const v4f (&acc)[ELL]) {
 #pragma unroll
   for (int k = 0; k < ELL; ++k) {
+    const int64_t c0 = int64_t(k) * L + x0;
+    float *dst = ghat + p * d + c0;
+    if (x0 + 4 <= L && c0 + 4 <= d) {
+      if (AL) __builtin_nontemporal_store(acc[k], reinterpret_cast<v4f *>(dst));
+      else *reinterpret_cast<v4fu *>(dst) = acc[k];
+    } else {
 #pragma unroll
-    for (int u = 0; u < kRecNV; ++u) {
-      const int64_t x0 = rec_x<VEC>(q, 4 * u);
-      const int64_t c0 = int64_t(k) * L + x0;
-      if (VEC == 4 && x0 < L && c0 + 3 < d) {
-        const float *a4 = &acc[k][4 * u];
-        __builtin_nontemporal_store(v4f{a4[0], a4[1], a4[2], a4[3]},
-                                    reinterpret_cast<v4f *>(ghat + p * d + c0));
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int64_t x = rec_x<VEC>(q, 4 * u + e);
-          const int64_t col = int64_t(k) * L + x;
-          if (x < L && col < d) __builtin_nontemporal_store(acc[k][4 * u + e], ghat + p * d + col);
-        }
-      }
+      for (int e = 0; e < 4; ++e)
+        if (x0 + e < L && c0 + e < d) dst[e] = acc[k][e];
     }
   }
 }
@@ -112,24 +96,24 @@ __device__ __forceinline__ void rec_store(float *__restrict__ ghat, int64_t p, i
 // partial sums in `part_s` until every item is done: a barrier waits for every
 // outstanding memory access of the block's waves, stores included, so the block's stores
 // all come after its last barrier.
-template <int ELL, int VEC, int K>
-__global__ __launch_bounds__(kRecThreads) void reconstruct_kernel(
+template <int ELL, bool AL, int K, int TH>
+__global__ __launch_bounds__(TH) void reconstruct_kernel(
     const float *__restrict__ T, const float *__restrict__ R, const int32_t *__restrict__ psi,
     int m, int64_t d, int64_t L, int64_t pieces, int64_t items, float *__restrict__ ghat,
     const float *__restrict__ gsum, double *__restrict__ partial) {
-  __shared__ double red[kRecThreads / kWave];
+  __shared__ double red[TH / kWave];
   __shared__ double part_s[K];
   __shared__ int rows[GC_MAX_M];      // the workers that transmitted, ascending
   __shared__ float rw[ELL][GC_MAX_M];  // their R[k][j]
   __shared__ int nrows;
   extern __shared__ __align__(16) unsigned char rec_dyn[];
-  v4f *held = reinterpret_cast<v4f *>(rec_dyn);  // [K][ELL][kRecThreads] (K > 1)
+  v4f *held = reinterpret_cast<v4f *>(rec_dyn);  // [K][ELL][TH] (K > 1)
   const int64_t it0 = int64_t(blockIdx.x) * K;
   const int nit = int(items - it0 < K ? items - it0 : K);
   int64_t cur_p = -1;
   for (int item = 0; item < nit; ++item) {
   const int64_t p = (it0 + item) / pieces;
-  const int64_t q = (it0 + item) % pieces;
+  const int64_t x0 = ((it0 + item) % pieces) * kRecPiece + int64_t(threadIdx.x) * 4;
   const float *Tp = T + p * int64_t(m) * L;
   __syncthreads();  // the previous item's rows, weights and reduction slots are free
 
@@ -157,20 +141,18 @@ __global__ __launch_bounds__(kRecThreads) void reconstruct_kernel(
   }
   const int nr = nrows;
 
-  float acc[ELL][kRecV];
+  v4f acc[ELL];
 #pragma unroll
-  for (int k = 0; k < ELL; ++k)
-#pragma unroll
-    for (int i = 0; i < kRecV; ++i) acc[k][i] = 0.f;
+  for (int k = 0; k < ELL; ++k) acc[k] = v4f{0.f, 0.f, 0.f, 0.f};
   // software pipeline: the loads of the next kRecUnroll rows are in flight while the
   // current ones are consumed
-  float va[kRecUnroll][kRecV], vb[kRecUnroll][kRecV];
-  auto issue = [&](int a0, float (&v)[kRecUnroll][kRecV]) {
+  v4f va[kRecUnroll], vb[kRecUnroll];
+  auto issue = [&](int a0, v4f (&v)[kRecUnroll]) {
 #pragma unroll
     for (int u = 0; u < kRecUnroll; ++u)
-      if (a0 + u < nr) rec_load<VEC>(Tp + int64_t(rows[a0 + u]) * L, q, L, v[u]);
+      if (a0 + u < nr) v[u] = rec_load<AL>(Tp + int64_t(rows[a0 + u]) * L, x0, L);
   };
-  auto consume = [&](int a0, const float (&v)[kRecUnroll][kRecV]) {
+  auto consume = [&](int a0, const v4f (&v)[kRecUnroll]) {
 #pragma unroll
     for (int u = 0; u < kRecUnroll; ++u)
       if (a0 + u < nr)
@@ -195,25 +177,18 @@ __global__ __launch_bounds__(kRecThreads) void reconstruct_kernel(
     double se = 0.0;
 #pragma unroll
     for (int k = 0; k < ELL; ++k) {
+      const int64_t c0 = int64_t(k) * L + x0;
+      if (x0 + 4 <= L && c0 + 4 <= d) {  // whole float4 inside the gradient
+        const v4f g = *reinterpret_cast<const v4fu *>(gsum + c0);
+        const double e0 = double(acc[k][0]) - g[0], e1 = double(acc[k][1]) - g[1];
+        const double e2 = double(acc[k][2]) - g[2], e3 = double(acc[k][3]) - g[3];
+        se += e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
+      } else {
 #pragma unroll
-      for (int u = 0; u < kRecNV; ++u) {
-        const int64_t x0 = rec_x<VEC>(q, 4 * u);
-        const int64_t c0 = int64_t(k) * L + x0;
-        if (VEC == 4 && x0 < L && c0 + 3 < d) {  // whole float4 inside the gradient
-          const float *a4 = &acc[k][4 * u];
-          const float4 g = *reinterpret_cast<const float4 *>(gsum + c0);
-          const double e0 = double(a4[0]) - g.x, e1 = double(a4[1]) - g.y;
-          const double e2 = double(a4[2]) - g.z, e3 = double(a4[3]) - g.w;
-          se += e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int64_t x = rec_x<VEC>(q, 4 * u + e);
-            const int64_t col = int64_t(k) * L + x;
-            if (x < L && col < d) {
-              const double diff = double(acc[k][4 * u + e]) - double(gsum[col]);
-              se += diff * diff;
-            }
+        for (int e = 0; e < 4; ++e) {
+          if (x0 + e < L && c0 + e < d) {
+            const double diff = double(acc[k][e]) - double(gsum[c0 + e]);
+            se += diff * diff;
           }
         }
       }
@@ -223,37 +198,38 @@ __global__ __launch_bounds__(kRecThreads) void reconstruct_kernel(
     __syncthreads();
     if (threadIdx.x == 0) {
       double tot = 0.0;
-      for (int w = 0; w < kRecThreads / kWave; ++w) tot += red[w];
+      for (int w = 0; w < TH / kWave; ++w) tot += red[w];
       part_s[item] = tot;
     }
   }
   if constexpr (K == 1) {
     // one item: nothing follows, so its stores can go out directly
-    if (ghat) rec_store<ELL, VEC>(ghat, p, q, d, L, acc);
+    if (ghat) rec_store<ELL, AL>(ghat, p, x0, d, L, acc);
   } else {
 #pragma unroll
-    for (int k = 0; k < ELL; ++k)
-      held[(item * ELL + k) * kRecThreads + threadIdx.x] = v4f{acc[k][0], acc[k][1], acc[k][2], acc[k][3]};
+    for (int k = 0; k < ELL; ++k) held[(item * ELL + k) * TH + threadIdx.x] = acc[k];
   }
   }  // items
 
   // the block's stores, after its last barrier
   if constexpr (K > 1) {
     for (int item = 0; item < nit; ++item) {
-      const int64_t p = (it0 + item) / pieces, q = (it0 + item) % pieces;
-      float acc[ELL][kRecV];
+      const int64_t p = (it0 + item) / pieces;
+      const int64_t x0 = ((it0 + item) % pieces) * kRecPiece + int64_t(threadIdx.x) * 4;
+      v4f acc[ELL];
 #pragma unroll
-      for (int k = 0; k < ELL; ++k) {
-        const v4f h = held[(item * ELL + k) * kRecThreads + threadIdx.x];
-        acc[k][0] = h.x; acc[k][1] = h.y; acc[k][2] = h.z; acc[k][3] = h.w;
-      }
-      rec_store<ELL, VEC>(ghat, p, q, d, L, acc);
+      for (int k = 0; k < ELL; ++k) acc[k] = held[(item * ELL + k) * TH + threadIdx.x];
+      rec_store<ELL, AL>(ghat, p, x0, d, L, acc);
     }
   }
   if (partial && threadIdx.x == 0)
     for (int item = 0; item < nit; ++item) partial[it0 + item] = part_s[item];
 }
 
+// sqerr[p] = the sum of its pieces' partial sums, in a fixed order: one thread per pattern
+// while there are few, one wave from kRecManyPieces on (2048 pieces of one pattern at d = 2^24, ell =
+// 2: 5 us against 150, a chain of 2048 loads)
+constexpr int kRecManyPieces = 32;
 __global__ void sqerr_finalize_kernel(const double *__restrict__ partial, int64_t P, int nslices,
                                       double *__restrict__ sqerr) {
   const int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -262,34 +238,51 @@ __global__ void sqerr_finalize_kernel(const double *__restrict__ partial, int64_
   for (int s = 0; s < nslices; ++s) tot += partial[p * nslices + s];
   sqerr[p] = tot;
 }
+__global__ void sqerr_finalize_wave_kernel(const double *__restrict__ partial, int64_t P, int nslices,
+                                           double *__restrict__ sqerr) {
+  const int64_t p = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
+  if (p >= P) return;  // a whole wave
+  double tot[4] = {0.0, 0.0, 0.0, 0.0};
+  const double *src = partial + p * nslices;
+  int s = int(threadIdx.x) % kWave;
+  for (; s + 3 * kWave < nslices; s += 4 * kWave)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) tot[u] += src[s + u * kWave];
+  for (; s < nslices; s += kWave) tot[0] += src[s];
+  const double t = wave_sum((tot[0] + tot[1]) + (tot[2] + tot[3]));
+  if (threadIdx.x % kWave == 0) sqerr[p] = t;
+}
 
-template <int ELL, int VEC, int K>
+template <int ELL, bool AL, int K, int TH>
 int launch_rec_k(const float *T, const float *R, const int32_t *psi, int64_t P, int m, int64_t d,
                  int64_t L, int64_t pieces, float *ghat, const float *gsum, double *partial,
                  hipStream_t st) {
   const int64_t items = P * pieces;
   const int64_t blocks = ceil_div(items, int64_t(K));
-  if (!grid_ok(blocks, kRecThreads)) return GC_EINVAL;
-  const size_t dyn = K > 1 ? sizeof(v4f) * size_t(K) * ELL * kRecThreads : 0;
-  if (dyn > 0 && hipFuncSetAttribute(reinterpret_cast<const void *>(&reconstruct_kernel<ELL, VEC, K>),
+  if (!grid_ok(blocks, TH)) return GC_EINVAL;
+  const size_t dyn = K > 1 ? sizeof(v4f) * size_t(K) * ELL * TH : 0;
+  if (dyn > 0 && hipFuncSetAttribute(reinterpret_cast<const void *>(&reconstruct_kernel<ELL, AL, K, TH>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(dyn)) != hipSuccess)
     return GC_ELAUNCH;
-  hipLaunchKernelGGL((reconstruct_kernel<ELL, VEC, K>), dim3(unsigned(blocks)), dim3(kRecThreads), dyn, st,
+  hipLaunchKernelGGL((reconstruct_kernel<ELL, AL, K, TH>), dim3(unsigned(blocks)), dim3(TH), dyn, st,
                      T, R, psi, m, d, L, pieces, items, ghat, gsum, partial);
   return GC_OK;
 }
 
-// items per block: rec_items<ELL>() when the estimate is written, else one
-template <int ELL>
-int launch_rec(bool vec4, const float *T, const float *R, const int32_t *psi, int64_t P, int m,
-               int64_t d, int64_t L, int64_t pieces, float *ghat, const float *gsum, double *partial,
-               hipStream_t st) {
+// Items per block: rec_items<ELL>() when the estimate is written and the blocks still fill the
+// chip, else one (100 patterns of m = 6, d = 64, ell = 2: 5 us with one item per block of 256
+// threads, 15 with four per block of 1024).
+template <int ELL, bool AL>
+int launch_rec(const float *T, const float *R, const int32_t *psi, int64_t P, int m, int64_t d, int64_t L,
+               int64_t pieces, float *ghat, const float *gsum, double *partial, hipStream_t st) {
   constexpr int KB = rec_items<ELL>();
-  if (ghat && KB > 1)
-    return vec4 ? launch_rec_k<ELL, 4, KB>(T, R, psi, P, m, d, L, pieces, ghat, gsum, partial, st)
-                : launch_rec_k<ELL, 1, KB>(T, R, psi, P, m, d, L, pieces, ghat, gsum, partial, st);
-  return vec4 ? launch_rec_k<ELL, 4, 1>(T, R, psi, P, m, d, L, pieces, ghat, gsum, partial, st)
-              : launch_rec_k<ELL, 1, 1>(T, R, psi, P, m, d, L, pieces, ghat, gsum, partial, st);
+  const bool many = ghat && KB > 1 && P * pieces >= int64_t(KB) * 2 * cu_count();
+  const bool small = L <= int64_t(kRecSmall) * kRecV;
+  if (many)
+    return small ? launch_rec_k<ELL, AL, KB, kRecSmall>(T, R, psi, P, m, d, L, pieces, ghat, gsum, partial, st)
+                 : launch_rec_k<ELL, AL, KB, kRecThreads>(T, R, psi, P, m, d, L, pieces, ghat, gsum, partial, st);
+  return small ? launch_rec_k<ELL, AL, 1, kRecSmall>(T, R, psi, P, m, d, L, pieces, ghat, gsum, partial, st)
+               : launch_rec_k<ELL, AL, 1, kRecThreads>(T, R, psi, P, m, d, L, pieces, ghat, gsum, partial, st);
 }
 
 __global__ void sum_chunks_kernel(const void *__restrict__ G, int bf16, int N, int64_t d,
@@ -329,23 +322,28 @@ int reconstruct_impl(const float *T, const float *R, const int32_t *psi, int64_t
   const int64_t L = ceil_div(d, ell);
   const int64_t pieces = rec_pieces(L);
   if (sqerr && pieces == 1) partial = sqerr;
-  // float4 path: rows of T, the estimate's rows and gsum all 16-byte aligned
-  const bool vec4 = L % 4 == 0 && d % 4 == 0 && aligned16(T) && (!ghat || aligned16(ghat)) &&
+  // rows of T, the estimate's rows and gsum all 16-byte aligned
+  const bool al = L % 4 == 0 && d % 4 == 0 && aligned16(T) && (!ghat || aligned16(ghat)) &&
                     (!gsum || aligned16(gsum));
   (void)hipGetLastError();
   int st = GC_OK;
   switch (ell) {
 #define GC_CASE(E)                                                                                 \
   case E:                                                                                          \
-    st = launch_rec<E>(vec4, T, R, psi, P, m, d, L, pieces, ghat, sqerr ? gsum : nullptr,          \
-                       sqerr ? partial : nullptr, stream);                                         \
+    st = al ? launch_rec<E, true>(T, R, psi, P, m, d, L, pieces, ghat, sqerr ? gsum : nullptr,      \
+                                  sqerr ? partial : nullptr, stream)                               \
+            : launch_rec<E, false>(T, R, psi, P, m, d, L, pieces, ghat, sqerr ? gsum : nullptr,     \
+                                   sqerr ? partial : nullptr, stream);                             \
     break;
     GC_CASE(1) GC_CASE(2) GC_CASE(3) GC_CASE(4) GC_CASE(5) GC_CASE(6) GC_CASE(7) GC_CASE(8)
 #undef GC_CASE
     default: return GC_EINVAL;
   }
   if (st != GC_OK) return st;
-  if (sqerr && pieces > 1)
+  if (sqerr && pieces >= kRecManyPieces)
+    hipLaunchKernelGGL(sqerr_finalize_wave_kernel, dim3(unsigned(ceil_div(P, 256 / kWave))), dim3(256), 0, stream,
+                       partial, P, int(pieces), sqerr);
+  else if (sqerr && pieces > 1)
     hipLaunchKernelGGL(sqerr_finalize_kernel, dim3(unsigned(ceil_div(P, 256))), dim3(256), 0, stream,
                        partial, P, int(pieces), sqerr);
   return launch_status();
