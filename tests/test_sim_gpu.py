@@ -175,3 +175,50 @@ def test_original_ls_matches_oracle(kind):
     ref = np.array([OS.original_ls_error(O, p) for p in psi])
     assert (np.abs(err - ref) <= 1e-9 * np.maximum(1.0, ref)).all(), np.abs(err - ref).max()
     assert iters.max() < 1000
+
+
+@pytest.mark.parametrize("m,s,N", [(64, 3, 64), (65, 8, 65), (200, 7, 200), (90, 15, 90), (90, 16, 90), (257, 5, 257), (300, 2, 310), (513, 3, 513), (1024, 4, 1024),
+                                   (1024, 63, 1024)])
+def test_original_ls_sizes(m, s, N):
+    """The least-squares error at the edges of the values held per lane (64, 256, 512, 1024
+    chunks and workers), more chunks than workers, and tables too large for LDS."""
+    rng = np.random.default_rng([m, s])
+    O = np.zeros((N, m), dtype=np.int32)
+    for j in range(m):
+        O[(j + np.arange(s + 1)) % N, j] = np.arange(s + 1) + 1
+    if N > m:  # the last chunks to workers that then hold one more
+        O[np.arange(m, N), np.arange(N - m)] = s + 2
+    _, order, holder, _ = gcx.gc_assign(gcx.GC_ASSIGN_ORDER, N, m, O=O)
+    P = 5
+    psi = np.where(rng.random((P, m)) < [[0.0], [0.1], [0.5], [0.9], [1.0]], (O != 0).sum(axis=0), 0).astype(np.int32)
+    err, iters = gcx.gc_original_ls(dev(psi), dev(order), dev(holder), max_iter=20000)
+    err, iters = host(err), host(iters)
+    ref = np.array([OS.original_ls_error(O.astype(np.int64), p) for p in psi])
+    assert iters.max() < 20000
+    assert (np.abs(err - ref) <= 1e-9 * np.maximum(1.0, ref)).all(), np.abs(err - ref).max()
+
+
+@pytest.mark.parametrize("delta", [1, 8, 9, 16, 17, 32, 33, 64])
+def test_progress_and_completion_loads(delta):
+    """psi(T) and completion times bit for bit at the edges of the loads whose finish times are
+    held in registers, and past the trials' times that fit LDS."""
+    m, R = (70, 3) if delta < 64 else (200, 2)
+    _, order, holder, hpos = gcx.gc_assign(gcx.GC_ASSIGN_CYCLIC, m, m, delta - 1)
+    rng = np.random.default_rng(delta)
+    tau = rng.exponential(1.0, size=(R, m, delta))
+    failed = rng.random((R, m)) < 0.1
+    T = np.array([0.0, 0.3 * delta, float(delta), 3.0 * delta, np.inf])
+    cum = np.zeros_like(tau)
+    c = np.zeros((R, m))
+    for t in range(delta):
+        c = c + tau[:, :, t]
+        cum[:, :, t] = c
+    cum[failed] = np.inf
+    psi = host(gcx.gc_progress(dev(tau), dev(T), dev(failed.astype(np.uint8))))
+    ref = np.stack([((cum <= x) & ~failed[:, :, None]).sum(axis=2) for x in T], axis=1)
+    assert (psi == ref).all()
+    for ell in (1, min(3, delta)):
+        part, orig = gcx.gc_completion_times(dev(tau), dev(holder), dev(hpos), ell, dev(failed.astype(np.uint8)))
+        at = np.sort(cum[:, holder, hpos], axis=2)[:, :, ell - 1].max(axis=1)
+        full = np.sort(cum[:, holder, delta - 1], axis=2)[:, :, ell - 1].max(axis=1)
+        assert (host(part) == at).all() and (host(orig) == full).all()
