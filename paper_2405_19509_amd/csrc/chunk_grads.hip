@@ -18,13 +18,16 @@
 // Many points (b >= 16, b % 4 == 0, d % 4 == 0): two fp32 MFMA GEMMs per chunk
 // (chunk_grads_mfma.hip).
 //
-// General path (any d): two streaming kernels
-//   residual_kernel  one wavefront per sample row: dot(x, w) reduced across
-//                    the wave, then the loss residual  -> workspace r [b][N][n]
-//   xtr_kernel       one block per (point, chunk, 256*VEC columns): the
-//                    chunk's residuals staged in LDS, every thread streams its
-//                    VEC columns down all n rows (coalesced, several loads in
-//                    flight), fixed summation order -> deterministic.
+// General path (any d, any alignment): two streaming kernels
+//   dot_kernel   x.w of 4 rows (few rows: 1) over a segment of the columns by one wave, 16-byte
+//                loads from any float on, w loaded once for the rows -> workspace [b][N][n][segments]
+//   xtr_kernel   one block per (point, chunk, 1024 or 256 columns): the chunk's residuals
+//                from the segments' sums in LDS, then the columns down all n rows, 8 loads
+//                in flight; fixed summation order -> deterministic.
+// Both read X at the rate of the memory (X of 20 x 100 x 250001, 2 GB: 0.36 ms each, 5.5
+// TB/s; scalar loads and one wave per row took 2.1 ms in all).
+#include <algorithm>
+
 #include "common.h"
 
 namespace gcx {
@@ -41,96 +44,154 @@ constexpr int kGradThreads = 256;
 constexpr int kGradWaves = kGradThreads / kWave;
 constexpr int kResidStage = 2048;  // residuals staged in LDS per step
 
-template <int VEC>
-__global__ __launch_bounds__(kGradThreads) void residual_kernel(
-    const float *__restrict__ X, const float *__restrict__ y, const float *__restrict__ W, int64_t rows,
-    int64_t Nn, int64_t d, int loss, float *__restrict__ resid) {
+// rows of X and W start on any float
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ float loss_residual(float z, float yv, int loss) {
+  return loss == GC_LOSS_LOGISTIC ? 1.0f / (1.0f + expf(-z)) - yv : z - yv;
+}
+
+// zpart[row][seg] = sum over the columns of segment seg of x * w, for ROWS rows by one wave:
+// w is read once for all of them.
+template <int ROWS>
+__global__ __launch_bounds__(kGradThreads) void dot_kernel(const float *__restrict__ X, const float *__restrict__ W,
+                                                           int64_t Nn, int64_t d, int64_t groups, int segs,
+                                                           int64_t seglen, int64_t units, float *__restrict__ zpart) {
   const int lane = threadIdx.x % kWave;
-  const int64_t row = int64_t(blockIdx.x) * kGradWaves + threadIdx.x / kWave;  // q*N*n + i*n + r
-  if (row >= rows) return;
-  const int64_t q = row / Nn, ir = row % Nn;
-  const float *x = X + ir * d;
+  const int64_t u = int64_t(blockIdx.x) * kGradWaves + threadIdx.x / kWave;  // (q, row group, segment)
+  if (u >= units) return;
+  const int seg = int(u % segs);
+  const int64_t q = u / segs / groups, r0 = u / segs % groups * ROWS;
+  const int64_t c0 = seg * seglen, c1 = c0 + seglen < d ? c0 + seglen : d;
   const float *w = W + q * d;
-  float s = 0.f;
-  if constexpr (VEC == 4) {
-    const int64_t d4 = d / 4;
-    const float4 *x4 = reinterpret_cast<const float4 *>(x);
-    const float4 *w4 = reinterpret_cast<const float4 *>(w);
-    for (int64_t c = lane; c < d4; c += kWave) {
-      const float4 a = x4[c], b = w4[c];
-      s = fmaf(a.x, b.x, s);
-      s = fmaf(a.y, b.y, s);
-      s = fmaf(a.z, b.z, s);
-      s = fmaf(a.w, b.w, s);
-    }
-  } else {
-    for (int64_t c = lane; c < d; c += kWave) s = fmaf(x[c], w[c], s);
+  const float *x[ROWS];
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) x[r] = X + (r0 + r < Nn ? r0 + r : Nn - 1) * d;
+  float s[ROWS][4];
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[r][e] = 0.f;
+  int64_t c = c0 + 4 * lane;
+#pragma unroll 2
+  for (; c + 4 <= c1; c += 4 * kWave) {
+    const v4fu b = *reinterpret_cast<const v4fu *>(w + c);
+    v4fu a[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) a[r] = *reinterpret_cast<const v4fu *>(x[r] + c);
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[r][e] = fmaf(a[r][e], b[e], s[r][e]);
   }
-  s = wave_sum(s);
-  if (lane == 0) {
-    const float yv = y[ir];
-    resid[row] = loss == GC_LOSS_LOGISTIC ? 1.0f / (1.0f + expf(-s)) - yv : s - yv;
+  for (; c < c1; ++c)  // the lane with the segment's last one to three columns
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) s[r][0] = fmaf(x[r][c], w[c], s[r][0]);
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) {
+    const float v = wave_sum((s[r][0] + s[r][1]) + (s[r][2] + s[r][3]));
+    if (lane == 0 && r0 + r < Nn) zpart[(q * Nn + r0 + r) * segs + seg] = v;
   }
 }
 
-template <int VEC>
-__global__ __launch_bounds__(kGradThreads) void xtr_kernel(const float *__restrict__ X,
-                                                           const float *__restrict__ resid, int N,
-                                                           int n, int64_t d, int64_t tiles,
-                                                           float *__restrict__ G) {
+// G[q][i][x] = sum_r residual(q, i, r) * X[i][r][x].  A block takes 1024 / RS columns; its waves
+// split the rows RS ways (wave w the rows of slice w % RS) and the slices are summed in order.
+template <int RS>
+__global__ __launch_bounds__(kGradThreads) void xtr_kernel(const float *__restrict__ X, const float *__restrict__ y,
+                                                           const float *__restrict__ zpart, int N, int n, int64_t d,
+                                                           int64_t tiles, int segs, int loss, float *__restrict__ G) {
   __shared__ float rs[kResidStage];
+  __shared__ float part[RS > 1 ? RS - 1 : 1][kGradThreads / RS][4];
   const int64_t tile = blockIdx.x % tiles;
-  const int64_t qi = blockIdx.x / tiles;  // q*N + i
-  const int64_t i = qi % N;
-  const int64_t x = (tile * kGradThreads + threadIdx.x) * VEC;
+  const int64_t q = blockIdx.x / tiles / N;
+  const int64_t i = N - 1 - blockIdx.x / tiles % N;  // descending: the last rows read are still cached
+  const int64_t qi = q * N + i;
+  const int slice = RS > 1 ? threadIdx.x / (kGradThreads / RS) : 0;
+  const int64_t x = (tile * (kGradThreads / RS) + threadIdx.x % (kGradThreads / RS)) * 4;
+  // columns xs .. xs + 3: past the end the last four, of which those from x on are stored
+  const int64_t xs = d < 4 || x + 4 <= d ? x : d - 4;
   const float *Xi = X + i * int64_t(n) * d;
-  const float *ri = resid + qi * n;
-  float acc[VEC];
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
   for (int r0 = 0; r0 < n; r0 += kResidStage) {
     const int rn = n - r0 < kResidStage ? n - r0 : kResidStage;
     __syncthreads();
-    for (int a = threadIdx.x; a < rn; a += kGradThreads) rs[a] = ri[r0 + a];
+    for (int a = threadIdx.x; a < rn; a += kGradThreads) {
+      const float *zp = zpart + (qi * n + r0 + a) * segs;
+      float z = 0.f;
+#pragma unroll 8
+      for (int g = 0; g < segs; ++g) z += zp[g];
+      rs[a] = loss_residual(z, y[i * n + r0 + a], loss);
+    }
     __syncthreads();
-    if (x < d) {
-      const float *xp = Xi + int64_t(r0) * d + x;
-      int r = 0;
-      for (; r + 8 <= rn; r += 8) {
-        float v[8][VEC];
+    const int per = (rn + RS - 1) / RS;
+    int r = slice * per;
+    const int re = r + per < rn ? r + per : rn;
+    const float *xp = Xi + int64_t(r0) * d + xs;
+    if (d >= 4) {
+      for (; r + 8 <= re; r += 8) {
+        v4fu v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          if constexpr (VEC == 4) {
-            const float4 t = *reinterpret_cast<const float4 *>(xp + int64_t(r + u) * d);
-            v[u][0] = t.x; v[u][1] = t.y; v[u][2] = t.z; v[u][3] = t.w;
-          } else {
-            v[u][0] = xp[int64_t(r + u) * d];
-          }
-        }
+        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const v4fu *>(xp + int64_t(r + u) * d);
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const float c = rs[r + u];
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) acc[e] = fmaf(c, v[u][e], acc[e]);
+          for (int e = 0; e < 4; ++e) acc[e] = fmaf(c, v[u][e], acc[e]);
         }
       }
-      for (; r < rn; ++r) {
-        const float c = rs[r];
+      for (; r < re; ++r) {
+        const v4fu v = *reinterpret_cast<const v4fu *>(xp + int64_t(r) * d);
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) acc[e] = fmaf(c, xp[int64_t(r) * d + e], acc[e]);
+        for (int e = 0; e < 4; ++e) acc[e] = fmaf(rs[r], v[e], acc[e]);
       }
+    } else {
+      for (; r < re; ++r)
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (xs + e < d) acc[e] = fmaf(rs[r], xp[int64_t(r) * d + e], acc[e]);
     }
   }
-  if (x < d) {
-    float *dst = G + qi * d + x;
-    if constexpr (VEC == 4) {
-      *reinterpret_cast<float4 *>(dst) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    } else {
-      dst[0] = acc[0];
-    }
+  if constexpr (RS > 1) {
+    const int col = threadIdx.x % (kGradThreads / RS);
+    if (slice > 0)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) part[slice - 1][col][e] = acc[e];
+    __syncthreads();
+    if (slice > 0) return;
+#pragma unroll
+    for (int v = 0; v < RS - 1; ++v)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += part[v][col][e];
+  }
+  float *dst = G + qi * d + xs;
+  if (x + 4 <= d) {
+    *reinterpret_cast<v4fu *>(dst) = v4fu{acc[0], acc[1], acc[2], acc[3]};
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (xs + e >= x && xs + e < d) dst[e] = acc[e];
   }
 }
 
+// Rows per wave, row groups and column segments of dot_kernel per point.  Segments of at least
+// 1024 columns (four rounds of a wave's 16-byte loads), as many as give every CU 32 waves; one row
+// per wave where four would leave the CUs short of 8 waves.
+struct DotPlan {
+  int rows;
+  int64_t groups, seglen;
+  int segs;
+};
+
+inline DotPlan dot_plan(int N, int n, int64_t d, int b) {
+  DotPlan dp{};
+  const int64_t R = int64_t(N) * n, most = std::max<int64_t>(1, d / 1024);
+  dp.rows = ceil_div(R, 4) * b * most < 2048 ? 1 : 4;
+  dp.groups = ceil_div(R, dp.rows);
+  const int64_t segs = std::max<int64_t>(1, std::min(ceil_div(8192, dp.groups * b), most));
+  dp.seglen = ceil_div(ceil_div(d, segs), 4) * 4;
+  dp.segs = int(ceil_div(d, dp.seglen));
+  return dp;
+}
 
 constexpr int kFusedThreads = 512;
 constexpr int kFusedWaves = kFusedThreads / kWave;
@@ -148,10 +209,6 @@ inline FusedPlan fused_plan(int N, int n) {
   int64_t rpb = ceil_div(R, blocks);
   if (rpb > n) rpb = n;
   return FusedPlan{ceil_div(R, rpb), rpb};
-}
-
-__device__ __forceinline__ float loss_residual(float z, float yv, int loss) {
-  return loss == GC_LOSS_LOGISTIC ? 1.0f / (1.0f + expf(-z)) - yv : z - yv;
 }
 
 template <int NV>
@@ -269,7 +326,7 @@ extern "C" size_t gc_chunk_grads_workspace_size(int32_t N, int32_t n, int64_t d,
     const gcx::FusedPlan fp = gcx::fused_plan(N, n);
     return sizeof(float) * size_t(b) * size_t(fp.blocks) * 2 * size_t(d);
   }
-  return sizeof(float) * size_t(b) * size_t(N) * size_t(n);
+  return sizeof(float) * size_t(b) * size_t(N) * size_t(n) * size_t(gcx::dot_plan(N, n, d, b).segs);
 }
 
 extern "C" int gc_chunk_grads(const float *X, const float *y, const float *W, int32_t N, int32_t n,
@@ -282,8 +339,7 @@ extern "C" int gc_chunk_grads(const float *X, const float *y, const float *W, in
   if (workspace_bytes < gc_chunk_grads_workspace_size(N, n, d, b)) return GC_EINVAL;
   const int64_t rows = int64_t(b) * N * n;
   const bool vec4 = d % 4 == 0 && aligned16(X) && aligned16(W) && aligned16(G);
-  const int vec = vec4 ? 4 : 1;
-  const int64_t tiles = ceil_div(d, int64_t(kGradThreads) * vec);
+  const int64_t tiles = ceil_div(d, int64_t(kGradThreads) * (vec4 ? 4 : 1));
   if (!grid_ok(ceil_div(rows, kGradWaves), kGradThreads) || !grid_ok(int64_t(b) * N * tiles, kGradThreads))
     return GC_EINVAL;
   const int dev = check_device();
@@ -314,16 +370,25 @@ extern "C" int gc_chunk_grads(const float *X, const float *y, const float *W, in
                        fp.rows_per_block, fp.blocks, G);
     return launch_status();
   }
-  float *resid = static_cast<float *>(workspace);
-  const dim3 g1(unsigned(ceil_div(rows, kGradWaves))), g2(unsigned(int64_t(b) * N * tiles));
-  if (vec4) {
-    hipLaunchKernelGGL(residual_kernel<4>, g1, dim3(kGradThreads), 0, stream, X, y, W, rows,
-                       int64_t(N) * n, d, loss, resid);
-    hipLaunchKernelGGL(xtr_kernel<4>, g2, dim3(kGradThreads), 0, stream, X, resid, N, n, d, tiles, G);
+  float *zpart = static_cast<float *>(workspace);
+  const DotPlan dp = dot_plan(N, n, d, b);
+  const int64_t units = dp.groups * dp.segs * b;
+  const dim3 g1(unsigned(ceil_div(units, kGradWaves)));
+  if (dp.rows == 4)
+    hipLaunchKernelGGL(dot_kernel<4>, g1, dim3(kGradThreads), 0, stream, X, W, int64_t(N) * n, d, dp.groups,
+                       dp.segs, dp.seglen, units, zpart);
+  else
+    hipLaunchKernelGGL(dot_kernel<1>, g1, dim3(kGradThreads), 0, stream, X, W, int64_t(N) * n, d, dp.groups,
+                       dp.segs, dp.seglen, units, zpart);
+  // few column tiles: four waves of a block split the rows instead of the columns
+  const int64_t wide = ceil_div(d, 4 * kGradThreads) * N * b;
+  if (wide >= 4 * int64_t(cu_count())) {
+    hipLaunchKernelGGL(xtr_kernel<1>, dim3(unsigned(wide)), dim3(kGradThreads), 0, stream, X, y, zpart, N, n, d,
+                       ceil_div(d, 4 * kGradThreads), dp.segs, loss, G);
   } else {
-    hipLaunchKernelGGL(residual_kernel<1>, g1, dim3(kGradThreads), 0, stream, X, y, W, rows,
-                       int64_t(N) * n, d, loss, resid);
-    hipLaunchKernelGGL(xtr_kernel<1>, g2, dim3(kGradThreads), 0, stream, X, resid, N, n, d, tiles, G);
+    const int64_t tiles = ceil_div(d, kGradThreads);
+    hipLaunchKernelGGL(xtr_kernel<4>, dim3(unsigned(tiles * N * b)), dim3(kGradThreads), 0, stream, X, y, zpart, N,
+                       n, d, tiles, dp.segs, loss, G);
   }
   return launch_status();
 }
