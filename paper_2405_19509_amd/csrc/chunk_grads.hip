@@ -15,8 +15,8 @@
 // block) and reduce_partials_kernel sums, for every chunk, the partials of
 // the blocks that touched it, in block order: one read of X, deterministic.
 //
-// Many points (b >= 16, b % 4 == 0, d % 4 == 0): two fp32 MFMA GEMMs per chunk
-// (chunk_grads_mfma.hip).
+// Many points (from 4 on, from 2 where the fused path does not apply): two matrix-core GEMMs
+// per chunk (chunk_grads_mfma.hip), two reads of X in all.
 //
 // General path (any d, any alignment): two streaming kernels
 //   dot_kernel   x.w of 4 rows (few rows: 1) over a segment of the columns by one wave, 16-byte
@@ -33,9 +33,9 @@
 namespace gcx {
 
 // multi-point path on the matrix cores (chunk_grads_mfma.hip)
-bool mfma_eligible(int64_t d, int b);
+bool mfma_eligible(int N, int n, int64_t d, int b, bool fused);
 size_t mfma_workspace_bytes(int N, int n, int64_t d, int b);
-int launch_mfma_grads(const float *X, const float *y, const float *W, int N, int n, int64_t d, int b,
+void launch_mfma_grads(const float *X, const float *y, const float *W, int N, int n, int64_t d, int b,
                       int loss, float *G, void *workspace, hipStream_t st);
 
 namespace {
@@ -321,7 +321,7 @@ bool grad_sizes_ok(int32_t N, int32_t n, int64_t d, int32_t b) {
 
 extern "C" size_t gc_chunk_grads_workspace_size(int32_t N, int32_t n, int64_t d, int32_t b) {
   if (!grad_sizes_ok(N, n, d, b)) return 0;
-  if (gcx::mfma_eligible(d, b)) return gcx::mfma_workspace_bytes(N, n, d, b);
+  if (gcx::mfma_eligible(N, n, d, b, fused_ok(d))) return gcx::mfma_workspace_bytes(N, n, d, b);
   if (fused_ok(d)) {
     const gcx::FusedPlan fp = gcx::fused_plan(N, n);
     return sizeof(float) * size_t(b) * size_t(fp.blocks) * 2 * size_t(d);
@@ -345,10 +345,10 @@ extern "C" int gc_chunk_grads(const float *X, const float *y, const float *W, in
   const int dev = check_device();
   if (dev != GC_OK) return dev;
   (void)hipGetLastError();
-  if (mfma_eligible(d, b)) {
-    if (!vec4 || !aligned16(y) || !aligned16(workspace)) return GC_EINVAL;
-    const int st = launch_mfma_grads(X, y, W, N, n, d, b, loss, G, workspace, stream);
-    if (st != GC_OK) return st;
+  if (mfma_eligible(N, n, d, b, fused_ok(d))) {
+    // 16 points or more in whole quads are taken on 16-byte boundaries only
+    if (b >= 16 && b % 4 == 0 && d % 4 == 0 && (!vec4 || !aligned16(y) || !aligned16(workspace))) return GC_EINVAL;
+    launch_mfma_grads(X, y, W, N, n, d, b, loss, G, workspace, stream);
     return launch_status();
   }
   if (vec4 && fused_ok(d) && aligned16(workspace)) {

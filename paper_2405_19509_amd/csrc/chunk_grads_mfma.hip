@@ -1,29 +1,33 @@
-// Chunk gradients at many evaluation points on the fp32 matrix cores.
+// Chunk gradients at many evaluation points on the bf16 matrix cores.
 //
 // With b evaluation points W [b][d] the per-chunk gradient (Sec. 1) is two
 // dense contractions per chunk i:
 //   Z_i = X_i W^T          [n][b]   (K = d)
 //   U_i = loss'(Z_i) - y_i [n][b]   (residuals, broadcast over the points)
 //   G_i = U_i^T X_i        [b][d]   (K = n),   stored as G[q][i][:]
-// Both run as 128 x 128-tiled GEMMs on v_mfma_f32_32x32x2f32: a 256-thread
-// block holds a 128 x 128 output tile as four 64 x 64 wave tiles (2 x 2 MFMA
-// tiles of 32 x 32 each); operands are staged through double-buffered LDS,
-// 32 values of K per stage, with the global loads of the stage after next in
-// flight (two register sets) while the current one feeds the MFMAs.  fp32 in,
-// fp32 accumulation.
 //
-//   zw_kernel     Z partials over a split of K = d (split-K keeps >= ~3 waves
-//                 of blocks on 256 CUs); both operands are K-contiguous, held
-//                 in LDS as [row][k] and read four k at a time: within a
-//                 stage lane half h takes the k in [16h, 16h + 16), so each
-//                 lane's operands for four consecutive MFMAs are one 16-byte
-//                 LDS read (the K order inside a stage is a permutation shared
-//                 by both operands, so the sum is unchanged).
-//   resid_kernel  U = loss'(sum of the partials, in split order) - y.
-//   utx_kernel    G tiles; both operands are row-contiguous along M and N,
-//                 held in LDS as [k][row].
-// Along the points both kernels use 128-wide tiles when b is a multiple of 128 and
-// 64-wide tiles otherwise, so b = 64 does not spend half the MFMAs on padding.
+// Arithmetic: every fp32 operand v is split into three bf16 parts v = v1 + v2 + v3 (X by
+// rounding to nearest, W and U by truncation) and the six products of parts i + j <= 4 are
+// kept; those dropped stay below 2^-22 of the term, with random signs.  Products of two
+// bf16 values are exact in fp32 and v_mfma_f32_32x32x16_bf16 accumulates them in fp32, the
+// products v1 w1 in one accumulator and the five small ones in another, so only one addition
+// per 16 terms rounds at the sum's own size (fp32 matrix instructions: one per 2 terms).
+// A NaN in a tile's sums (an infinity's or a NaN's parts, or values near the largest float
+// that round up) makes its wave compute the tile again with the fp32 matrix instructions, which
+// treat infinities as the vector units do.
+//
+//   zw_kernel     Z partials over a split of K = d, for 128 of the N n sample rows and up to
+//                 128 points per block.  A wave loads its 32 rows of X from memory in the
+//                 matrix operand's layout (32 neighbouring bytes of a row per instruction, four
+//                 instructions a cache line), two stages of 32 k ahead; W's parts are shared
+//                 through LDS by the block's four waves.
+//   resid_kernel  U = loss'(sum of the partials, in split order) - y, split and laid out as
+//                 the next kernel's operand.
+//   utx_kernel    G tiles: a wave loads 32 PW positions of the rows of X straight in the
+//                 operand's layout (contiguous across the lanes), U's parts come through LDS.
+//                 Chunks are taken in descending order: the last ones read by zw_kernel are
+//                 still in the memory-side cache.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -31,303 +35,518 @@
 namespace gcx {
 namespace {
 
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+// rows of X, W and G start on any float
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+template <int N>
+struct Floats;
+template <>
+struct Floats<2> { typedef float T __attribute__((ext_vector_type(2), aligned(4))); };
+template <>
+struct Floats<4> { typedef float T __attribute__((ext_vector_type(4), aligned(4))); };
 
-constexpr int kTM = 128;  // tile rows
-constexpr int kTN = 128;  // tile cols
-constexpr int kTK = 32;   // K per stage
-constexpr int kMThreads = 256;
-constexpr int kPadK = 4;  // [row][k] LDS rows: 36 floats apart, conflict-free 16-byte reads
+constexpr int kZThreads = 256;                    // zw_kernel
+constexpr int kZRows = 32 * (kZThreads / kWave);  // sample rows per block
+constexpr int kMThreads = 256;                    // utx_kernel
+constexpr int kMWaves = kMThreads / kWave;
+constexpr int kZK = 32;               // k per stage of zw_kernel
 
-__device__ __forceinline__ v16f mfma32(float a, float b, v16f c) {
+__device__ __forceinline__ v16f mfma16(v8bf a, v8bf b, v16f c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ v16f mfma2(float a, float b, v16f c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-__device__ __forceinline__ float4 ld4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
-
-__device__ __forceinline__ float comp(const float4 &v, int e) {
-  return e == 0 ? v.x : (e == 1 ? v.y : (e == 2 ? v.z : v.w));
+// Eight values in three bf16 parts, each the rounding of what the earlier ones leave; the
+// subtractions (one dot product each: v - 1 part + 0 other) are exact and what the third part
+// leaves is below 2^-25 of the value.
+__device__ __forceinline__ void split3_rne(const float (&v)[8], v8bf (&g)[3]) {
+  // (-1, 0) and (0, -1), kept in registers: as an instruction's inline constant the first is read
+  // otherwise
+  uint32_t l = 0x0000bf80u, h = 0xbf800000u;
+  asm("" : "+s"(l), "+s"(h));
+  const v2bf lo = __builtin_bit_cast(v2bf, l), hi = __builtin_bit_cast(v2bf, h);
+  v4u p[3];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float a = v[2 * j], b = v[2 * j + 1];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const v2bf u = __builtin_convertvector(v2f{a, b}, v2bf);
+      p[s][j] = __builtin_bit_cast(uint32_t, u);
+      a = __builtin_amdgcn_fdot2_f32_bf16(u, lo, a, false);
+      b = __builtin_amdgcn_fdot2_f32_bf16(u, hi, b, false);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 3; ++s) g[s] = __builtin_bit_cast(v8bf, p[s]);
 }
 
-// Z partial: Zp[s][i][r][q] = sum_{x in split s} X[i][r][x] * W[q][x].  TB = tile width
-// along the points (128, or 64 when b is not a multiple of 128: no padded half tile).
-template <int TB>
-__global__ __launch_bounds__(kMThreads, 2) void zw_kernel(const float *__restrict__ X,
-                                                          const float *__restrict__ W, int N, int n,
-                                                          int64_t d, int b, int splits, int64_t kper,
-                                                          int mtiles, int ntiles,
-                                                          float *__restrict__ Zp) {
-  constexpr int NB = TB / 64;  // 32-wide MFMA blocks per wave along the points
-  __shared__ __align__(16) float As[2][kTM][kTK + kPadK];
-  __shared__ __align__(16) float Bs[2][TB][kTK + kPadK];
+// Two values in three parts by truncation: v = v1 + v2 + v3 exactly (|v| >= 2^-100), packed.
+__device__ __forceinline__ void split3_trunc(float a, float b, uint32_t (&p)[3]) {
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+    p[s] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+    a -= __uint_as_float(ua & 0xffff0000u);
+    b -= __uint_as_float(ub & 0xffff0000u);
+  }
+}
+
+// a value from its truncated parts: the first alone where it is an infinity or a NaN
+__device__ __forceinline__ float join3(uint16_t p1, uint16_t p2, uint16_t p3) {
+  const float a = __uint_as_float(uint32_t(p1) << 16);
+  const float r = __uint_as_float(uint32_t(p2) << 16) + __uint_as_float(uint32_t(p3) << 16);
+  return fabsf(a) < __builtin_huge_valf() ? a + r : a;
+}
+
+// big += a1 b1; small += the other products kept, the smallest first
+__device__ __forceinline__ void products(const v8bf (&a)[3], const v8bf (&b)[3], v16f &big, v16f &small) {
+  small = mfma16(a[2], b[0], small);
+  small = mfma16(a[1], b[1], small);
+  small = mfma16(a[0], b[2], small);
+  small = mfma16(a[1], b[0], small);
+  small = mfma16(a[0], b[1], small);
+  big = mfma16(a[0], b[0], big);
+}
+
+// Zp[s][r][q] = sum_{k in split s} X[r][k] * W[q][k] for the rows r of all chunks.
+//   A (32 rows x 16 k): lane (h, li) holds row li at k = 4h .. 4h + 3 and 8 + 4h .. 8 + 4h + 3
+//   of each 16; B (W) the same k of point li, its parts in LDS as the lanes read them:
+//   Ws[buffer][16-step][part][point tile][lane] of 16 bytes.
+template <int QT>  // point tiles of 32 per block
+__global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(QT == 1 ? 4 : (QT == 2 ? 3 : 2)))) void zw_kernel(const float *__restrict__ X, const float *__restrict__ W,
+                                                          int64_t R, int64_t d, int b, int splits, int64_t kper,
+                                                          int qblocks, float *__restrict__ Zp) {
+  __shared__ __align__(16) uint2 Ws[2][2][3][QT][kWave][2];
   int64_t bid = blockIdx.x;
-  const int nt = int(bid % ntiles);
-  bid /= ntiles;
-  const int mt = int(bid % mtiles);
-  bid /= mtiles;
+  const int q0 = int(bid % qblocks) * 32 * QT;
+  bid /= qblocks;
   const int s = int(bid % splits);
-  const int64_t i = bid / splits;
-  const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
-  const int wm = wave >> 1, wn = wave & 1, h = lane >> 5, li = lane & 31;
-  const float *Xi = X + i * int64_t(n) * d;
+  const int64_t r0 = bid / splits * kZRows;
+  const int t = threadIdx.x, lane = t % kWave, wave = t / kWave, h = lane >> 5, li = lane & 31;
   const int64_t k0 = int64_t(s) * kper;
   const int64_t k1 = k0 + kper < d ? k0 + kper : d;
-  const int lrow = t >> 3, lk = (t & 7) * 4;
+  const int64_t row = r0 + 32 * wave + li;
+  const float *xr = X + (row < R ? row : R - 1) * d;  // rows past the last repeat it, not stored
 
-  // two register sets: the stage after next loads while this stage feeds the MFMAs
-  float4 ra[2][4], rb[2][4];
-  auto gload = [&](int set, int64_t kb) {
+  float rx[16];  // a stage of X: 4 times 4 neighbouring k
+  auto xload = [&](int64_t kb) {
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const int row = lrow + 32 * p;
-      const int64_t k = kb + lk;
-      const int r = mt * kTM + row, q = nt * TB + row;
-      ra[set][p] = (r < n && k < k1) ? ld4(Xi + int64_t(r) * d + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-      rb[set][p] = (row < TB && q < b && k < k1) ? ld4(W + int64_t(q) * d + k)
-                                                 : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int u = 0; u < 4; ++u) {
+      const v4fu v = *reinterpret_cast<const v4fu *>(xr + kb + 8 * u + 4 * h);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rx[4 * u + e] = v[e];
     }
   };
-  auto lstore = [&](int set, int buf) {
+  // unit c = t + 256 i of a stage of W: point c / 8, k = 4 (c % 8) .. + 3
+  float rw[QT][4];
+  auto wload = [&](int64_t kb) {
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      *reinterpret_cast<float4 *>(&As[buf][lrow + 32 * p][lk]) = ra[set][p];
-      if (lrow + 32 * p < TB) *reinterpret_cast<float4 *>(&Bs[buf][lrow + 32 * p][lk]) = rb[set][p];
+    for (int i = 0; i < QT; ++i) {
+      const int q = q0 + t / 8 + 32 * i;
+      const v4fu v = *reinterpret_cast<const v4fu *>(W + int64_t(q < b ? q : b - 1) * d + kb + 4 * (t % 8));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rw[i][e] = v[e];
+    }
+  };
+  auto wstore = [&](int buf) {
+    const int kq = t % 8, l = 32 * (kq & 1) + t / 8;  // the lane that holds these k
+#pragma unroll
+    for (int i = 0; i < QT; ++i) {
+      uint32_t lo[3], hi[3];
+      split3_trunc(rw[i][0], rw[i][1], lo);
+      split3_trunc(rw[i][2], rw[i][3], hi);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) Ws[buf][kq >> 2][p][i][l][(kq >> 1) & 1] = make_uint2(lo[p], hi[p]);
     }
   };
 
-  v16f acc[2][NB];
+  v16f big[QT], small[QT];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int i = 0; i < QT; ++i) big[i] = small[i] = v16f{};
+  // the products of the stage in rx, its W in LDS buffer buf; next(): what to issue once rx is free
+  auto stage = [&](int buf, auto next) {
+    v8bf a[2][3];
 #pragma unroll
-    for (int c = 0; c < NB; ++c)
+    for (int m = 0; m < 2; ++m) {
+      float v[8];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][c][v] = 0.f;
-
-  const int64_t nst = ceil_div(k1 - k0, kTK);
-  gload(0, k0);
-  if (nst > 1) gload(1, k0 + kTK);
-  lstore(0, 0);
-  __syncthreads();
-  // stage st is in LDS buffer st & 1, stage st + 1 in register set (st + 1) & 1
-  auto stage = [&](int64_t st, auto setc) {
-    constexpr int SET = decltype(setc)::value;  // st & 1
-    if (st + 2 < nst) gload(SET, k0 + (st + 2) * kTK);
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) {
-      float4 a[2], bb[NB];
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb) a[mb] = ld4(&As[SET][wm * 64 + mb * 32 + li][h * 16 + s4 * 4]);
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        bb[nb] = ld4(&Bs[SET][wn * (TB / 2) + nb * 32 + li][h * 16 + s4 * 4]);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-            acc[mb][nb] = mfma32(comp(a[mb], e), comp(bb[nb], e), acc[mb][nb]);
+      for (int e = 0; e < 8; ++e) v[e] = rx[8 * m + e];
+      split3_rne(v, a[m]);
     }
-    if (st + 1 < nst) lstore(SET ^ 1, SET ^ 1);
+    next();
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int i = 0; i < QT; ++i) {
+        v8bf w[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) w[p] = *reinterpret_cast<const v8bf *>(&Ws[buf][m][p][i][lane][0]);
+        products(a[m], w, big[i], small[i]);
+      }
+  };
+  const int64_t nst = (k1 - k0) / kZK;  // whole stages
+  if (nst > 0) {
+    wload(k0);
+    xload(k0);
+    wstore(0);
+    if (nst > 1) wload(k0 + kZK);
     __syncthreads();
-  };
-  for (int64_t st = 0; st < nst; st += 2) {
-    stage(st, std::integral_constant<int, 0>{});
-    if (st + 1 < nst) stage(st + 1, std::integral_constant<int, 1>{});
+  }
+  // stage st: its X in rx, its W in LDS buffer st & 1, the next W in rw
+  for (int64_t st = 0; st < nst; ++st) {
+    stage(int(st & 1), [&] {
+      if (st + 1 < nst) xload(k0 + (st + 1) * kZK);
+    });
+    if (st + 1 < nst) {
+      wstore(int(st & 1) ^ 1);
+      if (st + 2 < nst) wload(k0 + (st + 2) * kZK);
+    }
+    __syncthreads();
+  }
+  if (const int left = int(k1 - k0 - nst * kZK); left > 0) {  // the last k: zeros past them
+    const int64_t kb = k0 + nst * kZK;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int k = 8 * (e / 4) + 4 * h + e % 4;
+      const float v = xr[kb + (k < left ? k : 0)];
+      rx[e] = k < left ? v : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < QT; ++i) {
+      const int q = q0 + t / 8 + 32 * i;
+      const float *src = W + int64_t(q < b ? q : b - 1) * d + kb;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = 4 * (t % 8) + e;
+        const float v = src[k < left ? k : 0];
+        rw[i][e] = k < left ? v : 0.f;
+      }
+    }
+    wstore(0);
+    __syncthreads();
+    stage(0, [] {});
   }
 
-  float *Zs = Zp + (int64_t(s) * N + i) * int64_t(n) * b;
+  bool bad = false;
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
+  for (int i = 0; i < QT; ++i)
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+    for (int v = 0; v < 16; ++v) {
+      big[i][v] += small[i][v];
+      bad = bad || big[i][v] != big[i][v];
+    }
+  if (__any(bad)) {  // the tile on the fp32 matrix instructions
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int r = mt * kTM + wm * 64 + mb * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-        const int q = nt * TB + wn * (TB / 2) + nb * 32 + li;
-        if (r < n && q < b) Zs[int64_t(r) * b + q] = acc[mb][nb][v];
+    for (int i = 0; i < QT; ++i) {
+      const int q = q0 + 32 * i + li;
+      const float *wr = W + int64_t(q < b ? q : b - 1) * d;
+      big[i] = v16f{};
+      for (int64_t k = k0 + h; k - h < k1; k += 2) {
+        const float x = xr[k < k1 ? k : k1 - 1], w = wr[k < k1 ? k : k1 - 1];
+        big[i] = mfma2(k < k1 ? x : 0.f, k < k1 ? w : 0.f, big[i]);
       }
+    }
+  }
+  float *Zs = Zp + (int64_t(s) * R + r0 + 32 * wave) * b + q0;
+#pragma unroll
+  for (int i = 0; i < QT; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int r = 8 * (v >> 2) + 4 * h + (v & 3);
+      if (r0 + 32 * wave + r < R && q0 + 32 * i + li < b) Zs[int64_t(r) * b + 32 * i + li] = big[i][v];
+    }
 }
 
-// U[i][r][q] = loss'(sum_s Zp[s][i][r][q]) - y[i][r], the splits summed in order.
-__global__ void resid_kernel(const float *__restrict__ Zp, const float *__restrict__ y, int64_t total,
-                             int b, int splits, int loss, float *__restrict__ Uo) {
+// U[i][r][q] = loss'(sum_s Zp[s][i n + r][q]) - y[i][r], the splits summed in order, as the
+// parts that utx_kernel's lanes read: one thread forms rows 16 ks + 2 j + h, j < 8, of point 32 qt + li,
+// Uf[i][ks][qt][part][lane] of 16 bytes, zero past the rows and the points.
+__global__ __launch_bounds__(256) void resid_kernel(const float *__restrict__ Zp, const float *__restrict__ y,
+                                                    int64_t R, int n, int b, int splits, int loss, int ksteps,
+                                                    int qtiles, int64_t units, uint4 *__restrict__ Uf) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= total) return;
-  float z = 0.f;
-  for (int s = 0; s < splits; ++s) z += Zp[int64_t(s) * total + e];
-  const float yv = y[e / b];
-  Uo[e] = loss == GC_LOSS_LOGISTIC ? 1.0f / (1.0f + expf(-z)) - yv : z - yv;
+  if (e >= units) return;
+  const int lane = int(e % kWave), h = lane >> 5, li = lane & 31;
+  int64_t f = e / kWave;
+  const int q = 32 * int(f % qtiles) + li;
+  const int r = 16 * int(f / qtiles % ksteps) + h;
+  const int64_t i = f / qtiles / ksteps;
+  float z[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) z[j] = 0.f;
+  // loads past the rows or the points repeat one inside, so that all are in flight at once
+  const float *src[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) src[j] = Zp + (i * n + (r + 2 * j < n ? r + 2 * j : n - 1)) * b + (q < b ? q : b - 1);
+#pragma unroll 4
+  for (int s = 0; s < splits; ++s)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) z[j] += src[j][int64_t(s) * R * b];
+  uint32_t p[4][3];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const bool in = r + 2 * j < n && q < b;
+    const float yv = y[i * n + (in ? r + 2 * j : 0)];
+    const float u = loss == GC_LOSS_LOGISTIC ? 1.0f / (1.0f + expf(-z[j])) - yv : z[j] - yv;
+    z[j] = in ? u : 0.f;
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) split3_trunc(z[2 * j], z[2 * j + 1], p[j]);
+#pragma unroll
+  for (int s = 0; s < 3; ++s) Uf[(f * 3 + s) * kWave + lane] = make_uint4(p[0][s], p[1][s], p[2][s], p[3][s]);
 }
 
-// G[q][i][x] = sum_r U[i][r][q] * X[i][r][x]; TB = tile height along the points.
-template <int TB>
-__global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const float *__restrict__ Ui,
-                                                           const float *__restrict__ X, int N, int n,
-                                                           int64_t d, int b, int mtiles,
-                                                           int64_t ntiles, float *__restrict__ G) {
-  constexpr int MB = TB / 64;  // 32-high MFMA blocks per wave along the points
-  __shared__ __align__(16) float As[2][kTK][TB + 4];
-  __shared__ __align__(16) float Bs[2][kTK][kTN + 4];
-  int64_t bid = blockIdx.x;
-  const int mt = int(bid % mtiles);  // the point tiles of one X tile run back to back
-  bid /= mtiles;
-  const int64_t nt = bid % ntiles;
-  const int64_t i = bid / ntiles;
-  const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
-  const int wm = wave >> 1, wn = wave & 1, h = lane >> 5, li = lane & 31;
+// G[q][i][x] = sum_r U[i][r][q] * X[i][r][x] for QT point tiles and 4 x 32 PW positions per block.
+//   B (16 rows x 32 positions): lane (h, li) holds rows h, h + 2, .. h + 14 of each 16 at positions
+//   PW li .. + PW - 1, PW separate 32-wide tiles
+template <int QT, int PW>
+__global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const uint4 *__restrict__ Uf, const float *__restrict__ X,
+                                                           int N, int n, int64_t d, int b, int ksteps, int qtiles,
+                                                           int qblocks, int64_t tiles, float *__restrict__ G) {
+  using VT = typename Floats<PW>::T;
+  constexpr int kUnits = QT * 3 * kWave;  // 16-byte pieces of U's parts per stage of 16 rows
+  constexpr int kPer = (kUnits + kMThreads - 1) / kMThreads;
+  __shared__ __align__(16) uint4 Us[2][kUnits];
+  // the point blocks of one tile of X: eight apart, so on one XCD (round-robin dispatch)
+  const int64_t bid = blockIdx.x;
+  const int qb = int(bid / 8 % qblocks);
+  const int64_t item = bid / 8 / qblocks * 8 + bid % 8;
+  if (item >= tiles * N) return;  // the whole block
+  const int64_t i = N - 1 - item / tiles;
+  const int t = threadIdx.x, lane = t % kWave, h = lane >> 5, li = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int64_t x0 = (item % tiles * kMWaves + wave) * 32 * PW;
+  const int64_t x = x0 + PW * li;
+  const bool inside = x0 + 32 * PW <= d;
   const float *Xi = X + i * int64_t(n) * d;
-  const float *Uc = Ui + i * int64_t(n) * b;
-  const int lrow = t >> 5, lc = (t & 31) * 4;
+  const uint4 *Ui = Uf + (i * ksteps * qtiles + qb * QT) * 3 * kWave;
+  const int units = (qtiles - qb * QT < QT ? qtiles - qb * QT : QT) * 3 * kWave;
 
-  // two register sets: the stage after next loads while this stage feeds the MFMAs
-  float4 ra[2][4], rb[2][4];
-  auto gload = [&](int set, int kb) {
+  const uint32_t loff = uint32_t(h) * uint32_t(d) * 4u + uint32_t(PW * li) * 4u;  // d <= 2^28
+  float rx[2][PW][8];
+  auto xload = [&](auto setc, int ks) {
+    constexpr int SET = decltype(setc)::value;
+    if (inside && 16 * ks + 16 <= n) {
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const int r = kb + lrow + 8 * p;
-      const int q = mt * TB + lc;
-      const int64_t x = nt * kTN + lc;
-      ra[set][p] = (lc < TB && r < n && q < b) ? ld4(Uc + int64_t(r) * b + q)
-                                               : make_float4(0.f, 0.f, 0.f, 0.f);
-      rb[set][p] = (r < n && x < d) ? ld4(Xi + int64_t(r) * d + x) : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int j = 0; j < 8; ++j) {
+        const char *src = reinterpret_cast<const char *>(Xi + int64_t(16 * ks + 2 * j) * d + x0);  // the same for all lanes
+        const VT v = *reinterpret_cast<const VT *>(src + loff);
+#pragma unroll
+        for (int w = 0; w < PW; ++w) rx[SET][w][j] = v[w];
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int r = 16 * ks + 2 * j + h;  // past the last row: that row again, times zero
+        const float *src = Xi + int64_t(r < n ? r : n - 1) * d;
+#pragma unroll
+        for (int w = 0; w < PW; ++w) rx[SET][w][j] = src[x + w < d ? x + w : d - 1];
+      }
     }
   };
-  auto lstore = [&](int set, int buf) {
+  uint4 ru[kPer];
+  auto uload = [&](int ks) {
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      if (lc < TB) *reinterpret_cast<float4 *>(&As[buf][lrow + 8 * p][lc]) = ra[set][p];
-      *reinterpret_cast<float4 *>(&Bs[buf][lrow + 8 * p][lc]) = rb[set][p];
+    for (int c = 0; c < kPer; ++c) {
+      const int e = t + c * kMThreads;
+      ru[c] = e < units ? Ui[int64_t(ks) * qtiles * 3 * kWave + e] : make_uint4(0u, 0u, 0u, 0u);
     }
   };
+  auto ustore = [&](int buf) {
+#pragma unroll
+    for (int c = 0; c < kPer; ++c)
+      if (t + c * kMThreads < kUnits) Us[buf][t + c * kMThreads] = ru[c];
+  };
 
-  v16f acc[MB][2];
+  v16f big[QT][PW], small[QT][PW];
 #pragma unroll
-  for (int a = 0; a < MB; ++a)
+  for (int q = 0; q < QT; ++q)
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][c][v] = 0.f;
-
-  const int nst = int(ceil_div(n, kTK));
-  gload(0, 0);
-  if (nst > 1) gload(1, kTK);
-  lstore(0, 0);
+    for (int w = 0; w < PW; ++w) big[q][w] = small[q][w] = v16f{};
+  using Zero = std::integral_constant<int, 0>;
+  using One = std::integral_constant<int, 1>;
+  uload(0);
+  xload(Zero{}, 0);
+  if (ksteps > 1) xload(One{}, 1);
+  ustore(0);
+  if (ksteps > 1) uload(1);
   __syncthreads();
-  // stage st is in LDS buffer st & 1, stage st + 1 in register set (st + 1) & 1
-  auto stage = [&](int st, auto setc) {
-    constexpr int SET = decltype(setc)::value;  // st & 1
-    if (st + 2 < nst) gload(SET, (st + 2) * kTK);
+  // stage ks: its X in register set ks & 1, its U in LDS buffer ks & 1, the next U in ru
+  auto stage = [&](int ks, auto setc) {
+    constexpr int SET = decltype(setc)::value;
+    v8bf xs[PW][3];
 #pragma unroll
-    for (int s = 0; s < kTK / 2; ++s) {
-      float a[MB], bb[2];
+    for (int w = 0; w < PW; ++w) split3_rne(rx[SET][w], xs[w]);
+    if (ks + 2 < ksteps) xload(setc, ks + 2);
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) a[mb] = As[SET][2 * s + h][wm * (TB / 2) + mb * 32 + li];
+    for (int q = 0; q < QT; ++q) {
+      v8bf u[3];
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) bb[nb] = Bs[SET][2 * s + h][wn * 64 + nb * 32 + li];
+      for (int p = 0; p < 3; ++p) u[p] = *reinterpret_cast<const v8bf *>(&Us[SET][(q * 3 + p) * kWave + lane]);
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = mfma32(a[mb], bb[nb], acc[mb][nb]);
+      for (int w = 0; w < PW; ++w) products(u, xs[w], big[q][w], small[q][w]);
     }
-    if (st + 1 < nst) lstore(SET ^ 1, SET ^ 1);
+    if (ks + 1 < ksteps) {
+      ustore(SET ^ 1);
+      if (ks + 2 < ksteps) uload(ks + 2);
+    }
     __syncthreads();
   };
-  for (int st = 0; st < nst; st += 2) {
-    stage(st, std::integral_constant<int, 0>{});
-    if (st + 1 < nst) stage(st + 1, std::integral_constant<int, 1>{});
+  for (int ks = 0; ks < ksteps; ks += 2) {
+    stage(ks, Zero{});
+    if (ks + 1 < ksteps) stage(ks + 1, One{});
   }
 
+  bool bad = false;
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+  for (int q = 0; q < QT; ++q)
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
+    for (int w = 0; w < PW; ++w)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int q = mt * TB + wm * (TB / 2) + mb * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-        const int64_t x = nt * kTN + wn * 64 + nb * 32 + li;
-        if (q < b && x < d) G[(int64_t(q) * N + i) * d + x] = acc[mb][nb][v];
+        big[q][w][v] += small[q][w][v];
+        bad = bad || big[q][w][v] != big[q][w][v];
       }
+  if (__any(bad)) {  // the tile on the fp32 matrix instructions, from U's joined parts
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+      if (qb * QT + q >= qtiles) break;
+#pragma unroll
+      for (int w = 0; w < PW; ++w) big[q][w] = v16f{};
+      for (int r = h; r - h < n; r += 2) {
+        const uint16_t *up = reinterpret_cast<const uint16_t *>(
+            Ui + (int64_t(r / 16) * qtiles + q) * 3 * kWave + 32 * (r % 2) + li) + r / 2 % 8;
+        const bool in = r < n;  // rows past n are zero in U
+        const float u = in ? join3(up[0], up[8 * kWave], up[16 * kWave]) : 0.f;
+        const float *src = Xi + int64_t(in ? r : n - 1) * d;
+#pragma unroll
+        for (int w = 0; w < PW; ++w) {
+          const float v = src[x + w < d ? x + w : d - 1];
+          big[q][w] = mfma2(u, in ? v : 0.f, big[q][w]);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < QT; ++q)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int qq = (qb * QT + q) * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+      if (qq >= b) continue;
+      float *dst = G + (int64_t(qq) * N + i) * d + x;
+      if (inside) {
+        VT o;
+#pragma unroll
+        for (int w = 0; w < PW; ++w) o[w] = big[q][w][v];
+        *reinterpret_cast<VT *>(dst) = o;
+      } else {
+#pragma unroll
+        for (int w = 0; w < PW; ++w)
+          if (x + w < d) dst[w] = big[q][w][v];
+      }
+    }
 }
-
-}  // namespace
 
 // Launch plan shared by the workspace-size query and the launch.
 struct MfmaPlan {
-  int tb;  // tile width along the points: 128, or 64 when b is not a multiple of 128
+  int zqt, uqt, upw;          // point tiles per block of each kernel, positions per lane
+  int zqblocks, uqblocks;
   int splits;
-  int64_t kper;
-  int mtiles1, ntiles1;  // zw tiles over (rows r, points q)
-  size_t zp_floats, u_floats;
+  int64_t kper, rblocks;
+  int ksteps, qtiles;         // U's parts: steps of 16 rows, tiles of 32 points
+  int64_t blocks1, units, tiles, blocks2;
+  size_t zp_bytes, u_bytes;
 };
 
 MfmaPlan mfma_plan(int N, int n, int64_t d, int b) {
   MfmaPlan pl{};
-  pl.tb = b % 128 == 0 ? 128 : 64;
-  pl.mtiles1 = int(ceil_div(n, kTM));
-  pl.ntiles1 = int(ceil_div(b, pl.tb));
-  const int64_t tiles = int64_t(N) * pl.mtiles1 * pl.ntiles1;
-  // K = d split (at most 16 ways) so that the blocks fill whole rounds of the 512 resident
-  // ones (two per CU on 256 CUs): a grid that overshoots a round by a little runs its last
-  // round mostly empty.  Each split is charged half a percent (its Z partials, written and
-  // summed again, and a block prologue per tile); ties go to fewer splits.
-  constexpr int64_t kResident = 512;
-  int64_t splits = 1;
-  double best = -1.0;
-  for (int64_t sp = 1; sp <= 16; ++sp) {
-    const int64_t kp = ceil_div(ceil_div(d, sp), kTK) * kTK;
-    if (ceil_div(d, kp) != sp) continue;  // stage rounding merges splits: a smaller sp covers it
-    const int64_t blocks = tiles * sp;
-    const double fill = double(blocks) / double(ceil_div(blocks, kResident) * kResident);
-    const double score = fill - 0.005 * double(sp);
-    if (score > best + 1e-9) {
-      best = score;
-      splits = sp;
+  pl.qtiles = int(ceil_div(b, 32));
+  const int64_t R = int64_t(N) * n;
+  const int64_t stages = ceil_div(d, kZK);
+  pl.rblocks = ceil_div(R, kZRows);
+  pl.zqt = pl.qtiles <= 2 ? pl.qtiles : 4;
+  // fewer point tiles per block where a few blocks are all there is
+  while (pl.zqt > 1 && pl.rblocks * ceil_div(pl.qtiles, pl.zqt) * ceil_div(stages, 4) < 256) pl.zqt /= 2;
+  pl.upw = 2;
+  pl.tiles = ceil_div(d, int64_t(32) * pl.upw * kMWaves);
+  pl.uqt = pl.qtiles == 1 || pl.tiles * N * ceil_div(pl.qtiles, 2) < 256 ? 1 : 2;
+  pl.zqblocks = int(ceil_div(pl.qtiles, pl.zqt));
+  pl.uqblocks = int(ceil_div(pl.qtiles, pl.uqt));
+  // K = d split so that the blocks fill whole rounds of the resident ones (four, three or two
+  // per CU by point tiles, on 256 CUs); a block costs about 8 stages beyond its own (its prologue,
+  // its Z partials written and summed again), and the sums about one per split.  At most 64
+  // stages per block: 128 additions at a partial's own size (n = 512, d = 16384, 4 points: the
+  // gradients' error 1.4e-7, with 103 stages 1.7e-7, on the vector units 1.6e-7).
+  const int64_t resident = 256 * (pl.zqt == 1 ? 4 : (pl.zqt == 2 ? 3 : 2));
+  constexpr int64_t kExtra = 8, kMaxStages = 64;
+  const int64_t tiles = pl.rblocks * pl.zqblocks;
+  const int64_t least = ceil_div(stages, kMaxStages);
+  int64_t best = -1;
+  for (int64_t sp = least; sp <= std::min(std::max<int64_t>(least + 8, 64), stages); ++sp) {
+    const int64_t nst = ceil_div(stages, sp);
+    const int64_t splits = ceil_div(stages, nst);
+    const int64_t cost = ceil_div(tiles * splits, resident) * (nst + kExtra) + splits;
+    if (best < 0 || cost < best) {
+      best = cost;
+      pl.splits = int(splits);
+      pl.kper = nst * kZK;
     }
   }
-  const int64_t kper = ceil_div(ceil_div(d, splits), kTK) * kTK;
-  splits = ceil_div(d, kper);
-  pl.splits = int(splits);
-  pl.kper = kper;
-  pl.zp_floats = size_t(splits) * N * size_t(n) * b;
-  pl.u_floats = size_t(N) * n * size_t(b);
+  pl.blocks1 = tiles * pl.splits;
+  pl.ksteps = int(ceil_div(n, 16));
+  pl.units = int64_t(N) * pl.ksteps * pl.qtiles * kWave;
+  pl.blocks2 = ceil_div(pl.tiles * N, 8) * 8 * pl.uqblocks;
+  pl.zp_bytes = ceil_div(sizeof(float) * size_t(pl.splits) * size_t(R) * size_t(b), 16) * 16;
+  pl.u_bytes = size_t(pl.units) * 3 * 16;
   return pl;
 }
 
-bool mfma_eligible(int64_t d, int b) { return b >= 16 && b % 4 == 0 && d % 4 == 0; }
+}  // namespace
 
-size_t mfma_workspace_bytes(int N, int n, int64_t d, int b) {
+// Two passes over X whatever b is, against one (fused) or two per point: from 4 or 2 points on,
+// but for small calls, where its third launch costs more than the passes saved (X of 111 x 1001
+// at 20 points 13 us against 19, of 256 x 4096 at 4 points 36 against 23).
+bool mfma_eligible(int N, int n, int64_t d, int b, bool fused) {
+  if (b < (fused ? 4 : 2) || d > int64_t(1) << 28) return false;
+  if (double(N) * double(n) * double(d) * double(b) < 3e6) return false;
   const MfmaPlan pl = mfma_plan(N, n, d, b);
-  return sizeof(float) * (pl.zp_floats + pl.u_floats);
+  return grid_ok(pl.blocks1, kZThreads) && grid_ok(pl.blocks2, kMThreads) && grid_ok(ceil_div(pl.units, 256), 256);
 }
 
-int launch_mfma_grads(const float *X, const float *y, const float *W, int N, int n, int64_t d, int b,
-                      int loss, float *G, void *workspace, hipStream_t st) {
+// 16 bytes more than the arrays take: they start at the next 16-byte boundary
+size_t mfma_workspace_bytes(int N, int n, int64_t d, int b) {
   const MfmaPlan pl = mfma_plan(N, n, d, b);
-  float *Zp = static_cast<float *>(workspace);
-  float *Uo = Zp + pl.zp_floats;
-  const int64_t blocks1 = int64_t(N) * pl.splits * pl.mtiles1 * pl.ntiles1;
-  const int mtiles2 = int(ceil_div(b, pl.tb));
-  const int64_t ntiles2 = ceil_div(d, kTN);
-  const int64_t blocks2 = int64_t(N) * ntiles2 * mtiles2;
-  const int64_t total = int64_t(N) * n * b;
-  if (!grid_ok(blocks1, kMThreads) || !grid_ok(blocks2, kMThreads) || !grid_ok(ceil_div(total, 256), 256))
-    return GC_EINVAL;
-  if (pl.tb == 128)
-    hipLaunchKernelGGL(zw_kernel<128>, dim3(unsigned(blocks1)), dim3(kMThreads), 0, st, X, W, N, n,
-                       d, b, pl.splits, pl.kper, pl.mtiles1, pl.ntiles1, Zp);
-  else
-    hipLaunchKernelGGL(zw_kernel<64>, dim3(unsigned(blocks1)), dim3(kMThreads), 0, st, X, W, N, n,
-                       d, b, pl.splits, pl.kper, pl.mtiles1, pl.ntiles1, Zp);
-  hipLaunchKernelGGL(resid_kernel, dim3(unsigned(ceil_div(total, 256))), dim3(256), 0, st, Zp, y,
-                     total, b, pl.splits, loss, Uo);
-  if (pl.tb == 128)
-    hipLaunchKernelGGL(utx_kernel<128>, dim3(unsigned(blocks2)), dim3(kMThreads), 0, st, Uo, X, N, n,
-                       d, b, mtiles2, ntiles2, G);
-  else
-    hipLaunchKernelGGL(utx_kernel<64>, dim3(unsigned(blocks2)), dim3(kMThreads), 0, st, Uo, X, N, n,
-                       d, b, mtiles2, ntiles2, G);
-  return GC_OK;
+  return pl.zp_bytes + pl.u_bytes + 16;
+}
+
+void launch_mfma_grads(const float *X, const float *y, const float *W, int N, int n, int64_t d, int b,
+                       int loss, float *G, void *workspace, hipStream_t st) {
+  const MfmaPlan pl = mfma_plan(N, n, d, b);
+  const int64_t R = int64_t(N) * n;
+  char *ws = reinterpret_cast<char *>((reinterpret_cast<uintptr_t>(workspace) + 15) & ~uintptr_t(15));
+  float *Zp = reinterpret_cast<float *>(ws);
+  uint4 *Uf = reinterpret_cast<uint4 *>(ws + pl.zp_bytes);
+#define GC_ZW(QT)                                                                                         \
+  hipLaunchKernelGGL(zw_kernel<QT>, dim3(unsigned(pl.blocks1)), dim3(kZThreads), 0, st, X, W, R, d, b,    \
+                     pl.splits, pl.kper, pl.zqblocks, Zp)
+  if (pl.zqt == 1) GC_ZW(1);
+  else if (pl.zqt == 2) GC_ZW(2);
+  else GC_ZW(4);
+#undef GC_ZW
+  hipLaunchKernelGGL(resid_kernel, dim3(unsigned(ceil_div(pl.units, 256))), dim3(256), 0, st, Zp, y, R, n, b,
+                     pl.splits, loss, pl.ksteps, pl.qtiles, pl.units, Uf);
+#define GC_UTX(QT, PW)                                                                                     \
+  hipLaunchKernelGGL((utx_kernel<QT, PW>), dim3(unsigned(pl.blocks2)), dim3(kMThreads), 0, st, Uf, X, N,   \
+                     n, d, b, pl.ksteps, pl.qtiles, pl.uqblocks, pl.tiles, G)
+  if (pl.uqt == 1) GC_UTX(1, 2);
+  else GC_UTX(2, 2);
+#undef GC_UTX
 }
 
 }  // namespace gcx

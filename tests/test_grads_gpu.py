@@ -1,0 +1,98 @@
+"""Chunk gradients where their paths change: column counts that no vector width divides, few and
+many rows and points, tile edges, unaligned rows, infinities and NaN.
+
+Reference: the same products in 64 bits.  Bar: relative 2-norm per chunk 1e-5, the repository's
+for G (measured errors are 0.5 to 2e-7)."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2405_19509_amd import gcx  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def problem(N, n, d, b, seed=0):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    X = torch.randn((N, n, d), generator=g, device="cuda") * d ** -0.5
+    y = (torch.rand((N, n), generator=g, device="cuda") < 0.5).float()
+    W = torch.randn((b, d), generator=g, device="cuda")
+    return X, y, W[0].contiguous() if b == 1 else W
+
+
+def reference(X, y, W, loss):
+    Wd = W.double().view(-1, X.shape[2])
+    G = torch.empty((Wd.shape[0], X.shape[0], X.shape[2]), dtype=torch.float64, device="cuda")
+    for i in range(X.shape[0]):
+        x = X[i].double()
+        z = x @ Wd.t()
+        r = (z if loss == gcx.GC_LOSS_LINEAR else torch.sigmoid(z)) - y[i].double()[:, None]
+        G[:, i] = r.t().contiguous() @ x
+    return G
+
+
+def check(G, ref):
+    G = G.double().view(ref.shape)
+    err = (G - ref).norm(dim=-1) / ref.norm(dim=-1).clamp_min(1e-30)
+    assert float(err.max()) <= 1e-5
+
+
+@pytest.mark.parametrize("N,n,d,b", [
+    # streaming: the last one to three columns, fewer than four, one and four rows per wave, split
+    # and whole rows per block, more rows than one stage of residuals
+    (1, 1, 1, 1), (2, 3, 3, 1), (3, 37, 1001, 1), (2, 9, 1023, 1), (5, 70, 16387, 1), (40, 20, 40002, 1),
+    (1, 2100, 1030, 1), (3, 50, 5003, 3),
+    # matrix cores: rows, columns and points just past and just short of their tiles of 32, 128,
+    # 64, 256, one and several splits of the columns, one to four point tiles per block
+    (4, 64, 4096, 4), (3, 33, 8191, 31), (2, 130, 16385, 33), (7, 17, 20001, 64), (1, 128, 32771, 65),
+    (5, 100, 2049, 97), (2, 31, 33000, 129), (30, 300, 70, 60), (60, 15, 33, 256), (1, 7, 200003, 5),
+])
+@pytest.mark.parametrize("loss", [gcx.GC_LOSS_LINEAR, gcx.GC_LOSS_LOGISTIC])
+def test_shapes(N, n, d, b, loss):
+    X, y, W = problem(N, n, d, b)
+    G = torch.full((N, d) if b == 1 else (b, N, d), float("nan"), device="cuda")
+    gcx.gc_chunk_grads(X, y, W, loss, G=G)
+    check(G, reference(X, y, W, loss))
+
+
+@pytest.mark.parametrize("N,n,d,b", [(3, 50, 40001, 1), (3, 50, 8190, 20)])
+def test_rows_on_any_float(N, n, d, b):
+    """Every array one float past a 16-byte boundary."""
+    X, y, W = problem(N, n, d, b)
+
+    def shifted(t):
+        s = torch.empty(t.numel() + 1, device="cuda")[1:].view(t.shape)
+        return s.copy_(t)
+
+    G = shifted(torch.full((N, d) if b == 1 else (b, N, d), float("nan"), device="cuda"))
+    need = gcx.gc_chunk_grads_workspace_size(N, n, d, b)
+    ws = torch.empty(need + 4, dtype=torch.uint8, device="cuda")[4:]
+    gcx.gc_chunk_grads(shifted(X), shifted(y), shifted(W), gcx.GC_LOSS_LOGISTIC, G=G, workspace=ws)
+    check(G, reference(X, y, W, gcx.GC_LOSS_LOGISTIC))
+
+
+@pytest.mark.parametrize("b", [1, 20, 64, 128])
+@pytest.mark.parametrize("kind", ["inf in X", "inf in W", "NaN in X", "NaN in W", "near the largest float"])
+def test_values_that_are_not_finite(kind, b):
+    """They reach the outputs that they reach in 64 bits, and no others."""
+    N, n, d = 3, 70, 5001
+    X, y, W = problem(N, n, d, b)
+    Wv = W.view(b, d)
+    if kind == "inf in X":
+        X[1, 40, 77] = float("inf")
+    elif kind == "inf in W":
+        Wv[b - 1, 5000] = -float("inf")
+    elif kind == "NaN in X":
+        X[2, 0, 5000] = float("nan")
+    elif kind == "NaN in W":
+        Wv[b // 2, 0] = float("nan")
+    else:
+        X[0, 69, 4096] = 3.4e38
+        Wv[:, 4096] = 2e-38
+    G = gcx.gc_chunk_grads(X, y, W, gcx.GC_LOSS_LOGISTIC).double().view(b, N, d)
+    ref = reference(X, y, W, gcx.GC_LOSS_LOGISTIC)
+    assert torch.equal(G.isnan(), ref.isnan())
+    assert torch.equal(G.isinf(), ref.isinf())
+    ok = ref.isfinite()
+    assert torch.allclose(G[ok].sign() * G[ok].abs().clamp_min(1e-3), ref[ok].sign() * ref[ok].abs().clamp_min(1e-3),
+                          rtol=2e-3, atol=2e-5)
