@@ -34,6 +34,19 @@ __device__ __forceinline__ void st_nt4(float *p, float a, float b, float c, floa
   __builtin_nontemporal_store(v4f_{a, b, c, d}, reinterpret_cast<v4f_ *>(p));
 }
 
+// ell neighbouring coefficients, from any float on
+template <int ELL>
+__device__ __forceinline__ void st_nt_row(float *p, const float (&v)[ELL]) {
+  typedef float v2f_ __attribute__((ext_vector_type(2), aligned(4)));
+  typedef float v4f_ __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+  for (int k = 0; k + 4 <= ELL; k += 4)
+    __builtin_nontemporal_store(v4f_{v[k], v[k + 1], v[k + 2], v[k + 3]}, reinterpret_cast<v4f_ *>(p + k));
+  constexpr int K4 = ELL / 4 * 4;
+  if constexpr (ELL % 4 >= 2) __builtin_nontemporal_store(v2f_{v[K4], v[K4 + 1]}, reinterpret_cast<v2f_ *>(p + K4));
+  if constexpr (ELL % 2 == 1) __builtin_nontemporal_store(v[ELL - 1], p + ELL - 1);
+}
+
 // One pattern by one wavefront, one lane per chunk: coverage, decodability, coefficient
 // error and the chunk's coefficients written straight to their (worker, position) slots.
 template <int ELL>
@@ -230,15 +243,16 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
 // Two-phase variant, used whenever the assignment tables fit in LDS.  A persistent block
 // stages the tables transposed ([gamma][N], so lane i's holder reads are consecutive
 // words) and each worker's load once; each wave then takes patterns in turn:
-//   phase 1, one lane per chunk: coverage, and the fp64 factor of the chunk's small
-//     system (ell = 1: sum_{S_i} R^2; Delta >= ell: Cholesky of X X^T; 0 < Delta < ell:
-//     Cholesky of the padded X^T X and the members), kept in the wave's LDS region;
+//   phase 1, one lane per chunk: coverage, and what the chunk's rows need (ell = 1: the
+//     reciprocal of sum_{S_i} R^2; Delta >= ell: the inverse K of the Cholesky factor of X X^T,
+//     fp64; 0 < Delta < ell: the members and their finished coefficients), kept in the wave's
+//     LDS region;
 //   phase 2, one lane per coefficient row (j, t) in Bc order: the chunk order[j][t], and
-//     the coefficients recomputed from the stored factor with the same operations as the
-//     one-phase kernel, written contiguously.
-// Both phases read psi from the wave's LDS copy.  Results equal decode_kernel's, except
-// that at ell = 1 the coefficient R_j / sum R^2 is formed as R_j * (1 / sum R^2) in fp64
-// before the fp32 rounding.
+//     K^T (K x_j), written contiguously.  There are delta times more rows than chunks, so the
+//     divisions stay in phase 1 (m = 200, delta = 20, ell = 2, 20,000 patterns, 640 MB of Bc:
+//     350 us with them in phase 2, 199 us without).
+// Both phases read psi from the wave's LDS copy.  Results equal decode_kernel's up to the fp64
+// rounding of reciprocals in place of divisions, before the one rounding to fp32.
 template <int ELL>
 struct DecodeLayout {
   static constexpr int NF = ELL * (ELL + 1) / 2;  // packed lower triangle
@@ -254,7 +268,7 @@ struct DecodeLayout {
     const int64_t ord = bc ? (int64_t(m) * delta + 1) / 2 : 0;
     return (r2_words(m, bc) + int64_t(gamma) * N + m + int64_t(ELL) * m + 1 + ord + 3) & ~int64_t(3);
   }
-  // F [N + 1][NF] doubles (row N: the sentinel chunk, zero), covS [N + 1], sel [N][ELL]
+  // F [NF][N + 1] doubles (entry N of each: the sentinel chunk), covS [N + 1], sel [N][ELL]
   // (ell > 1), psi [m + 1] (entry m: the sentinel worker)
   __host__ __device__ static int64_t wave_words(int N, int m, bool bc) {
     const int64_t f = bc ? 2 * int64_t(N + 1) * NF : 0;
@@ -269,7 +283,7 @@ constexpr int decode_tiled_max_waves() { return ELL <= 4 ? 16 : 4; }
 
 template <int ELL>
 __global__ __launch_bounds__(decode_tiled_max_waves<ELL>() * 64)
-__attribute__((amdgpu_waves_per_eu(ELL <= 2 ? 8 : 1))) void decode_tiled_kernel(
+__attribute__((amdgpu_waves_per_eu(ELL == 1 ? 8 : (ELL == 2 ? 6 : (ELL <= 4 ? 4 : 1))))) void decode_tiled_kernel(
     const int32_t *__restrict__ psi, int64_t P, int N, int m, const int32_t *__restrict__ order,
     int delta, const int32_t *__restrict__ holder, const int32_t *__restrict__ hpos, int gamma,
     const float *__restrict__ R, int32_t *__restrict__ cov, uint8_t *__restrict__ dec,
@@ -318,7 +332,8 @@ __attribute__((amdgpu_waves_per_eu(ELL <= 2 ? 8 : 1))) void decode_tiled_kernel(
   const int nw = blockDim.x / kWave;
   int32_t *region = sh + Lay::shared_words(N, m, gamma, delta, want_bc) +
                     int64_t(wave) * Lay::wave_words(N, m, want_bc);
-  double *F = reinterpret_cast<double *>(region);                      // [N + 1][NF]
+  double *F = reinterpret_cast<double *>(region);                      // [NF][N + 1]
+  float *Fs = reinterpret_cast<float *>(F);
   int32_t *covS = region + (want_bc ? 2 * int64_t(N + 1) * NF : 0);    // [N + 1]
   int32_t *sel = covS + N + 1;                                          // [N][ELL] (ELL > 1)
   int32_t *pss = sel + ((want_bc && ELL > 1) ? int64_t(N) * ELL : 0);  // [m]
@@ -329,7 +344,7 @@ __attribute__((amdgpu_waves_per_eu(ELL <= 2 ? 8 : 1))) void decode_tiled_kernel(
   if (want_bc && lane == 0) {  // the sentinel chunk: no coverage, zero coefficients
     covS[N] = 0;
 #pragma unroll
-    for (int a = 0; a < NF; ++a) F[int64_t(N) * NF + a] = 0.0;
+    for (int a = 0; a < NF; ++a) F[a * (N + 1) + N] = 0.0;
   }
 
   for (int64_t p = int64_t(blockIdx.x) * nw + wave; p < P; p += int64_t(gridDim.x) * nw) {
@@ -349,19 +364,36 @@ __attribute__((amdgpu_waves_per_eu(ELL <= 2 ? 8 : 1))) void decode_tiled_kernel(
     int err = 0;
     bool all_ok = true;
     for (int i = lane; i < N; i += kWave) {
+      // branch-free, every load unconditional (the sentinel worker m has psi -1 and weight 0),
+      // so the unrolled holders' LDS reads overlap
       int Delta = 0;
       double ss = 0.0;  // ell = 1: sum of R_j^2 over the members, in holder order
-      if (ELL == 1 && want_bc) {
-        // branch-free, every load unconditional (the sentinel worker m has psi -1 and
-        // weight 0), so the unrolled holders' LDS reads overlap
+      double M[ELL][ELL];  // ell > 1: X X^T, lower triangle
+#pragma unroll
+      for (int a = 0; a < ELL; ++a)
+#pragma unroll
+        for (int b = 0; b < ELL; ++b) M[a][b] = 0.0;
+      if (want_bc) {
 #pragma unroll 4
         for (int u = 0; u < gamma; ++u) {
           const int jt = hjt[u * N + i], j = jt & 0xffff, t = jt >> 16;
-          const int pv = pss[j];
-          const double x2 = R2s[j];
-          const bool member = pv > t;
+          const bool member = pss[j] > t;
           Delta += member ? 1 : 0;
-          ss += member ? x2 : 0.0;
+          if constexpr (ELL == 1) {
+            const double x2 = R2s[j];
+            ss += member ? x2 : 0.0;
+          } else {
+            double x[ELL];
+#pragma unroll
+            for (int k = 0; k < ELL; ++k) {
+              const float r = Rs[k * m + j];
+              x[k] = member ? r : 0.f;
+            }
+#pragma unroll
+            for (int a = 0; a < ELL; ++a)
+#pragma unroll
+              for (int b = 0; b <= a; ++b) M[a][b] += x[a] * x[b];
+          }
         }
       } else {
 #pragma unroll 4
@@ -373,40 +405,35 @@ __attribute__((amdgpu_waves_per_eu(ELL <= 2 ? 8 : 1))) void decode_tiled_kernel(
       if (cov != nullptr) cov[p * N + i] = Delta;
       err += Delta < ELL ? ELL - Delta : 0;
       all_ok = all_ok && Delta >= ELL;
-      covS[i] = Delta;
+      covS[i] = invalid ? 0 : Delta;  // an invalid pattern's coefficients are zero
       if (!want_bc) continue;
-      double *Fi = F + int64_t(i) * NF;
       if constexpr (ELL == 1) {
         // phase 2 multiplies by the reciprocal (one rounding more than a division); zero
         // when nothing is covered or the pattern is invalid, so phase 2 writes zeros
-        Fi[0] = (invalid || Delta == 0) ? 0.0 : 1.0 / ss;
+        F[i] = (invalid || Delta == 0) ? 0.0 : 1.0 / ss;
         continue;
       }
       if (invalid || Delta == 0) continue;
       if constexpr (ELL == 1) {
       } else if (Delta >= ELL) {
-        double M[ELL][ELL];
+        cholesky<ELL>(M);
+        // K = L^-1, row by row: K[a][b] = -(sum_{b <= q < a} L[a][q] K[q][b]) / L[a][a]
+        double K[ELL][ELL];
 #pragma unroll
-        for (int a = 0; a < ELL; ++a)
+        for (int a = 0; a < ELL; ++a) {
+          K[a][a] = 1.0 / M[a][a];
 #pragma unroll
-          for (int b = 0; b < ELL; ++b) M[a][b] = 0.0;
-        for (int u = 0; u < gamma; ++u) {
-          const int jt = hjt[u * N + i], j = jt & 0xffff, t = jt >> 16;
-          if (pss[j] > t) {
-            double x[ELL];
+          for (int b = 0; b < a; ++b) {
+            double v = 0.0;
 #pragma unroll
-            for (int k = 0; k < ELL; ++k) x[k] = Rs[k * m + j];
-#pragma unroll
-            for (int a = 0; a < ELL; ++a)
-#pragma unroll
-              for (int b = 0; b <= a; ++b) M[a][b] += x[a] * x[b];
+            for (int q = b; q < a; ++q) v -= M[a][q] * K[q][b];
+            K[a][b] = v * K[a][a];
           }
         }
-        cholesky<ELL>(M);
 #pragma unroll
         for (int a = 0; a < ELL; ++a)
 #pragma unroll
-          for (int b = 0; b <= a; ++b) Fi[a * (a + 1) / 2 + b] = M[a][b];
+          for (int b = 0; b <= a; ++b) F[(a * (a + 1) / 2 + b) * (N + 1) + i] = K[a][b];
       } else {
         int selj[ELL];
 #pragma unroll
@@ -439,11 +466,23 @@ __attribute__((amdgpu_waves_per_eu(ELL <= 2 ? 8 : 1))) void decode_tiled_kernel(
             H[a][b] = (a < Delta) ? v : (a == b ? 1.0 : 0.0);
           }
         cholesky<ELL>(H);
+        // the members' coefficients in fp32: at most (ell - 1) ell of them, two to a double of F
 #pragma unroll
-        for (int a = 0; a < ELL; ++a) {
+        for (int a = 0; a < ELL - 1; ++a) {
           sel[int64_t(i) * ELL + a] = selj[a];
+          if (a >= Delta) continue;
+          double z[ELL];  // column a of H^-1 (= row a, H symmetric)
 #pragma unroll
-          for (int b = 0; b <= a; ++b) Fi[a * (a + 1) / 2 + b] = H[a][b];
+          for (int b = 0; b < ELL; ++b) z[b] = (a == b) ? 1.0 : 0.0;
+          chol_solve<ELL>(H, z);
+#pragma unroll
+          for (int k = 0; k < ELL; ++k) {
+            double v = 0.0;
+#pragma unroll
+            for (int b = 0; b < ELL; ++b) v += z[b] * X[k][b];
+            const int f = a * ELL + k;
+            Fs[2 * ((f / 2) * (N + 1) + i) + f % 2] = float(v);
+          }
         }
       }
     }
@@ -526,67 +565,47 @@ __attribute__((amdgpu_waves_per_eu(ELL <= 2 ? 8 : 1))) void decode_tiled_kernel(
       }
     } else {
       int j = j_first, t = t_first;
-  #pragma unroll 4
+      constexpr int kRows = ELL <= 2 ? 4 : 1;  // rows in flight per lane
+#pragma unroll kRows
       for (int e = lane; e < nrow; e += kWave) {
         const int c = ordS[e];
+        const bool done = pss[j] > t;
         float out[ELL];
-  #pragma unroll
-        for (int k = 0; k < ELL; ++k) out[k] = 0.f;
-        const bool valid = c < N && pss[j] > t;
         if constexpr (ELL == 1) {
-          if (valid && F[c] != 0.0) out[0] = float(double(Rs[j]) * F[c]);  // +0 otherwise
-        }
-        const int Delta = (ELL > 1 && valid) ? covS[c] : 0;
-        if (ELL > 1 && !invalid && Delta > 0) {
-          const double *Fc = F + int64_t(c) * NF;
-          if constexpr (ELL == 1) {
-          } else if (Delta >= ELL) {
-            double Lf[ELL][ELL];
-  #pragma unroll
-            for (int a = 0; a < ELL; ++a)
-  #pragma unroll
-              for (int b = 0; b < ELL; ++b) Lf[a][b] = b <= a ? Fc[a * (a + 1) / 2 + b] : 0.0;
-            double cc[ELL];
-  #pragma unroll
-            for (int k = 0; k < ELL; ++k) cc[k] = Rs[k * m + j];
-            chol_solve<ELL>(Lf, cc);
-  #pragma unroll
-            for (int k = 0; k < ELL; ++k) out[k] = float(cc[k]);
-          } else {
-            double Lf[ELL][ELL];
-  #pragma unroll
-            for (int a = 0; a < ELL; ++a)
-  #pragma unroll
-              for (int b = 0; b < ELL; ++b) Lf[a][b] = b <= a ? Fc[a * (a + 1) / 2 + b] : 0.0;
-            int selj[ELL];
+          const double f = F[c];
+          const float v = float(double(Rs[j]) * f);
+          out[0] = done && f != 0.0 ? v : 0.f;  // +0 otherwise
+        } else {
+          const int Delta = covS[c];
+          double x[ELL], z[ELL];
+#pragma unroll
+          for (int k = 0; k < ELL; ++k) x[k] = Rs[k * m + j];
+#pragma unroll
+          for (int a = 0; a < ELL; ++a) {
+            z[a] = 0.0;
+#pragma unroll
+            for (int b = 0; b <= a; ++b) z[a] += F[(a * (a + 1) / 2 + b) * (N + 1) + c] * x[b];
+          }
+#pragma unroll
+          for (int b = 0; b < ELL; ++b) {
+            double v = 0.0;
+#pragma unroll
+            for (int a = b; a < ELL; ++a) v += F[(a * (a + 1) / 2 + b) * (N + 1) + c] * z[a];
+            out[b] = done && Delta >= ELL ? float(v) : 0.f;
+          }
+          if (done && Delta > 0 && Delta < ELL) {
             int me = 0;  // j's place among the members
-  #pragma unroll
-            for (int a = 0; a < ELL; ++a) {
-              selj[a] = sel[int64_t(c) * ELL + a];
-              if (a < Delta && selj[a] == j) me = a;
-            }
-            double X[ELL][ELL];
-  #pragma unroll
-            for (int a = 0; a < ELL; ++a) {
-              const int ja = a < Delta ? selj[a] : 0;
-  #pragma unroll
-              for (int k = 0; k < ELL; ++k) X[k][a] = a < Delta ? double(Rs[k * m + ja]) : 0.0;
-            }
-            double z[ELL];
-  #pragma unroll
-            for (int b = 0; b < ELL; ++b) z[b] = (me == b) ? 1.0 : 0.0;
-            chol_solve<ELL>(Lf, z);
-  #pragma unroll
+#pragma unroll
+            for (int a = 0; a < ELL - 1; ++a)
+              if (a < Delta && sel[int64_t(c) * ELL + a] == j) me = a;
+#pragma unroll
             for (int k = 0; k < ELL; ++k) {
-              double v = 0.0;
-  #pragma unroll
-              for (int b = 0; b < ELL; ++b) v += z[b] * X[k][b];
-              out[k] = float(v);
+              const int f = me * ELL + k;
+              out[k] = Fs[2 * ((f / 2) * (N + 1) + c) + f % 2];
             }
           }
         }
-  #pragma unroll
-        for (int k = 0; k < ELL; ++k) st_nt(Bp + int64_t(e) * ELL + k, out[k]);
+        st_nt_row<ELL>(Bp + int64_t(e) * ELL, out);
         j += j_step;
         t += t_step;
         if (t >= delta) {
