@@ -281,16 +281,16 @@ struct DecodeLayout {
 template <int ELL>
 constexpr int decode_tiled_max_waves() { return ELL <= 4 ? 16 : 4; }
 
-template <int ELL>
-__global__ __launch_bounds__(decode_tiled_max_waves<ELL>() * 64)
-__attribute__((amdgpu_waves_per_eu(ELL == 1 ? 8 : (ELL == 2 ? 6 : (ELL <= 4 ? 4 : 1))))) void decode_tiled_kernel(
+// Body of the kernels below.  BLOCK: all waves of a block take one pattern together, in one LDS
+// region, instead of a pattern each.
+template <int ELL, bool BLOCK>
+__device__ __forceinline__ void decode_tiled(
     const int32_t *__restrict__ psi, int64_t P, int N, int m, const int32_t *__restrict__ order,
     int delta, const int32_t *__restrict__ holder, const int32_t *__restrict__ hpos, int gamma,
     const float *__restrict__ R, int32_t *__restrict__ cov, uint8_t *__restrict__ dec,
-    int32_t *__restrict__ coef_err, float *__restrict__ Bc) {
+    int32_t *__restrict__ coef_err, float *__restrict__ Bc, int32_t *sh) {
   using Lay = DecodeLayout<ELL>;
   constexpr int NF = Lay::NF;
-  extern __shared__ __align__(16) int32_t sh[];
   const bool want_bc = Bc != nullptr;
   double *R2s = reinterpret_cast<double *>(sh);  // [m + 1] (ell = 1 with Bc)
   int32_t *hjt = sh + Lay::r2_words(m, want_bc);  // [gamma][N]: j | t << 16
@@ -326,10 +326,24 @@ __attribute__((amdgpu_waves_per_eu(ELL == 1 ? 8 : (ELL == 2 ? 6 : (ELL <= 4 ? 4 
       ordS[e] = int16_t((c >= 0 && c < N) ? c : N);
     }
   }
-  __syncthreads();  // the only block barrier; every thread reaches it
+  __shared__ int errS;  // BLOCK: the pattern's coefficient error
+  if (BLOCK && threadIdx.x == 0) errS = 0;
+  __syncthreads();
 
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  const int nw = blockDim.x / kWave;
+  // the threads that share a pattern, and this one's place among them
+  const int step = BLOCK ? int(blockDim.x) : kWave;
+  const int lane = BLOCK ? int(threadIdx.x) : int(threadIdx.x % kWave);
+  const int wave = BLOCK ? 0 : int(threadIdx.x / kWave);
+  const int nw = BLOCK ? 1 : int(blockDim.x / kWave);
+  auto sync = [] {
+    if constexpr (BLOCK) {
+      __syncthreads();
+    } else {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+  };
   int32_t *region = sh + Lay::shared_words(N, m, gamma, delta, want_bc) +
                     int64_t(wave) * Lay::wave_words(N, m, want_bc);
   double *F = reinterpret_cast<double *>(region);                      // [NF][N + 1]
@@ -338,9 +352,9 @@ __attribute__((amdgpu_waves_per_eu(ELL == 1 ? 8 : (ELL == 2 ? 6 : (ELL <= 4 ? 4 
   int32_t *sel = covS + N + 1;                                          // [N][ELL] (ELL > 1)
   int32_t *pss = sel + ((want_bc && ELL > 1) ? int64_t(N) * ELL : 0);  // [m]
   const int64_t wstride = int64_t(delta) * ELL;
-  // phase 2 walks e = lane, lane + 64, ... as (worker, position) = (e / delta, e % delta)
+  // phase 2 walks e = lane, lane + step, ... as (worker, position) = (e / delta, e % delta)
   const int j_first = lane / delta, t_first = lane % delta;
-  const int j_step = kWave / delta, t_step = kWave % delta;
+  const int j_step = step / delta, t_step = step % delta;
   if (want_bc && lane == 0) {  // the sentinel chunk: no coverage, zero coefficients
     covS[N] = 0;
 #pragma unroll
@@ -349,21 +363,23 @@ __attribute__((amdgpu_waves_per_eu(ELL == 1 ? 8 : (ELL == 2 ? 6 : (ELL <= 4 ? 4 
 
   for (int64_t p = int64_t(blockIdx.x) * nw + wave; p < P; p += int64_t(gridDim.x) * nw) {
     bool bad = false;
-    for (int j = lane; j < m; j += kWave) {
+    for (int j = lane; j < m; j += step) {
       const int v = psi[p * m + j];
       pss[j] = v;
       bad = bad || v < 0 || v > loads[j];
     }
     if (lane == 0) pss[m] = -1;
-    const bool invalid = __any(bad);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    bool invalid;
+    if constexpr (BLOCK) {
+      invalid = __syncthreads_or(bad ? 1 : 0) != 0;
+    } else {
+      invalid = __any(bad);
+      sync();
+    }
 
     // ---- phase 1: one lane per chunk
     int err = 0;
-    bool all_ok = true;
-    for (int i = lane; i < N; i += kWave) {
+    for (int i = lane; i < N; i += step) {
       // branch-free, every load unconditional (the sentinel worker m has psi -1 and weight 0),
       // so the unrolled holders' LDS reads overlap
       int Delta = 0;
@@ -404,7 +420,6 @@ __attribute__((amdgpu_waves_per_eu(ELL == 1 ? 8 : (ELL == 2 ? 6 : (ELL <= 4 ? 4 
       }
       if (cov != nullptr) cov[p * N + i] = Delta;
       err += Delta < ELL ? ELL - Delta : 0;
-      all_ok = all_ok && Delta >= ELL;
       covS[i] = invalid ? 0 : Delta;  // an invalid pattern's coefficients are zero
       if (!want_bc) continue;
       if constexpr (ELL == 1) {
@@ -487,15 +502,20 @@ __attribute__((amdgpu_waves_per_eu(ELL == 1 ? 8 : (ELL == 2 ? 6 : (ELL <= 4 ? 4 
       }
     }
     err = wave_sum(err);
-    const bool ok = __all(all_ok);
-    if (lane == 0) {
-      dec[p] = invalid ? GC_DEC_INVALID : (ok ? GC_DEC_YES : GC_DEC_NO);
+    if constexpr (BLOCK) {
+      if (threadIdx.x % kWave == 0 && err > 0) atomicAdd(&errS, err);
+      sync();
+      if (lane == 0) {
+        err = errS;
+        errS = 0;  // added to again after the barrier at the pattern's end only
+      }
+    }
+    if (lane == 0) {  // decodable: every chunk is covered ell times, so nothing is missing
+      dec[p] = invalid ? GC_DEC_INVALID : (err == 0 ? GC_DEC_YES : GC_DEC_NO);
       coef_err[p] = err;
     }
-    if (!want_bc) continue;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (!BLOCK && !want_bc) continue;
+    if constexpr (!BLOCK) sync();
 
     // ---- phase 2: one lane per coefficient row (j, t), Bc order
     float *Bp = Bc + p * int64_t(m) * wstride;
@@ -503,8 +523,8 @@ __attribute__((amdgpu_waves_per_eu(ELL == 1 ? 8 : (ELL == 2 ? 6 : (ELL <= 4 ? 4 
     if (ELL == 1 && delta >= 4 && (nrow & 3) == 0 && (reinterpret_cast<uintptr_t>(Bp) & 15) == 0) {
       // four consecutive rows per lane, one 16-byte store
       int j4 = (4 * lane) / delta, t4 = (4 * lane) % delta;
-      const int j4_step = (4 * kWave) / delta, t4_step = (4 * kWave) % delta;
-      for (int e0 = 4 * lane; (delta & 3) == 0 && e0 < nrow; e0 += 4 * kWave) {
+      const int j4_step = (4 * step) / delta, t4_step = (4 * step) % delta;
+      for (int e0 = 4 * lane; (delta & 3) == 0 && e0 < nrow; e0 += 4 * step) {
         // delta a multiple of 4: the four rows are positions t4 .. t4 + 3 of one worker
         double f[4];  // zero for the sentinel chunk, Delta = 0, invalid
 #pragma unroll
@@ -525,7 +545,7 @@ __attribute__((amdgpu_waves_per_eu(ELL == 1 ? 8 : (ELL == 2 ? 6 : (ELL <= 4 ? 4 
           ++j4;
         }
       }
-      for (int e0 = 4 * lane; (delta & 3) != 0 && e0 < nrow; e0 += 4 * kWave) {
+      for (int e0 = 4 * lane; (delta & 3) != 0 && e0 < nrow; e0 += 4 * step) {
         // the four rows' (worker, position), then every LDS read, then the selects: no
         // branches, so the reads of the four rows overlap
         int jq[4], tq[4], cq[4];
@@ -567,7 +587,7 @@ __attribute__((amdgpu_waves_per_eu(ELL == 1 ? 8 : (ELL == 2 ? 6 : (ELL <= 4 ? 4 
       int j = j_first, t = t_first;
       constexpr int kRows = ELL <= 2 ? 4 : 1;  // rows in flight per lane
 #pragma unroll kRows
-      for (int e = lane; e < nrow; e += kWave) {
+      for (int e = lane; e < nrow; e += step) {
         const int c = ordS[e];
         const bool done = pss[j] > t;
         float out[ELL];
@@ -614,11 +634,32 @@ __attribute__((amdgpu_waves_per_eu(ELL == 1 ? 8 : (ELL == 2 ? 6 : (ELL <= 4 ? 4 
         }
       }
     }
-    // the next pattern overwrites this wave's region only after every lane is done with it
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    sync();  // the next pattern overwrites the region only after every lane is done with it
   }
+}
+
+template <int ELL>
+__global__ __launch_bounds__(decode_tiled_max_waves<ELL>() * 64)
+__attribute__((amdgpu_waves_per_eu(ELL == 1 ? 8 : (ELL == 2 ? 6 : (ELL <= 4 ? 4 : 1))))) void decode_tiled_kernel(
+    const int32_t *__restrict__ psi, int64_t P, int N, int m, const int32_t *__restrict__ order,
+    int delta, const int32_t *__restrict__ holder, const int32_t *__restrict__ hpos, int gamma,
+    const float *__restrict__ R, int32_t *__restrict__ cov, uint8_t *__restrict__ dec,
+    int32_t *__restrict__ coef_err, float *__restrict__ Bc) {
+  extern __shared__ __align__(16) int32_t sh[];
+  decode_tiled<ELL, false>(psi, P, N, m, order, delta, holder, hpos, gamma, R, cov, dec, coef_err, Bc, sh);
+}
+
+// Up to eight waves per pattern: for few patterns, and where a region per wave leaves few waves
+// per CU (the factors of ell = 8 take 288 bytes per chunk).  With coefficients only.
+constexpr int kDecodeBlockWaves = 8;
+template <int ELL>
+__global__ __launch_bounds__(kDecodeBlockWaves * 64) void decode_block_kernel(
+    const int32_t *__restrict__ psi, int64_t P, int N, int m, const int32_t *__restrict__ order,
+    int delta, const int32_t *__restrict__ holder, const int32_t *__restrict__ hpos, int gamma,
+    const float *__restrict__ R, int32_t *__restrict__ cov, uint8_t *__restrict__ dec,
+    int32_t *__restrict__ coef_err, float *__restrict__ Bc) {
+  extern __shared__ __align__(16) int32_t sh[];
+  decode_tiled<ELL, true>(psi, P, N, m, order, delta, holder, hpos, gamma, R, cov, dec, coef_err, Bc, sh);
 }
 
 // ell = 1 with coefficients, N = m and gamma = delta: the cyclic assignment is checked
@@ -631,7 +672,9 @@ __attribute__((amdgpu_waves_per_eu(ELL == 1 ? 8 : (ELL == 2 ? 6 : (ELL <= 4 ? 4 
 // The arithmetic is the tiled kernel's (sum of R^2 over the holders in fp64, the
 // reciprocal, R_j times it in fp64, one rounding to fp32), with the holders summed in
 // ascending cyclic order (the tables' ascending worker order except for the chunks whose
-// holders wrap past worker N - 1).  Other tables: the one-phase path, per wave.
+// holders wrap past worker N - 1).  Other tables: the two-phase path above where its LDS fits as
+// well (200 workers of 20 chunks, regular, 20,000 patterns: 2020 us on the one-phase path,
+// 109 us), else the one-phase path.
 //   LDS: R2x [m + delta] fp64, Rs [m] (+ pad); per wave F [N + delta] fp64, psi [m + delta].
 constexpr int kCycMaxWaves = 16;
 
@@ -750,7 +793,7 @@ decode_cyclic_l1_kernel(const int32_t *__restrict__ psi, int64_t P, int N, int m
                         const int32_t *__restrict__ order, int delta, const int32_t *__restrict__ holder,
                         const int32_t *__restrict__ hpos, int gamma, const float *__restrict__ R,
                         int32_t *__restrict__ cov, uint8_t *__restrict__ dec, int32_t *__restrict__ coef_err,
-                        float *__restrict__ Bc) {
+                        float *__restrict__ Bc, bool two_phase) {
   extern __shared__ __align__(16) unsigned char lds_c[];
   double *R2x = reinterpret_cast<double *>(lds_c);       // [m + delta]
   float *Rs = reinterpret_cast<float *>(R2x + m + delta);  // [m]
@@ -774,7 +817,12 @@ decode_cyclic_l1_kernel(const int32_t *__restrict__ psi, int64_t P, int N, int m
     R2x[k] = x * x;
   }
   for (int j = threadIdx.x; j < m; j += blockDim.x) Rs[j] = R[j];
-  const bool all_cyc = __syncthreads_and(cyc ? 1 : 0) != 0;  // the only block barrier
+  const bool all_cyc = __syncthreads_and(cyc ? 1 : 0) != 0;
+  if (!all_cyc && two_phase) {  // the whole block; nobody reads the arrays above after the barrier
+    decode_tiled<1, false>(psi, P, N, m, order, delta, holder, hpos, gamma, R, cov, dec, coef_err, Bc,
+                           reinterpret_cast<int32_t *>(lds_c));
+    return;
+  }
 
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int nw = blockDim.x / kWave;
@@ -791,6 +839,22 @@ decode_cyclic_l1_kernel(const int32_t *__restrict__ psi, int64_t P, int N, int m
 
 constexpr size_t kDecodeLdsCU = 160 * 1024;  // LDS of one CU
 
+// Waves per block (a power of two up to most) with the most waves per CU (at most 32) that LDS of
+// shared bytes per block and per_wave per wave allows; total 0 if not even one fits.
+struct DecodeFit {
+  int waves, total;
+};
+inline DecodeFit decode_fit(size_t shared, size_t per_wave, int most) {
+  DecodeFit f{0, 0};
+  for (int w = most; w >= 1; w >>= 1) {
+    const size_t lds = shared + w * per_wave;
+    if (lds > kDecodeLdsCU) continue;
+    const int per_cu = int(std::min<size_t>(kDecodeLdsCU / lds, 32 / w));
+    if (per_cu * w > f.total) f = DecodeFit{w, per_cu * w};
+  }
+  return f;
+}
+
 // the cyclic ell = 1 kernel when its LDS leaves at least 8 waves per CU; false otherwise
 bool launch_decode_cyclic_l1(const int32_t *psi, int64_t P, int N, int m, const int32_t *order, int delta,
                              const int32_t *holder, const int32_t *hpos, int gamma, const float *R,
@@ -798,25 +862,24 @@ bool launch_decode_cyclic_l1(const int32_t *psi, int64_t P, int N, int m, const 
                              bool *launched) {
   *launched = false;
   const size_t shared = size_t(cyc_shared_bytes(m, delta)), per_wave = size_t(cyc_wave_bytes(N, m, delta));
-  int best_w = 0, best_total = 0;
-  for (int w = kCycMaxWaves; w >= 1; w >>= 1) {
-    const size_t lds = shared + w * per_wave;
-    if (lds > kDecodeLdsCU) continue;
-    const int per_cu = int(std::min<size_t>(kDecodeLdsCU / lds, 32 / w));
-    if (per_cu * w > best_total) {
-      best_total = per_cu * w;
-      best_w = w;
-    }
-  }
-  if (best_total < 8) return true;
-  const size_t lds = shared + best_w * per_wave;
+  const auto cyclic = decode_fit(shared, per_wave, kCycMaxWaves);
+  if (cyclic.total < 8) return true;
+  // room for the two-phase path's tables too, where they leave half of the cyclic path's waves
+  using Lay = DecodeLayout<1>;
+  const size_t shared2 = 4 * size_t(Lay::shared_words(N, m, gamma, delta, true));
+  const size_t per_wave2 = 4 * size_t(Lay::wave_words(N, m, true));
+  const auto both = decode_fit(std::max(shared, shared2), std::max(per_wave, per_wave2), kCycMaxWaves);
+  const bool two_phase = N < 32768 && 2 * both.total >= cyclic.total;
+  const int best_w = two_phase ? both.waves : cyclic.waves, best_total = two_phase ? both.total : cyclic.total;
+  const size_t lds = two_phase ? std::max(shared, shared2) + best_w * std::max(per_wave, per_wave2)
+                               : shared + best_w * per_wave;
   const int64_t blocks = std::min(ceil_div(P, best_w), int64_t(best_total / best_w) * cu_count());
   if (lds > 64 * 1024 &&
       hipFuncSetAttribute(reinterpret_cast<const void *>(&decode_cyclic_l1_kernel),
                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
     return false;
   hipLaunchKernelGGL(decode_cyclic_l1_kernel, dim3(unsigned(blocks)), dim3(best_w * kWave), lds, st, psi, P,
-                     N, m, order, delta, holder, hpos, gamma, R, cov, dec, coef_err, Bc);
+                     N, m, order, delta, holder, hpos, gamma, R, cov, dec, coef_err, Bc, two_phase);
   *launched = true;
   return true;
 }
@@ -827,6 +890,31 @@ bool launch_decode(const int32_t *psi, int64_t P, int N, int m, const int32_t *o
                    int32_t *cov, uint8_t *dec, int32_t *coef_err, float *Bc, hipStream_t st) {
   using Lay = DecodeLayout<ELL>;
   const bool bc = Bc != nullptr;
+  const size_t shared = 4 * size_t(Lay::shared_words(N, m, gamma, delta, bc));
+  const size_t per_wave = 4 * size_t(Lay::wave_words(N, m, bc));
+  const DecodeFit fit = decode_fit(shared, per_wave, decode_tiled_max_waves<ELL>());
+  // A block per pattern where the patterns are so few that every one has its own eight waves at
+  // once, and where the region per wave leaves fewer than 8 waves per CU, with a wave per 64
+  // chunks.  m = 200, delta = 20, ell = 2: 64 patterns 68 -> 14 us, but 4000 patterns 45 -> 70 us, so
+  // those keep a wave per pattern; ell = 4, 10,000 patterns 1883 -> 287 us, ell = 8, 2000 patterns
+  // 536 -> 275 us (both from the one-phase kernel).
+  const size_t block_lds = shared + per_wave, block_all = block_lds + 64;  // and its static LDS
+  constexpr int reg_waves = ELL <= 2 ? 32 : (ELL <= 5 ? 16 : 8);  // per CU, as registers allow
+  int bw = kDecodeBlockWaves;
+  if (P > cu_count())
+    while (bw > 1 && 32 * bw >= N) bw /= 2;
+  const int64_t block_cu = block_all > kDecodeLdsCU ? 0 : std::min<int64_t>(kDecodeLdsCU / block_all, reg_waves / bw);
+  // the two-phase kernels' order table holds chunk indices as int16
+  if (bc && N < 32768 && block_cu > 0 && (fit.total < 8 || P <= cu_count())) {
+    if (block_lds > 64 * 1024 &&
+        hipFuncSetAttribute(reinterpret_cast<const void *>(&decode_block_kernel<ELL>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, int(block_lds)) != hipSuccess)
+      return false;
+    hipLaunchKernelGGL(decode_block_kernel<ELL>, dim3(unsigned(std::min(P, block_cu * cu_count()))),
+                       dim3(bw * kWave), block_lds, st, psi, P, N, m, order, delta, holder, hpos,
+                       gamma, R, cov, dec, coef_err, Bc);
+    return true;
+  }
   if (ELL == 1 && bc && N == m && gamma == delta) {
     bool launched = false;
     if (!launch_decode_cyclic_l1(psi, P, N, m, order, delta, holder, hpos, gamma, R, cov, dec, coef_err, Bc,
@@ -834,31 +922,15 @@ bool launch_decode(const int32_t *psi, int64_t P, int N, int m, const int32_t *o
       return false;
     if (launched) return true;
   }
-  const size_t shared = 4 * size_t(Lay::shared_words(N, m, gamma, delta, bc));
-  const size_t per_wave = 4 * size_t(Lay::wave_words(N, m, bc));
-  // the most waves per CU the LDS allows (at most 32), in blocks of up to 16 waves
-  int best_w = 0, best_total = 0;
-  for (int w = decode_tiled_max_waves<ELL>(); w >= 1; w >>= 1) {
-    const size_t lds = shared + w * per_wave;
-    if (lds > kDecodeLdsCU) continue;
-    const int per_cu = int(std::min<size_t>(kDecodeLdsCU / lds, 32 / w));
-    if (per_cu * w > best_total) {
-      best_total = per_cu * w;
-      best_w = w;
-    }
-  }
-  // else the one-phase kernel, which needs no LDS per wave (the two-phase kernel's order
-  // table holds chunk indices as int16)
-  if (best_total >= 8 && N < 32768) {
-    const size_t lds = shared + best_w * per_wave;
-    const int64_t want = ceil_div(P, best_w);
-    const int64_t resident = int64_t(best_total / best_w) * cu_count();
-    const int64_t blocks = std::min(want, resident);
+  // else the one-phase kernel, which needs no LDS per wave
+  if (fit.total >= 8 && N < 32768) {
+    const size_t lds = shared + fit.waves * per_wave;
+    const int64_t blocks = std::min(ceil_div(P, fit.waves), int64_t(fit.total / fit.waves) * cu_count());
     if (lds > 64 * 1024 &&
         hipFuncSetAttribute(reinterpret_cast<const void *>(&decode_tiled_kernel<ELL>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
       return false;
-    hipLaunchKernelGGL(decode_tiled_kernel<ELL>, dim3(unsigned(blocks)), dim3(best_w * kWave), lds,
+    hipLaunchKernelGGL(decode_tiled_kernel<ELL>, dim3(unsigned(blocks)), dim3(fit.waves * kWave), lds,
                        st, psi, P, N, m, order, delta, holder, hpos, gamma, R, cov, dec, coef_err, Bc);
     return true;
   }
