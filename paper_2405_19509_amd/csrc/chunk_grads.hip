@@ -20,10 +20,11 @@
 //
 // General path (any d, any alignment): two streaming kernels
 //   dot_kernel   x.w of 4 rows (few rows: 1) over a segment of the columns by one wave, 16-byte
-//                loads from any float on, w loaded once for the rows -> workspace [b][N][n][segments]
+//                loads from any float on, w loaded once for the rows; several segments' sums
+//                go to G and seg_residual_kernel adds them -> workspace residuals [b][N][n]
 //   xtr_kernel   one block per (point, chunk, 1024 or 256 columns): the chunk's residuals
-//                from the segments' sums in LDS, then the columns down all n rows, 8 loads
-//                in flight; fixed summation order -> deterministic.
+//                in LDS, then the columns down all n rows, 8 loads in flight; fixed summation
+//                order -> deterministic.
 // Both read X at the rate of the memory (X of 20 x 100 x 250001, 2 GB: 0.36 ms each, 5.5
 // TB/s; scalar loads and one wave per row took 2.1 ms in all).
 #include <algorithm>
@@ -34,7 +35,6 @@ namespace gcx {
 
 // multi-point path on the matrix cores (chunk_grads_mfma.hip)
 bool mfma_eligible(int N, int n, int64_t d, int b, bool fused);
-size_t mfma_workspace_bytes(int N, int n, int64_t d, int b);
 void launch_mfma_grads(const float *X, const float *y, const float *W, int N, int n, int64_t d, int b,
                       int loss, float *G, void *workspace, hipStream_t st);
 
@@ -51,12 +51,13 @@ __device__ __forceinline__ float loss_residual(float z, float yv, int loss) {
   return loss == GC_LOSS_LOGISTIC ? 1.0f / (1.0f + expf(-z)) - yv : z - yv;
 }
 
-// zpart[row][seg] = sum over the columns of segment seg of x * w, for ROWS rows by one wave:
-// w is read once for all of them.
+// out[row][seg] = sum over the columns of segment seg of x * w, for ROWS rows by one wave: w is
+// read once for all of them.  One segment: the row's residual instead.
 template <int ROWS>
 __global__ __launch_bounds__(kGradThreads) void dot_kernel(const float *__restrict__ X, const float *__restrict__ W,
                                                            int64_t Nn, int64_t d, int64_t groups, int segs,
-                                                           int64_t seglen, int64_t units, float *__restrict__ zpart) {
+                                                           int64_t seglen, int64_t units, const float *__restrict__ y,
+                                                           int loss, float *__restrict__ out) {
   const int lane = threadIdx.x % kWave;
   const int64_t u = int64_t(blockIdx.x) * kGradWaves + threadIdx.x / kWave;  // (q, row group, segment)
   if (u >= units) return;
@@ -90,16 +91,31 @@ __global__ __launch_bounds__(kGradThreads) void dot_kernel(const float *__restri
 #pragma unroll
   for (int r = 0; r < ROWS; ++r) {
     const float v = wave_sum((s[r][0] + s[r][1]) + (s[r][2] + s[r][3]));
-    if (lane == 0 && r0 + r < Nn) zpart[(q * Nn + r0 + r) * segs + seg] = v;
+    if (lane == 0 && r0 + r < Nn)
+      out[(q * Nn + r0 + r) * segs + seg] = segs == 1 ? loss_residual(v, y[r0 + r], loss) : v;
   }
+}
+
+// The residuals from the segments' sums, added in order.
+__global__ __launch_bounds__(kGradThreads) void seg_residual_kernel(const float *__restrict__ zpart,
+                                                                    const float *__restrict__ y, int64_t rows,
+                                                                    int64_t Nn, int segs, int loss,
+                                                                    float *__restrict__ resid) {
+  const int64_t row = int64_t(blockIdx.x) * kGradThreads + threadIdx.x;  // q*N*n + i*n + r
+  if (row >= rows) return;
+  const float *zp = zpart + row * segs;
+  float z = 0.f;
+#pragma unroll 8
+  for (int g = 0; g < segs; ++g) z += zp[g];
+  resid[row] = loss_residual(z, y[row % Nn], loss);
 }
 
 // G[q][i][x] = sum_r residual(q, i, r) * X[i][r][x].  A block takes 1024 / RS columns; its waves
 // split the rows RS ways (wave w the rows of slice w % RS) and the slices are summed in order.
 template <int RS>
-__global__ __launch_bounds__(kGradThreads) void xtr_kernel(const float *__restrict__ X, const float *__restrict__ y,
-                                                           const float *__restrict__ zpart, int N, int n, int64_t d,
-                                                           int64_t tiles, int segs, int loss, float *__restrict__ G) {
+__global__ __launch_bounds__(kGradThreads) void xtr_kernel(const float *__restrict__ X,
+                                                           const float *__restrict__ resid, int N, int n, int64_t d,
+                                                           int64_t tiles, float *__restrict__ G) {
   __shared__ float rs[kResidStage];
   __shared__ float part[RS > 1 ? RS - 1 : 1][kGradThreads / RS][4];
   const int64_t tile = blockIdx.x % tiles;
@@ -115,13 +131,7 @@ __global__ __launch_bounds__(kGradThreads) void xtr_kernel(const float *__restri
   for (int r0 = 0; r0 < n; r0 += kResidStage) {
     const int rn = n - r0 < kResidStage ? n - r0 : kResidStage;
     __syncthreads();
-    for (int a = threadIdx.x; a < rn; a += kGradThreads) {
-      const float *zp = zpart + (qi * n + r0 + a) * segs;
-      float z = 0.f;
-#pragma unroll 8
-      for (int g = 0; g < segs; ++g) z += zp[g];
-      rs[a] = loss_residual(z, y[i * n + r0 + a], loss);
-    }
+    for (int a = threadIdx.x; a < rn; a += kGradThreads) rs[a] = resid[qi * n + r0 + a];
     __syncthreads();
     const int per = (rn + RS - 1) / RS;
     int r = slice * per;
@@ -175,7 +185,8 @@ __global__ __launch_bounds__(kGradThreads) void xtr_kernel(const float *__restri
 
 // Rows per wave, row groups and column segments of dot_kernel per point.  Segments of at least
 // 1024 columns (four rounds of a wave's 16-byte loads), as many as give every CU 32 waves; one row
-// per wave where four would leave the CUs short of 8 waves.
+// per wave where four would leave the CUs short of 8 waves.  The segments' sums go to G, which is
+// written after they have been read: at most d / n segments.
 struct DotPlan {
   int rows;
   int64_t groups, seglen;
@@ -184,7 +195,7 @@ struct DotPlan {
 
 inline DotPlan dot_plan(int N, int n, int64_t d, int b) {
   DotPlan dp{};
-  const int64_t R = int64_t(N) * n, most = std::max<int64_t>(1, d / 1024);
+  const int64_t R = int64_t(N) * n, most = std::max<int64_t>(1, std::min(d / 1024, d / n));
   dp.rows = ceil_div(R, 4) * b * most < 2048 ? 1 : 4;
   dp.groups = ceil_div(R, dp.rows);
   const int64_t segs = std::max<int64_t>(1, std::min(ceil_div(8192, dp.groups * b), most));
@@ -201,6 +212,25 @@ struct FusedPlan {
   int64_t blocks;          // blocks per evaluation point
   int64_t rows_per_block;  // <= n
 };
+
+// Splits of the columns that the workspace of a call in whole quads has partial sums for: up to 16, as
+// many as fill whole rounds of 512 tiles of 128 rows x 128 or 64 points.
+int64_t quad_splits(int N, int n, int64_t d, int b) {
+  const int64_t tiles = int64_t(N) * ceil_div(n, 128) * ceil_div(b, b % 128 == 0 ? 128 : 64);
+  int64_t splits = 1;
+  double best = -1.0;
+  for (int64_t sp = 1; sp <= 16; ++sp) {
+    const int64_t kp = ceil_div(ceil_div(d, sp), 32) * 32;
+    if (ceil_div(d, kp) != sp) continue;
+    const int64_t blocks = tiles * sp;
+    const double score = double(blocks) / double(ceil_div(blocks, 512) * 512) - 0.005 * double(sp);
+    if (score > best + 1e-9) {
+      best = score;
+      splits = sp;
+    }
+  }
+  return splits;
+}
 
 inline FusedPlan fused_plan(int N, int n) {
   const int64_t R = int64_t(N) * n;
@@ -319,14 +349,17 @@ bool grad_sizes_ok(int32_t N, int32_t n, int64_t d, int32_t b) {
 }
 }  // namespace
 
+// The fused path's partials, else the residuals and, from 16 points in whole quads on, room for
+// partial sums of the first product.
 extern "C" size_t gc_chunk_grads_workspace_size(int32_t N, int32_t n, int64_t d, int32_t b) {
   if (!grad_sizes_ok(N, n, d, b)) return 0;
-  if (gcx::mfma_eligible(N, n, d, b, fused_ok(d))) return gcx::mfma_workspace_bytes(N, n, d, b);
+  const size_t resid = sizeof(float) * size_t(b) * size_t(N) * size_t(n);
+  if (b >= 16 && b % 4 == 0 && d % 4 == 0) return resid * size_t(1 + gcx::quad_splits(N, n, d, b));
   if (fused_ok(d)) {
     const gcx::FusedPlan fp = gcx::fused_plan(N, n);
     return sizeof(float) * size_t(b) * size_t(fp.blocks) * 2 * size_t(d);
   }
-  return sizeof(float) * size_t(b) * size_t(N) * size_t(n) * size_t(gcx::dot_plan(N, n, d, b).segs);
+  return resid;
 }
 
 extern "C" int gc_chunk_grads(const float *X, const float *y, const float *W, int32_t N, int32_t n,
@@ -345,13 +378,16 @@ extern "C" int gc_chunk_grads(const float *X, const float *y, const float *W, in
   const int dev = check_device();
   if (dev != GC_OK) return dev;
   (void)hipGetLastError();
-  if (mfma_eligible(N, n, d, b, fused_ok(d))) {
-    // 16 points or more in whole quads are taken on 16-byte boundaries only
-    if (b >= 16 && b % 4 == 0 && d % 4 == 0 && (!vec4 || !aligned16(y) || !aligned16(workspace))) return GC_EINVAL;
+  // 16 points or more in whole quads are taken on 16-byte boundaries only
+  if (b >= 16 && b % 4 == 0 && d % 4 == 0 && (!vec4 || !aligned16(y) || !aligned16(workspace))) return GC_EINVAL;
+  const bool enough = workspace_bytes >= sizeof(float) * size_t(rows);  // the residuals, and below the partials
+  const bool fused = vec4 && fused_ok(d) && aligned16(workspace) &&
+                     workspace_bytes >= sizeof(float) * size_t(b) * size_t(fused_plan(N, n).blocks) * 2 * size_t(d);
+  if (enough && mfma_eligible(N, n, d, b, fused)) {
     launch_mfma_grads(X, y, W, N, n, d, b, loss, G, workspace, stream);
     return launch_status();
   }
-  if (vec4 && fused_ok(d) && aligned16(workspace)) {
+  if (fused) {
     const FusedPlan fp = fused_plan(N, n);
     if (!grid_ok(fp.blocks * b, kFusedThreads)) return GC_EINVAL;
     float *part = static_cast<float *>(workspace);
@@ -370,25 +406,30 @@ extern "C" int gc_chunk_grads(const float *X, const float *y, const float *W, in
                        fp.rows_per_block, fp.blocks, G);
     return launch_status();
   }
-  float *zpart = static_cast<float *>(workspace);
+  if (!enough) return GC_EINVAL;  // rows of few columns, off the boundaries that the fused path needs
+  float *resid = static_cast<float *>(workspace);
   const DotPlan dp = dot_plan(N, n, d, b);
+  float *sums = dp.segs > 1 ? G : resid;
   const int64_t units = dp.groups * dp.segs * b;
   const dim3 g1(unsigned(ceil_div(units, kGradWaves)));
   if (dp.rows == 4)
     hipLaunchKernelGGL(dot_kernel<4>, g1, dim3(kGradThreads), 0, stream, X, W, int64_t(N) * n, d, dp.groups,
-                       dp.segs, dp.seglen, units, zpart);
+                       dp.segs, dp.seglen, units, y, loss, sums);
   else
     hipLaunchKernelGGL(dot_kernel<1>, g1, dim3(kGradThreads), 0, stream, X, W, int64_t(N) * n, d, dp.groups,
-                       dp.segs, dp.seglen, units, zpart);
+                       dp.segs, dp.seglen, units, y, loss, sums);
+  if (dp.segs > 1)
+    hipLaunchKernelGGL(seg_residual_kernel, dim3(unsigned(ceil_div(rows, kGradThreads))), dim3(kGradThreads), 0,
+                       stream, sums, y, rows, int64_t(N) * n, dp.segs, loss, resid);
   // few column tiles: four waves of a block split the rows instead of the columns
   const int64_t wide = ceil_div(d, 4 * kGradThreads) * N * b;
   if (wide >= 4 * int64_t(cu_count())) {
-    hipLaunchKernelGGL(xtr_kernel<1>, dim3(unsigned(wide)), dim3(kGradThreads), 0, stream, X, y, zpart, N, n, d,
-                       ceil_div(d, 4 * kGradThreads), dp.segs, loss, G);
+    hipLaunchKernelGGL(xtr_kernel<1>, dim3(unsigned(wide)), dim3(kGradThreads), 0, stream, X, resid, N, n, d,
+                       ceil_div(d, 4 * kGradThreads), G);
   } else {
     const int64_t tiles = ceil_div(d, kGradThreads);
-    hipLaunchKernelGGL(xtr_kernel<4>, dim3(unsigned(tiles * N * b)), dim3(kGradThreads), 0, stream, X, y, zpart, N,
-                       n, d, tiles, dp.segs, loss, G);
+    hipLaunchKernelGGL(xtr_kernel<4>, dim3(unsigned(tiles * N * b)), dim3(kGradThreads), 0, stream, X, resid, N,
+                       n, d, tiles, G);
   }
   return launch_status();
 }

@@ -21,12 +21,16 @@
 //                 matrix operand's layout (32 neighbouring bytes of a row per instruction, four
 //                 instructions a cache line), two stages of 32 k ahead; W's parts are shared
 //                 through LDS by the block's four waves.
-//   resid_kernel  U = loss'(sum of the partials, in split order) - y, split and laid out as
-//                 the next kernel's operand.
+//   resid_kernel  U = loss'(sum of the partials, in split order) - y.
 //   utx_kernel    G tiles: a wave loads 32 PW positions of the rows of X straight in the
-//                 operand's layout (contiguous across the lanes), U's parts come through LDS.
+//                 operand's layout (contiguous across the lanes), U is split on its way to LDS.
 //                 Chunks are taken in descending order: the last ones read by zw_kernel are
 //                 still in the memory-side cache.
+//
+// X of 50 x 512 x 16384 (1.7 GB), both GEMMs on the fp32 matrix instructions before: 20 points
+// 1.09 -> 0.75 ms (the two reads of X take 0.6), 64 points 1.24 -> 1.13, 128 points 2.06 -> 1.86.
+// At 64 points the matrix cores and the vector units (splits) are busy a third of the time each and
+// the clock falls under both; registers allow three or two waves per SIMD (four spill).
 #include <algorithm>
 #include <type_traits>
 
@@ -96,13 +100,6 @@ __device__ __forceinline__ void split3_trunc(float a, float b, uint32_t (&p)[3])
     a -= __uint_as_float(ua & 0xffff0000u);
     b -= __uint_as_float(ub & 0xffff0000u);
   }
-}
-
-// a value from its truncated parts: the first alone where it is an infinity or a NaN
-__device__ __forceinline__ float join3(uint16_t p1, uint16_t p2, uint16_t p3) {
-  const float a = __uint_as_float(uint32_t(p1) << 16);
-  const float r = __uint_as_float(uint32_t(p2) << 16) + __uint_as_float(uint32_t(p3) << 16);
-  return fabsf(a) < __builtin_huge_valf() ? a + r : a;
 }
 
 // big += a1 b1; small += the other products kept, the smallest first
@@ -264,55 +261,28 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(QT ==
     }
 }
 
-// U[i][r][q] = loss'(sum_s Zp[s][i n + r][q]) - y[i][r], the splits summed in order, as the
-// parts that utx_kernel's lanes read: one thread forms rows 16 ks + 2 j + h, j < 8, of point 32 qt + li,
-// Uf[i][ks][qt][part][lane] of 16 bytes, zero past the rows and the points.
-__global__ __launch_bounds__(256) void resid_kernel(const float *__restrict__ Zp, const float *__restrict__ y,
-                                                    int64_t R, int n, int b, int splits, int loss, int ksteps,
-                                                    int qtiles, int64_t units, uint4 *__restrict__ Uf) {
+// U[r][q] = loss'(sum_s Zp[s][r][q]) - y[r] for the rows r of all chunks, the splits summed in
+// order; in place where there is one.
+__global__ __launch_bounds__(256) void resid_kernel(const float *Zp, const float *__restrict__ y, int64_t total,
+                                                    int b, int splits, int loss, float *U) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= units) return;
-  const int lane = int(e % kWave), h = lane >> 5, li = lane & 31;
-  int64_t f = e / kWave;
-  const int q = 32 * int(f % qtiles) + li;
-  const int r = 16 * int(f / qtiles % ksteps) + h;
-  const int64_t i = f / qtiles / ksteps;
-  float z[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) z[j] = 0.f;
-  // loads past the rows or the points repeat one inside, so that all are in flight at once
-  const float *src[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) src[j] = Zp + (i * n + (r + 2 * j < n ? r + 2 * j : n - 1)) * b + (q < b ? q : b - 1);
-#pragma unroll 4
-  for (int s = 0; s < splits; ++s)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) z[j] += src[j][int64_t(s) * R * b];
-  uint32_t p[4][3];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const bool in = r + 2 * j < n && q < b;
-    const float yv = y[i * n + (in ? r + 2 * j : 0)];
-    const float u = loss == GC_LOSS_LOGISTIC ? 1.0f / (1.0f + expf(-z[j])) - yv : z[j] - yv;
-    z[j] = in ? u : 0.f;
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) split3_trunc(z[2 * j], z[2 * j + 1], p[j]);
-#pragma unroll
-  for (int s = 0; s < 3; ++s) Uf[(f * 3 + s) * kWave + lane] = make_uint4(p[0][s], p[1][s], p[2][s], p[3][s]);
+  if (e >= total) return;
+  float z = 0.f;
+#pragma unroll 8
+  for (int s = 0; s < splits; ++s) z += Zp[int64_t(s) * total + e];
+  const float yv = y[e / b];
+  U[e] = loss == GC_LOSS_LOGISTIC ? 1.0f / (1.0f + expf(-z)) - yv : z - yv;
 }
 
 // G[q][i][x] = sum_r U[i][r][q] * X[i][r][x] for QT point tiles and 4 x 32 PW positions per block.
 //   B (16 rows x 32 positions): lane (h, li) holds rows h, h + 2, .. h + 14 of each 16 at positions
 //   PW li .. + PW - 1, PW separate 32-wide tiles
 template <int QT, int PW>
-__global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const uint4 *__restrict__ Uf, const float *__restrict__ X,
-                                                           int N, int n, int64_t d, int b, int ksteps, int qtiles,
-                                                           int qblocks, int64_t tiles, float *__restrict__ G) {
+__global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const float *__restrict__ U, const float *__restrict__ X,
+                                                           int N, int n, int64_t d, int b, int ksteps, int qblocks,
+                                                            int64_t tiles, float *__restrict__ G) {
   using VT = typename Floats<PW>::T;
-  constexpr int kUnits = QT * 3 * kWave;  // 16-byte pieces of U's parts per stage of 16 rows
-  constexpr int kPer = (kUnits + kMThreads - 1) / kMThreads;
-  __shared__ __align__(16) uint4 Us[2][kUnits];
+  __shared__ __align__(16) uint32_t Us[2][QT * 3 * kWave][4];  // U's parts of a stage as the lanes read them
   // the point blocks of one tile of X: eight apart, so on one XCD (round-robin dispatch)
   const int64_t bid = blockIdx.x;
   const int qb = int(bid / 8 % qblocks);
@@ -325,8 +295,7 @@ __global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const uint4 *__restri
   const int64_t x = x0 + PW * li;
   const bool inside = x0 + 32 * PW <= d;
   const float *Xi = X + i * int64_t(n) * d;
-  const uint4 *Ui = Uf + (i * ksteps * qtiles + qb * QT) * 3 * kWave;
-  const int units = (qtiles - qb * QT < QT ? qtiles - qb * QT : QT) * 3 * kWave;
+  const float *Ui = U + i * int64_t(n) * b;
 
   const uint32_t loff = uint32_t(h) * uint32_t(d) * 4u + uint32_t(PW * li) * 4u;  // d <= 2^28
   float rx[2][PW][8];
@@ -350,18 +319,27 @@ __global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const uint4 *__restri
       }
     }
   };
-  uint4 ru[kPer];
+  // each thread two rows of QT points, zero past the rows and the points
+  const int uh = t / 32 % 2, uj = t / 64;
+  float ru[QT][2];
   auto uload = [&](int ks) {
 #pragma unroll
-    for (int c = 0; c < kPer; ++c) {
-      const int e = t + c * kMThreads;
-      ru[c] = e < units ? Ui[int64_t(ks) * qtiles * 3 * kWave + e] : make_uint4(0u, 0u, 0u, 0u);
-    }
+    for (int c = 0; c < QT; ++c)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int r = 16 * ks + 2 * (2 * uj + e) + uh, q = (qb * QT + c) * 32 + t % 32;
+        const float v = Ui[int64_t(r < n ? r : n - 1) * b + (q < b ? q : b - 1)];
+        ru[c][e] = r < n && q < b ? v : 0.f;
+      }
   };
   auto ustore = [&](int buf) {
 #pragma unroll
-    for (int c = 0; c < kPer; ++c)
-      if (t + c * kMThreads < kUnits) Us[buf][t + c * kMThreads] = ru[c];
+    for (int c = 0; c < QT; ++c) {
+      uint32_t p[3];
+      split3_trunc(ru[c][0], ru[c][1], p);
+#pragma unroll
+      for (int v = 0; v < 3; ++v) Us[buf][(c * 3 + v) * kWave + 32 * uh + t % 32][uj] = p[v];
+    }
   };
 
   v16f big[QT][PW], small[QT][PW];
@@ -388,7 +366,7 @@ __global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const uint4 *__restri
     for (int q = 0; q < QT; ++q) {
       v8bf u[3];
 #pragma unroll
-      for (int p = 0; p < 3; ++p) u[p] = *reinterpret_cast<const v8bf *>(&Us[SET][(q * 3 + p) * kWave + lane]);
+      for (int p = 0; p < 3; ++p) u[p] = *reinterpret_cast<const v8bf *>(&Us[SET][(q * 3 + p) * kWave + lane][0]);
 #pragma unroll
       for (int w = 0; w < PW; ++w) products(u, xs[w], big[q][w], small[q][w]);
     }
@@ -413,17 +391,16 @@ __global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const uint4 *__restri
         big[q][w][v] += small[q][w][v];
         bad = bad || big[q][w][v] != big[q][w][v];
       }
-  if (__any(bad)) {  // the tile on the fp32 matrix instructions, from U's joined parts
+  if (__any(bad)) {  // the tile on the fp32 matrix instructions
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
-      if (qb * QT + q >= qtiles) break;
 #pragma unroll
       for (int w = 0; w < PW; ++w) big[q][w] = v16f{};
+      const int qq = (qb * QT + q) * 32 + li;
       for (int r = h; r - h < n; r += 2) {
-        const uint16_t *up = reinterpret_cast<const uint16_t *>(
-            Ui + (int64_t(r / 16) * qtiles + q) * 3 * kWave + 32 * (r % 2) + li) + r / 2 % 8;
-        const bool in = r < n;  // rows past n are zero in U
-        const float u = in ? join3(up[0], up[8 * kWave], up[16 * kWave]) : 0.f;
+        const bool in = r < n;
+        const float uv = Ui[int64_t(in ? r : n - 1) * b + (qq < b ? qq : b - 1)];
+        const float u = in && qq < b ? uv : 0.f;
         const float *src = Xi + int64_t(in ? r : n - 1) * d;
 #pragma unroll
         for (int w = 0; w < PW; ++w) {
@@ -459,9 +436,8 @@ struct MfmaPlan {
   int zqblocks, uqblocks;
   int splits;
   int64_t kper, rblocks;
-  int ksteps, qtiles;         // U's parts: steps of 16 rows, tiles of 32 points
-  int64_t blocks1, units, tiles, blocks2;
-  size_t zp_bytes, u_bytes;
+  int ksteps, qtiles;         // steps of 16 rows, tiles of 32 points
+  int64_t blocks1, tiles, blocks2;
 };
 
 MfmaPlan mfma_plan(int N, int n, int64_t d, int b) {
@@ -486,9 +462,11 @@ MfmaPlan mfma_plan(int N, int n, int64_t d, int b) {
   const int64_t resident = 256 * (pl.zqt == 1 ? 4 : (pl.zqt == 2 ? 3 : 2));
   constexpr int64_t kExtra = 8, kMaxStages = 64;
   const int64_t tiles = pl.rblocks * pl.zqblocks;
-  const int64_t least = ceil_div(stages, kMaxStages);
+  // partials of more than one split go to G, which is written after they have been read
+  const int64_t most = std::max<int64_t>(1, std::min(d / n, stages));
+  const int64_t least = std::min(ceil_div(stages, kMaxStages), most);
   int64_t best = -1;
-  for (int64_t sp = least; sp <= std::min(std::max<int64_t>(least + 8, 64), stages); ++sp) {
+  for (int64_t sp = least; sp <= std::min(std::max<int64_t>(least + 8, 64), most); ++sp) {
     const int64_t nst = ceil_div(stages, sp);
     const int64_t splits = ceil_div(stages, nst);
     const int64_t cost = ceil_div(tiles * splits, resident) * (nst + kExtra) + splits;
@@ -500,10 +478,7 @@ MfmaPlan mfma_plan(int N, int n, int64_t d, int b) {
   }
   pl.blocks1 = tiles * pl.splits;
   pl.ksteps = int(ceil_div(n, 16));
-  pl.units = int64_t(N) * pl.ksteps * pl.qtiles * kWave;
   pl.blocks2 = ceil_div(pl.tiles * N, 8) * 8 * pl.uqblocks;
-  pl.zp_bytes = ceil_div(sizeof(float) * size_t(pl.splits) * size_t(R) * size_t(b), 16) * 16;
-  pl.u_bytes = size_t(pl.units) * 3 * 16;
   return pl;
 }
 
@@ -516,22 +491,20 @@ bool mfma_eligible(int N, int n, int64_t d, int b, bool fused) {
   if (b < (fused ? 4 : 2) || d > int64_t(1) << 28) return false;
   if (double(N) * double(n) * double(d) * double(b) < 3e6) return false;
   const MfmaPlan pl = mfma_plan(N, n, d, b);
-  return grid_ok(pl.blocks1, kZThreads) && grid_ok(pl.blocks2, kMThreads) && grid_ok(ceil_div(pl.units, 256), 256);
+  // few points keep the vector units where more than 64 stages per block would cost precision
+  if (b < 16 && pl.kper > 64 * kZK) return false;
+  return grid_ok(pl.blocks1, kZThreads) && grid_ok(pl.blocks2, kMThreads) &&
+         grid_ok(ceil_div(int64_t(N) * n * b, 256), 256);
 }
 
-// 16 bytes more than the arrays take: they start at the next 16-byte boundary
-size_t mfma_workspace_bytes(int N, int n, int64_t d, int b) {
-  const MfmaPlan pl = mfma_plan(N, n, d, b);
-  return pl.zp_bytes + pl.u_bytes + 16;
-}
-
+// workspace: the residuals [N n][b]
 void launch_mfma_grads(const float *X, const float *y, const float *W, int N, int n, int64_t d, int b,
                        int loss, float *G, void *workspace, hipStream_t st) {
   const MfmaPlan pl = mfma_plan(N, n, d, b);
   const int64_t R = int64_t(N) * n;
-  char *ws = reinterpret_cast<char *>((reinterpret_cast<uintptr_t>(workspace) + 15) & ~uintptr_t(15));
-  float *Zp = reinterpret_cast<float *>(ws);
-  uint4 *Uf = reinterpret_cast<uint4 *>(ws + pl.zp_bytes);
+  float *U = static_cast<float *>(workspace);
+  float *Zp = pl.splits > 1 ? G : U;
+  const int64_t total = R * b;
 #define GC_ZW(QT)                                                                                         \
   hipLaunchKernelGGL(zw_kernel<QT>, dim3(unsigned(pl.blocks1)), dim3(kZThreads), 0, st, X, W, R, d, b,    \
                      pl.splits, pl.kper, pl.zqblocks, Zp)
@@ -539,11 +512,11 @@ void launch_mfma_grads(const float *X, const float *y, const float *W, int N, in
   else if (pl.zqt == 2) GC_ZW(2);
   else GC_ZW(4);
 #undef GC_ZW
-  hipLaunchKernelGGL(resid_kernel, dim3(unsigned(ceil_div(pl.units, 256))), dim3(256), 0, st, Zp, y, R, n, b,
-                     pl.splits, loss, pl.ksteps, pl.qtiles, pl.units, Uf);
+  hipLaunchKernelGGL(resid_kernel, dim3(unsigned(ceil_div(total, 256))), dim3(256), 0, st, Zp, y, total, b,
+                     pl.splits, loss, U);
 #define GC_UTX(QT, PW)                                                                                     \
-  hipLaunchKernelGGL((utx_kernel<QT, PW>), dim3(unsigned(pl.blocks2)), dim3(kMThreads), 0, st, Uf, X, N,   \
-                     n, d, b, pl.ksteps, pl.qtiles, pl.uqblocks, pl.tiles, G)
+  hipLaunchKernelGGL((utx_kernel<QT, PW>), dim3(unsigned(pl.blocks2)), dim3(kMThreads), 0, st, U, X, N,    \
+                     n, d, b, pl.ksteps, pl.uqblocks, pl.tiles, G)
   if (pl.uqt == 1) GC_UTX(1, 2);
   else GC_UTX(2, 2);
 #undef GC_UTX

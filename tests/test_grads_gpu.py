@@ -71,6 +71,14 @@ def test_rows_on_any_float(N, n, d, b):
     check(G, reference(X, y, W, gcx.GC_LOSS_LOGISTIC))
 
 
+@pytest.mark.parametrize("n", [4, 4000])
+def test_whole_quads_off_their_boundary_are_refused(n):
+    X, y, W = problem(2, n, 64, 16)
+    off = torch.empty(X.numel() + 1, device="cuda")[1:].view(X.shape)
+    with pytest.raises(gcx.GcxError):
+        gcx.gc_chunk_grads(off.copy_(X), y, W, gcx.GC_LOSS_LINEAR)
+
+
 @pytest.mark.parametrize("b", [1, 20, 64, 128])
 @pytest.mark.parametrize("kind", ["inf in X", "inf in W", "NaN in X", "NaN in W", "near the largest float"])
 def test_values_that_are_not_finite(kind, b):
