@@ -28,7 +28,7 @@
 //                 still in the memory-side cache.
 //
 // X of 50 x 512 x 16384 (1.7 GB), both GEMMs on the fp32 matrix instructions before: 20 points
-// 1.09 -> 0.75 ms (the two reads of X take 0.6), 64 points 1.24 -> 1.13, 128 points 2.06 -> 1.86.
+// 1.11 -> 0.73 ms (the two reads of X take 0.6), 64 points 1.22 -> 1.01, 128 points 2.03 -> 1.65.
 // At 64 points the matrix cores and the vector units (splits) are busy a third of the time each and
 // the clock falls under both; registers allow three or two waves per SIMD (four spill).
 #include <algorithm>
@@ -322,7 +322,25 @@ __global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const float *__restri
   // each thread two rows of QT points, zero past the rows and the points
   const int uh = t / 32 % 2, uj = t / 64;
   float ru[QT][2];
+  // the thread's first row of the first stage (addresses formed anew per stage cost 12% at 64 points)
+  const float *up[QT];
+#pragma unroll
+  for (int c = 0; c < QT; ++c) {
+    const int q = (qb * QT + c) * 32 + t % 32;
+    up[c] = Ui + int64_t(4 * uj + uh) * b + (q < b ? q : b - 1);
+  }
   auto uload = [&](int ks) {
+    if (16 * ks + 16 <= n) {
+#pragma unroll
+      for (int c = 0; c < QT; ++c) {
+        const float *src = up[c] + int64_t(16 * ks) * b;
+        const bool in = (qb * QT + c) * 32 + t % 32 < b;
+        const float v0 = src[0], v1 = src[2 * int64_t(b)];
+        ru[c][0] = in ? v0 : 0.f;
+        ru[c][1] = in ? v1 : 0.f;
+      }
+      return;
+    }
 #pragma unroll
     for (int c = 0; c < QT; ++c)
 #pragma unroll
