@@ -37,6 +37,8 @@ constexpr size_t kEncMetaLds = 24 * 1024;    // row metadata budget
 constexpr int kEncGroup = 256;               // rows of metadata staged per step, at most
 constexpr int kEncGroupsPerBlock = 2;        // rows per block = 2 groups
 constexpr int64_t kEncFewRows = 128, kEncFewOutputs = int64_t(1) << 22;  // small calls keep this layout
+constexpr int64_t kEncShortRow = 64;  // and so do rows of at most one wave's positions with at most
+constexpr int kEncShortTerms = 8;     // this many terms per output
 
 template <typename GT>
 __device__ __forceinline__ float to_f32(GT v);
@@ -1003,10 +1005,13 @@ extern "C" int gc_encode(const void *G, int32_t g_dtype, int32_t N, int64_t d, c
   // matrix cores; on rows that start anywhere its narrow accesses lose: m = 37, ell = 3, d = 100003
   // 2.1 ms against 0.62), and on any rows for calls that are over in a few microseconds, where
   // its shorter setup counts (m = 20, ell = 3, d = 131075, 4 patterns 12 us against 17; m = 60, d =
-  // 32770, one pattern 11 against 13; m = 20, d = 131075, 32 patterns 45 against 26).  Else the
-  // matrix cores up to 176 (fp32) or 192 (bf16) terms per output, and past that the worker
-  // groups.
-  const bool few = a.rows <= kEncFewRows && a.rows * a.L <= kEncFewOutputs;
+  // 32770, one pattern 11 against 13; m = 20, d = 131075, 32 patterns 45 against 26), and for few
+  // terms on rows of at most one wave's positions, where three of a matrix-core block's four waves
+  // have no tile (600,000 rows of L = 33: 3 terms 51 us against 73, 6 terms 62 against 78, 10 terms 79
+  // against 84, 21 terms 144 against 154; L = 65, 3 terms 110 against 77).  Else the matrix cores up
+  // to 176 (fp32) or 192 (bf16) terms per output, and past that the worker groups.
+  const bool few = (a.rows <= kEncFewRows && a.rows * a.L <= kEncFewOutputs) ||
+                   (a.L <= kEncShortRow && delta * ell <= kEncShortTerms);
   if (((vec == 4 && a.stage16) || few) && size_t(N) * ell * kWave * vec * esize <= kEncSliceLds) {
     const int st = g_dtype == GC_F32 ? dispatch_all_chunks<float>(a, vec, stream)
                                      : dispatch_all_chunks<uint16_t>(a, vec, stream);

@@ -127,7 +127,10 @@ struct MxArgs {
   int ngroups;
   int64_t ntp;   // pattern windows
   int slots;     // chunk slots (rows of B / ell)
-  int64_t ntiles, tpb, nsr;  // position tiles, per block, ranges (a multiple of 8)
+  int64_t ntiles, tpb, nsr;  // position tiles, per block, ranges
+  // grid: (group, pattern window) units; blocks of the ranges in whole eights; (range, unit) pairs of
+  // the ranges left, and an eighth of them
+  uint32_t units, whole, left, eighth;
 };
 
 // dynamic LDS of a block, as laid out at the kernel
@@ -210,16 +213,25 @@ encode_mx_kernel(MxArgs a) {
   __shared__ int nuni_s, jn_s;
 
   // block -> (position range, unit = (group, pattern window)); XCD x takes ranges x, x + 8, ...
+  // of whole eights, and an eighth of the (range, unit) pairs of the ranges left: all of them on
+  // short rows, where whole ranges would leave XCDs idle (m = 37, d = 1001, ell = 3, 5000 patterns,
+  // one range: 540 us on one XCD, 83 on eight; m = 50, d = 2047, ell = 2, two: 549, 209)
   const int nth = blockDim.x;
-  const int64_t b = blockIdx.x;
-  const int64_t units = int64_t(a.ngroups) * a.ntp;
-  const int64_t sr = (b & 7) + 8 * ((b >> 3) / units);
-  const int64_t unit = (b >> 3) % units;
-  const int64_t t_begin = sr * a.tpb;
+  uint32_t b = blockIdx.x, sr, unit;
+  if (b < a.whole) {
+    sr = (b & 7) + 8 * ((b >> 3) / a.units);
+    unit = (b >> 3) % a.units;
+  } else {
+    b -= a.whole;
+    const uint32_t e = (b & 7) * a.eighth + (b >> 3);
+    if (e >= a.left) return;  // the whole block
+    sr = uint32_t(a.nsr & ~int64_t(7)) + e / a.units;
+    unit = e % a.units;
+  }
+  const int64_t t_begin = int64_t(sr) * a.tpb;
   const int64_t t_end = t_begin + a.tpb < a.ntiles ? t_begin + a.tpb : a.ntiles;
-  if (t_begin >= t_end) return;  // the whole block: an empty range at the end
-  const int64_t p0 = (unit / a.ngroups) * a.PB;
-  const int j0 = int(unit % a.ngroups) * a.J;
+  const int64_t p0 = int64_t(unit / uint32_t(a.ngroups)) * a.PB;
+  const int j0 = int(unit % uint32_t(a.ngroups)) * a.J;
   const int nj = a.m - j0 < a.J ? a.m - j0 : a.J;
   const int ell = a.ell;
   float *const Tw = a.T + (p0 * a.m + j0) * a.L;  // row (pattern p0, worker j0) of T
@@ -540,11 +552,23 @@ encode_mx_kernel(MxArgs a) {
   }
 }
 
+// The grid of a launch and its blocks: every (range, unit) pair, those of the ranges past whole eights
+// in eight equal parts.  False past the launch limits.
+bool mx_grid(MxArgs &a, int threads, int64_t *blocks) {
+  const int64_t units = int64_t(a.ngroups) * a.ntp, eights = a.nsr & ~int64_t(7);
+  const int64_t left = (a.nsr - eights) * units;
+  *blocks = eights * units + 8 * ceil_div(left, 8);
+  if (!grid_ok(*blocks, threads)) return false;
+  a.units = uint32_t(units);
+  a.whole = uint32_t(eights * units);
+  a.left = uint32_t(left);
+  a.eighth = uint32_t(ceil_div(left, 8));
+  return true;
+}
+
 template <typename GT, int KS, int PW>
-int launch_mx(const MxArgs &a, int threads, hipStream_t st) {
+int launch_mx(const MxArgs &a, int64_t blocks, int threads, hipStream_t st) {
   const size_t lds = mx_lds(a, KS);
-  const int64_t blocks = a.nsr * a.ngroups * a.ntp;
-  if (!grid_ok(blocks, threads)) return GC_EINVAL;
   if (hipFuncSetAttribute(reinterpret_cast<const void *>(&encode_mx_kernel<GT, KS, PW>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess)
     return GC_ELAUNCH;
@@ -619,15 +643,17 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
   const int64_t units = int64_t(a.ngroups) * a.ntp;
   a.tpb = int64_t(nw) * (KS <= 3 ? 2 : 8);
   while (a.tpb > nw && ceil_div(a.ntiles, a.tpb) * units < 4 * int64_t(cu_count())) a.tpb -= nw;
-  a.nsr = ceil_div(ceil_div(a.ntiles, a.tpb), 8) * 8;
-  while (a.nsr > 8 && a.nsr * units > 0xffffffffLL / kMxThreads) {  // the launch limits
+  a.nsr = ceil_div(a.ntiles, a.tpb);
+  int64_t blocks = 0;
+  while (!mx_grid(a, threads, &blocks) && a.nsr > 1) {
     a.tpb *= 2;
-    a.nsr = ceil_div(ceil_div(a.ntiles, a.tpb), 8) * 8;
+    a.nsr = ceil_div(a.ntiles, a.tpb);
   }
+  if (!mx_grid(a, threads, &blocks)) return GC_EINVAL;
 #define GC_BF16_CASE(K, PWN) \
-  case K: return launch_mx<uint16_t, K, PWN>(a, threads, stream);
+  case K: return launch_mx<uint16_t, K, PWN>(a, blocks, threads, stream);
 #define GC_F32_CASE(K, PWN) \
-  case K: return launch_mx<float, K, PWN>(a, threads, stream);
+  case K: return launch_mx<float, K, PWN>(a, blocks, threads, stream);
   if (!f32) {
     switch (KS) {
       GC_BF16_CASE(1, 4) GC_BF16_CASE(2, 4) GC_BF16_CASE(3, 4) GC_BF16_CASE(4, 4) GC_BF16_CASE(5, 4)

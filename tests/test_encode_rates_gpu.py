@@ -1,0 +1,41 @@
+"""The encode's time against a fill of the bytes that it writes, at sizes where its plan decides
+between a good and a bad use of the chip.  Bars: about midway between the two ratios measured."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2405_19509_amd import gcx  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def fastest(fn, reps=7):
+    fn()
+    ms = []
+    for _ in range(reps):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        fn()
+        fn()
+        e1.record()
+        e1.synchronize()
+        ms.append(e0.elapsed_time(e1) / 2)
+    return min(ms)
+
+
+def encode_over_fill(m, delta, ell, d, P):
+    _, order, _, _ = gcx.gc_assign(gcx.GC_ASSIGN_CYCLIC, m, m, delta - 1)
+    order = torch.from_numpy(order).cuda()
+    g = torch.Generator(device="cuda").manual_seed(m + P)
+    psi = torch.randint(max(1, delta // 2), delta + 1, (P, m), generator=g, device="cuda", dtype=torch.int32)
+    G = torch.randn((m, d), generator=g, device="cuda")
+    Bc = torch.randn((P, m, delta, ell), generator=g, device="cuda")
+    T = torch.empty((P, m, -(-d // ell)), device="cuda")
+    return fastest(lambda: gcx.gc_encode(G, psi, order, Bc, T=T)) / fastest(lambda: T.fill_(1.0))
+
+
+def test_short_rows_use_every_xcd():
+    """Rows of one and two position ranges (540 and 549 us on one and two XCDs, 83 and 209 on all)."""
+    assert encode_over_fill(37, 7, 3, 1001, 5000) < 6
+    assert encode_over_fill(50, 5, 2, 2047, 5000) < 4
