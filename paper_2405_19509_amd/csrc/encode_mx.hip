@@ -649,7 +649,13 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
     a.tpb *= 2;
     a.nsr = ceil_div(a.ntiles, a.tpb);
   }
-  if (!mx_grid(a, threads, &blocks)) return GC_EINVAL;
+  if (!mx_grid(a, threads, &blocks)) {  // so many windows: half of the patterns at a time
+    const int64_t half = P / 2;
+    const int st = encode_mx(G, f32, N, d, psi, order, Bc, half, m, delta, ell, T, stream);
+    if (st != GC_OK) return st;
+    return encode_mx(G, f32, N, d, psi + half * m, order, Bc + half * m * delta * ell, P - half, m, delta, ell,
+                     T + half * m * a.L, stream);
+  }
 #define GC_BF16_CASE(K, PWN) \
   case K: return launch_mx<uint16_t, K, PWN>(a, blocks, threads, stream);
 #define GC_F32_CASE(K, PWN) \

@@ -75,3 +75,26 @@ def test_abi_limits():
     assert (np.abs(host(ghd).astype(np.float64) - ref) <= bound + 1e-30).all()
     # the decodable pattern recovers the sum of the chunk gradients
     assert np.abs(host(ghd)[1] - G64.sum(axis=0)).max() <= 1e-3 * np.abs(G64).sum(axis=0).max()
+
+
+def test_encode_of_very_many_windows():
+    """A hundred million patterns of short rows off their boundaries: more windows than eight blocks
+    each would leave within the launch limits."""
+    m, delta, ell, d, P = 6, 6, 2, 7, 100_000_000
+    if torch.cuda.mem_get_info()[0] < 60 << 30:
+        pytest.skip("needs 60 GB of device memory")
+    _, order, _, _ = gcx.gc_assign(gcx.GC_ASSIGN_CYCLIC, m, m, delta - 1)
+    G = torch.randn((m, d), device="cuda")
+    psi = torch.full((P, m), delta, dtype=torch.int32, device="cuda")
+    Bc = torch.empty((P, m, delta, ell), device="cuda")
+    base = torch.randn((1 << 16, m, delta, ell), device="cuda")
+    for p in range(0, P, 1 << 16):
+        Bc[p:p + (1 << 16)] = base[:min(1 << 16, P - p)]
+    T = gcx.gc_encode(G, psi, dev(order), Bc)
+    few = gcx.gc_encode(G, psi[:1 << 16], dev(order), base)
+    ref, M, nterm = R_.encode_ref(host(base[:200]).astype(np.float64), host(psi[:200]), order, host(G).astype(np.float64),
+                                  ell)
+    assert (np.abs(host(few[:200]).astype(np.float64) - ref) <= R_.encode_bound(nterm, M, "f32")).all()
+    for p in (0, (P // 2) >> 16 << 16, (P - 1) >> 16 << 16):
+        n = min(1 << 16, P - p)
+        assert torch.allclose(T[p:p + n], few[:n], rtol=0, atol=1e-5)
