@@ -80,7 +80,8 @@ struct Smallest {
 
 // Chunk i reaches ell processed copies at the ell-th smallest finish time over its holders; the
 // protocol can decode once every chunk has (the proposed protocol), and original GC once every
-// chunk has ell holders that finished *all* their chunks.  One block per trial: the workers'
+// chunk has ell holders that finished *all* their chunks.  A block per trial (and every
+// gridDim.x-th one after it where the trials pass the launch limits): the workers'
 // finish times are summed once, in position order, into LDS ([m][delta], +inf for failed
 // workers), then one thread per chunk (m = 200, delta = 8, 200 trials: 7 us; a wave per trial that
 // summed the times again for every holder took 42).  Where they do not fit (kCompleteLds), LDS is
@@ -88,12 +89,12 @@ struct Smallest {
 constexpr size_t kCompleteLds = 64 * 1024;
 
 __global__ __launch_bounds__(kSimThreads) void completion_kernel(
-    const double *__restrict__ tau, const uint8_t *__restrict__ failed, int N, int m, int delta,
+    const double *__restrict__ tau, const uint8_t *__restrict__ failed, int64_t R, int N, int m, int delta,
     const int32_t *__restrict__ holder, const int32_t *__restrict__ hpos, int gamma, int ell, int staged,
     double *__restrict__ partial, double *__restrict__ original) {
   extern __shared__ double done[];  // [m][delta] (staged)
   __shared__ double red[2][kSimWaves];
-  const int64_t r = blockIdx.x;
+  for (int64_t r = blockIdx.x; r < R; r += gridDim.x) {
   const double *tr = tau + r * int64_t(m) * delta;
   if (staged) {
     for (int j = threadIdx.x; j < m; j += kSimThreads) {
@@ -157,6 +158,8 @@ __global__ __launch_bounds__(kSimThreads) void completion_kernel(
     partial[r] = worst_p;
     original[r] = worst_o;
   }
+  if (r + gridDim.x < R) __syncthreads();  // the next trial overwrites the times and the waves' maxima
+  }  // trials
 }
 
 // Sum over the wave by DPP, without LDS: lane i of each row of 16 adds lanes i - 1, i - 2, i - 4 and
@@ -427,14 +430,15 @@ extern "C" int gc_completion_times(const double *tau, const uint8_t *failed, int
   if (!sizes_ok({R, m, delta}) || !sizes_ok({N, gamma})) return GC_EINVAL;  // tau, tables
   if (R == 0) return GC_OK;
   if (!tau || !holder || !hpos || !partial || !original) return GC_EINVAL;
-  if (!grid_ok(R, kSimThreads)) return GC_EINVAL;
+  if (!grid_ok(ceil_div(R, kSimWaves), kSimThreads)) return GC_EINVAL;
   const int dev = check_device();
   if (dev != GC_OK) return dev;
   (void)hipGetLastError();
   const size_t lds = sizeof(double) * size_t(m) * delta;
   const bool staged = lds <= kCompleteLds;
-  hipLaunchKernelGGL(completion_kernel, dim3(unsigned(R)), dim3(kSimThreads), staged ? lds : 0, stream, tau,
-                     failed, N, m, delta, holder, hpos, gamma, ell, staged ? 1 : 0, partial, original);
+  const int64_t blocks = R < 0xffffffffLL / kSimThreads ? R : 0xffffffffLL / kSimThreads;  // the launch limits
+  hipLaunchKernelGGL(completion_kernel, dim3(unsigned(blocks)), dim3(kSimThreads), staged ? lds : 0, stream, tau,
+                     failed, R, N, m, delta, holder, hpos, gamma, ell, staged ? 1 : 0, partial, original);
   return launch_status();
 }
 

@@ -222,3 +222,13 @@ def test_progress_and_completion_loads(delta):
         at = np.sort(cum[:, holder, hpos], axis=2)[:, :, ell - 1].max(axis=1)
         full = np.sort(cum[:, holder, delta - 1], axis=2)[:, :, ell - 1].max(axis=1)
         assert (host(part) == at).all() and (host(orig) == full).all()
+
+
+def test_completion_times_past_one_block_per_trial():
+    """More trials than the launch limits allow blocks of 256 threads."""
+    R, m = (1 << 24) + 5, 2
+    _, order, holder, hpos = gcx.gc_assign(gcx.GC_ASSIGN_CYCLIC, m, m, 0)
+    tau = torch.rand((R, m, 1), dtype=torch.float64, device="cuda")
+    part, orig = gcx.gc_completion_times(tau, dev(holder), dev(hpos), 1)
+    want = tau[:, :, 0].amax(1)
+    assert torch.equal(part, want) and torch.equal(orig, want)
