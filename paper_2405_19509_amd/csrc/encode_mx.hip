@@ -603,6 +603,12 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
   // 128 / 192 rows 2.4 / 2.1 / 2.05 ms).  With few K steps on rows that start anywhere 128 rows
   // and four positions per lane (0.62 ms against 0.65 with 256 rows, 0.68 with two positions).
   const bool small_odd = f32 && !a.nt && steps(delta) <= 2;
+  // The same on rows at 64 bytes with many patterns: at most 64 patterns per K step and window, so
+  // that a window takes several workers, and four positions per lane.  Windows of 256 patterns of one
+  // worker wrote 256-byte pieces m rows apart, below the worker groups' rate (ms, one worker / this /
+  // worker groups: m = 100, delta = 10, d = 2^20, ell = 1, 256 patterns 21.4 / 16.1 / 15.8, ell = 2, 512
+  // patterns 24.3 / 17.7 / 22.8; m = 200, delta = 20, d = 2^18, 512 patterns 27.6 / 19.2 / 22.9).
+  const bool many = f32 && a.nt && steps(delta) <= 2 && P > 64;
   int KS = 0;
   for (int cw = small_odd ? 128 : (f32 ? kMxMaxCW : 192);; cw -= 32) {
     // one pattern window where P allows, else balanced ones; then workers while there is
@@ -610,7 +616,7 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
     // K steps the most workers it holds, and of these the one with the least work per row: KS
     // products per row tile, and for each K step loads and splits that cost about as much as
     // 2.5 row tiles' products
-    a.PB = int(ceil_div(P, ceil_div(P, cw)));
+    a.PB = int(ceil_div(P, ceil_div(P, many ? std::min<int64_t>(cw, 64 * steps(delta)) : cw)));
     a.ntp = ceil_div(P, a.PB);
     const int64_t most = N <= kMxMapChunks ? std::min<int64_t>(cw / a.PB, m) : 1;
     double best = 0;
@@ -633,7 +639,7 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
     if (mx_lds(a, KS) <= kMxLds || cw == 32) break;  // 32 rows always fit
   }
   // positions per lane, as registers allow (fp32: 12 PW per K step, bf16 4 PW; 16 PW sums)
-  const int pw = f32 ? (KS <= 2 ? (small_odd ? 4 : 2) : (KS <= 5 ? 2 : 1)) : (KS <= 8 ? 4 : 2);
+  const int pw = f32 ? (KS <= 2 ? (small_odd || many ? 4 : 2) : (KS <= 5 ? 2 : 1)) : (KS <= 8 ? 4 : 2);
   const int threads = KS <= (f32 ? 2 : 3) ? 256 : 512;
   const int nw = threads / kWave;
   a.ntiles = ceil_div(a.L, int64_t(32) * pw);
