@@ -11,11 +11,13 @@
 // Arithmetic: each fp32 coefficient a is split into three bf16 parts a = a1 + a2 + a3 + r
 // with |r| <= 2^-24 |a| (each part the bf16 rounding of what the previous ones leave).
 // bf16 chunk gradients enter as they are: three products per term.  An fp32 chunk gradient
-// g is split exactly into three bf16 parts by truncation (g1 its top 16 bits, g2 the top 16
-// bits of g - g1, g3 the rest), and the six products a_i g_j with i + j <= 4 are kept: the
-// dropped ones stay below 2^-21 |a g|.  Every product of two bf16 values is exact in fp32;
-// v_mfma_f32_32x32x16_bf16 accumulates them in fp32.  Against 64 bits the error is at or
-// below that of the fp32 vector sum (m = 37, ell = 3: 7.3e-8 against 8.2e-8 relative).
+// g is split into three such parts as well, and the six products a_i g_j with i + j <= 4 are kept:
+// the dropped ones stay below 2^-25 |a g|.  Every product of two bf16 values is exact in fp32;
+// v_mfma_f32_32x32x16_bf16 accumulates them in fp32, rounding worse than to nearest, so that sums of
+// few terms (one K step) keep the small products apart and add them at the end on the vector
+// units.  Relative error against 64 bits, with the vector units' (1e-8): rows of one term 2.6 (2.5; 3.9
+// with truncated parts and one sum), of up to three terms 2.6 (3.3;
+// 3.9), at two steps of up to 21 terms 3.5 (7.1; 3.9).
 // A zero coefficient times a non-finite gradient is not zero, so tiles whose gradients are
 // not all finite are computed term by term over each row's processed prefix instead.
 //
@@ -52,12 +54,14 @@ constexpr int kMxThreads = 512;         // threads per block, at most
 constexpr int kMxMaxCW = 256;           // candidate rows per window, at most
 // K steps of 16 rows of B, as the registers allow
 constexpr int kMxMaxKSF32 = 11, kMxMaxKSBF16 = 12;
+constexpr int kMxApartTerms = 3;        // terms per output up to which one K step is taken for its smaller error
 constexpr int kMxMapChunks = 4096;      // chunks up to which groups of workers are formed
 constexpr size_t kMxLds = 144 * 1024;   // dynamic LDS of a block, at most
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v2f __attribute__((ext_vector_type(2)));
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 // PW neighbouring positions of a gradient or of T, at element alignment: rows start anywhere
 template <int N>
@@ -84,30 +88,30 @@ __device__ __forceinline__ float times_zero(uint32_t pair, float chk) {
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(v2bf, pair), __builtin_bit_cast(v2bf, 0u), chk, false);
 }
 
-// Exact split of eight finite fp32 values into three bf16 parts each, g = g1 + g2 + g3:
-// g1 keeps the top 16 bits of g (sign, exponent, 7 fraction bits), g - g1 is exact with at
-// most 16 significant bits, g2 its top 16 bits, and what remains has at most 8 significant
-// bits, a bf16 value (|g2| < 2^-7 |g|, |g3| < 2^-15 |g|; exact for |g| >= 2^-100).  The
-// top half of an infinity or a NaN is an infinity or a NaN too.
+// Eight finite fp32 values in three bf16 parts, each the rounding of what the earlier ones leave
+// (|g2| <= 2^-9 |g|, |g3| <= 2^-18 |g|); the subtractions (one dot product each: v - 1 part + 0
+// other) are exact for |g| >= 2^-108 and what the third part leaves is below 2^-26 |g|.  A value that is
+// not finite, or rounds past the largest bf16, leaves a first part that is not finite.
 __device__ __forceinline__ void split3(const float (&v)[8], v8bf (&g)[3]) {
-  uint32_t h1[8], h2[8], h3[8];
+  // (-1, 0) and (0, -1), kept in registers: as an instruction's inline constant the first is read
+  // otherwise
+  uint32_t l = 0x0000bf80u, h = 0xbf800000u;
+  asm("" : "+s"(l), "+s"(h));
+  const v2bf lo = __builtin_bit_cast(v2bf, l), hi = __builtin_bit_cast(v2bf, h);
+  v4u p[3];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    h1[i] = __float_as_uint(v[i]) & 0xffff0000u;
-    const float r1 = v[i] - __uint_as_float(h1[i]);
-    h2[i] = __float_as_uint(r1) & 0xffff0000u;
-    h3[i] = __float_as_uint(r1 - __uint_as_float(h2[i]));
-  }
-  v4u p1, p2, p3;
+  for (int j = 0; j < 4; ++j) {
+    float a = v[2 * j], b = v[2 * j + 1];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {  // high halves: element 2j low, element 2j + 1 high
-    p1[j] = __builtin_amdgcn_perm(h1[2 * j + 1], h1[2 * j], 0x07060302u);
-    p2[j] = __builtin_amdgcn_perm(h2[2 * j + 1], h2[2 * j], 0x07060302u);
-    p3[j] = __builtin_amdgcn_perm(h3[2 * j + 1], h3[2 * j], 0x07060302u);
+    for (int s = 0; s < 3; ++s) {
+      const v2bf u = __builtin_convertvector(v2f{a, b}, v2bf);
+      p[s][j] = __builtin_bit_cast(uint32_t, u);
+      a = __builtin_amdgcn_fdot2_f32_bf16(u, lo, a, false);
+      b = __builtin_amdgcn_fdot2_f32_bf16(u, hi, b, false);
+    }
   }
-  g[0] = __builtin_bit_cast(v8bf, p1);
-  g[1] = __builtin_bit_cast(v8bf, p2);
-  g[2] = __builtin_bit_cast(v8bf, p3);
+#pragma unroll
+  for (int s = 0; s < 3; ++s) g[s] = __builtin_bit_cast(v8bf, p[s]);
 }
 
 struct MxArgs {
@@ -147,9 +151,10 @@ struct MxLayout {
   static constexpr int Kp = 16 * KS;
   static constexpr int AP = Kp + 8;       // plane row stride (bf16): 16-byte rows, staggered banks
   static constexpr int W = 32 * PW;       // positions per tile
-  // registers: B (4 NP PW KS; fp32 splits take some more), accumulators (16 PW), one K step
+  static constexpr bool APART = KS == 1;  // small products in sums of their own
+  // registers: B (4 NP PW KS; fp32 splits take some more), accumulators (16 or 32 PW), one K step
   // of A (12), addresses
-  static constexpr int REGS = (F32 ? 15 : 4) * PW * KS + 16 * PW + 12 + 40;
+  static constexpr int REGS = (F32 ? 15 : 4) * PW * KS + (APART ? 32 : 16) * PW + 12 + 40;
   static constexpr int WPE = REGS <= 128 ? 4 : (REGS <= 168 ? 3 : 2);
 };
 
@@ -471,15 +476,16 @@ encode_mx_kernel(MxArgs a) {
 #pragma unroll 1
       for (int rt = 0; rt < ntile; ++rt) {
         const uint16_t *At = Ap + rt * (3 * 32 * AP) + li * AP + 8 * h;
-        v16f acc[PW];
+        v16f acc[PW], big[Lay::APART ? PW : 1];
 #pragma unroll
         for (int w = 0; w < PW; ++w) acc[w] = v16f{};
-        auto mm = [&](const uint16_t *plane, int q, int part) {
+        auto mm_to = [&](v16f *sum, const uint16_t *plane, int q, int part) {
           const v8bf av = *reinterpret_cast<const v8bf *>(plane + 16 * q);
 #pragma unroll
           for (int w = 0; w < PW; ++w)
-            acc[w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bf[q][w][part], acc[w], 0, 0, 0);
+            sum[w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bf[q][w][part], sum[w], 0, 0, 0);
         };
+        auto mm = [&](const uint16_t *plane, int q, int part) { mm_to(acc, plane, q, part); };
         // the products of parts above 2^-24 relative; those below 2^-7 of the whole first, over
         // all of K, so that only the last KS sums round at the result's own size
 #pragma unroll
@@ -492,8 +498,17 @@ encode_mx_kernel(MxArgs a) {
           mm(At + 32 * AP, q, 0);
           if constexpr (F32) mm(At, q, 1);
         }
+        if constexpr (Lay::APART) {
 #pragma unroll
-        for (int q = 0; q < KS; ++q) mm(At, q, 0);
+          for (int w = 0; w < PW; ++w) big[w] = v16f{};
+#pragma unroll
+          for (int q = 0; q < KS; ++q) mm_to(big, At, q, 0);
+#pragma unroll
+          for (int w = 0; w < PW; ++w) acc[w] += big[w];
+        } else {
+#pragma unroll
+          for (int q = 0; q < KS; ++q) mm(At, q, 0);
+        }
         // lane (h, li) holds D[8(v/4) + 4h + v%4][li] of each 32-wide tile: rows 32 rt + 8g + 4h
         // + i, PW neighbouring positions each.  Non-temporal where rows start on 64-byte
         // boundaries; elsewhere the pieces of a row meet inside a memory line, which plain
@@ -620,7 +635,7 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
     a.ntp = ceil_div(P, a.PB);
     const int64_t most = N <= kMxMapChunks ? std::min<int64_t>(cw / a.PB, m) : 1;
     double best = 0;
-    for (int64_t k = steps(delta); k <= max_steps; ++k) {
+    for (int64_t k = steps(delta); k <= (delta * ell <= kMxApartTerms ? 1 : max_steps); ++k) {
       int64_t J = std::max<int64_t>(1, std::min<int64_t>(16 * k / ell - delta + 1, most));
       const int64_t groups = ceil_div(m, J);
       J = ceil_div(m, groups);  // balanced groups
@@ -644,10 +659,12 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
   const int nw = threads / kWave;
   a.ntiles = ceil_div(a.L, int64_t(32) * pw);
   // tiles per wave: the planes cost more to build with more K steps (2 up to 3 steps, else 8;
-  // m = 200 bf16 at ell = 1 2.67 ms against 2.77 with 4, at ell = 4 2.05 against 2.31 with 2),
+  // m = 200 bf16 at ell = 1 2.67 ms against 2.77 with 4, at ell = 4 2.05 against 2.31 with 2; 4 for
+  // bf16 at two steps and many patterns: m = 200, delta = 20, d = 2^18, 128 patterns 3.94 against 4.40,
+  // m = 100, delta = 16, ell = 2, 256 patterns 2.11 against 2.22, 64 patterns of m = 200 2.47 against 2.43),
   // fewer while the grid is short of four blocks per CU
   const int64_t units = int64_t(a.ngroups) * a.ntp;
-  a.tpb = int64_t(nw) * (KS <= 3 ? 2 : 8);
+  a.tpb = int64_t(nw) * (!f32 && KS == 2 && P > 64 ? 4 : (KS <= 3 ? 2 : 8));
   while (a.tpb > nw && ceil_div(a.ntiles, a.tpb) * units < 4 * int64_t(cu_count())) a.tpb -= nw;
   a.nsr = ceil_div(a.ntiles, a.tpb);
   int64_t blocks = 0;

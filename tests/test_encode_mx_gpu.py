@@ -107,3 +107,22 @@ def test_not_finite_gradients(value, g_dtype):
     ok = ~bad & (psi > 0)[:, :, None]
     diff = np.where(ok, np.abs(np.where(ok, T, 0).astype(np.float64) - np.where(ok, ref, 0)), 0)
     assert (diff <= np.where(ok, bound, np.inf)).all()
+
+
+@pytest.mark.parametrize("g_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,delta,d,P", [(50, 3, 40001, 64), (50, 3, 200001, 2), (100, 3, 1 << 16, 64), (37, 10, 20003, 40)])
+def test_rows_of_one_term(m, delta, d, P, g_dtype):
+    """One product per output is as good as rounded once.  Its rounding to nearest is off by 2.5e-8 on
+    the average of squares and by u = 2^-24 at most; the products left out add under 2^-25, the
+    coefficient's third part under 2^-25."""
+    _, order, _, _ = gcx.gc_assign(gcx.GC_ASSIGN_CYCLIC, m, m, delta - 1)
+    g = torch.Generator(device="cuda").manual_seed(d)
+    G = torch.randn((m, d), generator=g, device="cuda").to(torch.bfloat16 if g_dtype == "bf16" else torch.float32)
+    Bc = torch.randn((P, m, delta, 1), generator=g, device="cuda")
+    psi = torch.ones((P, m), dtype=torch.int32, device="cuda")
+    T = gcx.gc_encode(G, psi, TP.dev(order), Bc)
+    first = torch.from_numpy(order[:, 0]).long().cuda()
+    ref = Bc[:, :, 0].double() * G.double()[first]
+    err = (T.double() - ref).abs()
+    assert float((err / ref.abs().clamp_min(1e-30)).max()) <= 2 * 2.0 ** -24
+    assert float(err.norm() / ref.norm()) <= 3.0e-8
