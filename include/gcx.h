@@ -198,11 +198,16 @@ int gc_decode_coeffs(const int32_t *psi, int64_t P, int32_t N, int32_t m, const 
  * 192 (bf16 G) a value of G that is not finite enters only the rows that have processed its
  * chunk; past that G must be finite, since a coefficient past a pattern's prefix or of a chunk
  * the worker does not hold may enter as zero (and zero times a non-finite value is not zero).
- * Accuracy per output, M = sum over its terms of |Bc||g| and u = 2^-24: where the sums run on
- * the matrix cores (every shape past the smallest), within u M plus the fp32 accumulation of 3
- * psi*ell products (bf16 G; coefficients split exactly into three bf16 parts), or within 8u M
- * plus that of 6 psi*ell products (fp32 G; G split exactly into three
- * bf16 parts as well), or gamma_{psi*ell} M (fp32 vector path).
+ * A coefficient that is not finite makes its row's values not finite, and no other row's.
+ * Accuracy per output, M = sum over its terms of |Bc||g| and u = 2^-24: sums run on the vector
+ * units (up to 8 terms on short rows, small calls, rows on 16-byte boundaries where every chunk's
+ * slice fits in LDS, up to 4 patterns of at most 24 terms), on the bf16 matrix cores (the rest up
+ * to 176 or 192 terms), or on the fp32 matrix cores or the vector units past that.  Everywhere
+ * within u M plus the fp32 accumulation of 3 psi*ell products (bf16 G) or within 8u M plus that
+ * of 6 psi*ell products (fp32 G); on the vector units within gamma_{psi*ell} M.  On the bf16
+ * matrix cores coefficients and fp32 gradients enter as three bf16 parts, rounded to nearest,
+ * which leave less than 2^-26 of a value of magnitude 2^-108 or more; smaller values enter with an
+ * absolute error of up to 2^-126.
  */
 int gc_encode(const void *G, int32_t g_dtype, int32_t N, int64_t d, const int32_t *psi,
               const int32_t *order, const float *Bc, int64_t P, int32_t m, int32_t delta,

@@ -83,6 +83,17 @@ __device__ __forceinline__ uint32_t bf16_rne(float v) {
   return (b + 0x7fffu + ((b >> 16) & 1u)) >> 16;
 }
 
+// A coefficient in three bf16 parts: b1 = bf16(v), b2 = bf16(v - b1), b3 = bf16(v - b1 - b2), all exact
+// steps.  What would round past the largest bf16 is cut to its top 16 bits instead; an infinity or a
+// NaN is in the first part alone.
+__device__ __forceinline__ void split_coef(float v, uint32_t (&b)[3]) {
+  const uint32_t bits = __float_as_uint(v), mag = bits & 0x7fffffffu;
+  b[0] = mag < 0x7f7f8000u ? bf16_rne(v) : (mag > 0x7f800000u ? 0x7fc0u : bits >> 16);
+  const float r1 = mag < 0x7f800000u ? v - __uint_as_float(b[0] << 16) : 0.f;
+  b[1] = bf16_rne(r1);
+  b[2] = bf16_rne(r1 - __uint_as_float(b[1] << 16));
+}
+
 // chk + 0 * (either bf16 half of pair): a NaN once a half is infinite or a NaN
 __device__ __forceinline__ float times_zero(uint32_t pair, float chk) {
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(v2bf, pair), __builtin_bit_cast(v2bf, 0u), chk, false);
@@ -350,8 +361,7 @@ encode_mx_kernel(MxArgs a) {
       lim[q] = rem < a.L ? rem : a.L;
     }
     __syncthreads();
-    // three bf16 planes per row tile: a1 = bf16(a), a2 = bf16(a - a1), a3 = bf16(a - a1 - a2),
-    // all exact steps; row kk at column 16 (kk / 16) + 8 (kk % 2) + (kk % 16) / 2
+    // three bf16 planes per row tile, one for each part of the coefficients; row kk at column 16 (kk / 16) + 8 (kk % 2) + (kk % 16) / 2
     for (int e = tid; e < nsend * a.delta; e += nth) {
       const int c = e / a.delta, t = e - c * a.delta;
       if (t >= cnp[c]) continue;
@@ -364,14 +374,10 @@ encode_mx_kernel(MxArgs a) {
       for (int k = 0; k < ell; ++k) {
         const int kk = s * ell + k;
         const int col = (kk & ~15) + 8 * (kk & 1) + ((kk & 15) >> 1);
-        const float v = src[k];
-        const uint32_t b1 = bf16_rne(v);
-        const float r1 = v - __uint_as_float(b1 << 16);
-        const uint32_t b2 = bf16_rne(r1);
-        const float r2 = r1 - __uint_as_float(b2 << 16);
-        tp[col] = uint16_t(b1);
-        tp[32 * AP + col] = uint16_t(b2);
-        tp[64 * AP + col] = uint16_t(bf16_rne(r2));
+        uint32_t part[3];
+        split_coef(src[k], part);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) tp[32 * i * AP + col] = uint16_t(part[i]);
       }
     }
     __syncthreads();

@@ -126,3 +126,60 @@ def test_rows_of_one_term(m, delta, d, P, g_dtype):
     err = (T.double() - ref).abs()
     assert float((err / ref.abs().clamp_min(1e-30)).max()) <= 2 * 2.0 ** -24
     assert float(err.norm() / ref.norm()) <= 3.0e-8
+
+
+@pytest.mark.parametrize("g_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,delta,ell,d", [(50, 3, 1, 5001), (40, 12, 3, 6003)])
+def test_coefficients_at_the_end_of_the_range(m, delta, ell, d, g_dtype):
+    """Coefficients that round past the largest bf16 times small gradients give the finite sums of 64
+    bits; a coefficient that is not finite makes its row's values not finite, and no other row's."""
+    P = 40
+    O, order, G, psi = problem(m, delta, d, P, "f32", seed=4)
+    psi = np.full_like(psi, delta)
+    G *= np.float32(2.0 ** -100)
+    if g_dtype == "bf16":
+        G = gen.f32_to_bf16_bits(G)
+    rng = np.random.default_rng(5)
+    Bc = rng.standard_normal((P, m, delta, ell)).astype(np.float32) * np.float32(2.0 ** 120)
+    Bc[3, 7, 1, 0] = np.float32(3.4e38)
+    Bc[P - 1, m - 1, delta - 1, ell - 1] = -np.finfo(np.float32).max
+    Bc[5, 2, 0, 0] = np.float32(np.inf)
+    Bc[6, 2, delta - 1, ell - 1] = np.array(0x7fffffff, np.uint32).view(np.float32)
+    Bc[6, 3, delta - 1, 0] = np.array(0xffffffff, np.uint32).view(np.float32)
+    Gt = TP.dev(G.view(np.int16)).view(torch.bfloat16) if g_dtype == "bf16" else TP.dev(G)
+    T = TP.host(gcx.gc_encode(Gt, TP.dev(psi), TP.dev(order), TP.dev(Bc)))
+    bad = np.zeros((P, m), dtype=bool)
+    bad[5, 2] = bad[6, 2] = bad[6, 3] = True
+    assert not np.isfinite(T[bad]).any() and np.isnan(T[6, 2:4]).all()
+    fine = np.where(np.isfinite(Bc), Bc, 0).astype(np.float64)
+    ref, M, nterm = R_.encode_ref(fine, psi, order, OP.widen(G, g_dtype).astype(np.float64), ell)
+    bound = R_.encode_bound(nterm, M, g_dtype)
+    assert (np.abs(T[~bad].astype(np.float64) - ref[~bad]) <= bound[~bad]).all()
+
+
+@pytest.mark.parametrize("g_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("scale", [104, 118])
+def test_small_magnitudes(scale, g_dtype):
+    """Coefficients, and fp32 gradients, far below 1: parts in full from 2^-108 on, an absolute error of
+    2^-126 per value below (magnitudes here mostly from 2^-scale * 2^-4 on)."""
+    m, delta, ell, d, P = 50, 16, 2, 4095, 8
+    for small_g in (False, True):
+        O, order, G, psi = problem(m, delta, d, P, "f32", seed=6)
+        rng = np.random.default_rng(7)
+        Bc = rng.standard_normal((P, m, delta, ell)).astype(np.float32)
+        if small_g:
+            G *= np.float32(2.0 ** -scale)
+        else:
+            Bc *= np.float32(2.0 ** -scale)
+        if g_dtype == "bf16":
+            G = gen.f32_to_bf16_bits(G)
+        Gt = TP.dev(G.view(np.int16)).view(torch.bfloat16) if g_dtype == "bf16" else TP.dev(G)
+        T = TP.host(gcx.gc_encode(Gt, TP.dev(psi), TP.dev(order), TP.dev(Bc)))
+        wide = OP.widen(G, g_dtype).astype(np.float64)
+        ref, M, nterm = R_.encode_ref(Bc.astype(np.float64), psi, order, wide, ell)
+        # what the absolute errors of the small operand make of the other one's magnitudes
+        other = R_.encode_ref(np.sign(Bc).astype(np.float64) if not small_g else Bc.astype(np.float64), psi, order,
+                              np.sign(wide) if small_g else wide, ell)[1]
+        sent = psi > 0
+        bound = R_.encode_bound(nterm, M, g_dtype) + 2.0 ** -126 * other
+        assert (np.abs(T[sent].astype(np.float64) - ref[sent]) <= bound[sent]).all()
