@@ -12,6 +12,8 @@
 // bf16 values are exact in fp32 and v_mfma_f32_32x32x16_bf16 accumulates them in fp32, the
 // products v1 w1 in one accumulator and the five small ones in another, so only one addition
 // per 16 terms rounds at the sum's own size (fp32 matrix instructions: one per 2 terms).
+// The matrix cores round worse than to nearest, so long sums drift: calls whose sums were short before
+// (see gc_chunk_grads) add them up in segments, of 512 columns and of 128 rows or more.
 // A NaN in a tile's sums (an infinity's or a NaN's parts, or values near the largest float
 // that round up) makes its wave compute the tile again with the fp32 matrix instructions, which
 // treat infinities as the vector units do.
@@ -58,6 +60,7 @@ constexpr int kZRows = 32 * (kZThreads / kWave);  // sample rows per block
 constexpr int kMThreads = 256;                    // utx_kernel
 constexpr int kMWaves = kMThreads / kWave;
 constexpr int kZK = 32;               // k per stage of zw_kernel
+constexpr int kZSeg = 16;             // stages per segment
 
 __device__ __forceinline__ v16f mfma16(v8bf a, v8bf b, v16f c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -112,12 +115,16 @@ __device__ __forceinline__ void products(const v8bf (&a)[3], const v8bf (&b)[3],
   big = mfma16(a[0], b[0], big);
 }
 
+// waves per SIMD of zw_kernel, as its registers allow
+constexpr int z_waves(int qt, bool seg) { return qt == 1 ? (seg ? 3 : 4) : (qt == 2 && !seg ? 3 : 2); }
+
 // Zp[s][r][q] = sum_{k in split s} X[r][k] * W[q][k] for the rows r of all chunks.
 //   A (32 rows x 16 k): lane (h, li) holds row li at k = 4h .. 4h + 3 and 8 + 4h .. 8 + 4h + 3
 //   of each 16; B (W) the same k of point li, its parts in LDS as the lanes read them:
 //   Ws[buffer][16-step][part][point tile][lane] of 16 bytes.
-template <int QT>  // point tiles of 32 per block
-__global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(QT == 1 ? 4 : (QT == 2 ? 3 : 2)))) void zw_kernel(const float *__restrict__ X, const float *__restrict__ W,
+//   SEG: the split in segments of kZSeg stages, each summed by itself and added to Zp.
+template <int QT, bool SEG>  // point tiles of 32 per block
+__global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(z_waves(QT, SEG)))) void zw_kernel(const float *__restrict__ X, const float *__restrict__ W,
                                                           int64_t R, int64_t d, int b, int splits, int64_t kper,
                                                           int qblocks, float *__restrict__ Zp) {
   __shared__ __align__(16) uint2 Ws[2][2][3][QT][kWave][2];
@@ -127,8 +134,8 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(QT ==
   const int s = int(bid % splits);
   const int64_t r0 = bid / splits * kZRows;
   const int t = threadIdx.x, lane = t % kWave, wave = t / kWave, h = lane >> 5, li = lane & 31;
-  const int64_t k0 = int64_t(s) * kper;
-  const int64_t k1 = k0 + kper < d ? k0 + kper : d;
+  const int64_t ks0 = int64_t(s) * kper;
+  const int64_t ks1 = ks0 + kper < d ? ks0 + kper : d;
   const int64_t row = r0 + 32 * wave + li;
   const float *xr = X + (row < R ? row : R - 1) * d;  // rows past the last repeat it, not stored
 
@@ -165,8 +172,6 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(QT ==
   };
 
   v16f big[QT], small[QT];
-#pragma unroll
-  for (int i = 0; i < QT; ++i) big[i] = small[i] = v16f{};
   // the products of the stage in rx, its W in LDS buffer buf; next(): what to issue once rx is free
   auto stage = [&](int buf, auto next) {
     v8bf a[2][3];
@@ -188,88 +193,106 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(QT ==
         products(a[m], w, big[i], small[i]);
       }
   };
-  const int64_t nst = (k1 - k0) / kZK;  // whole stages
-  if (nst > 0) {
-    wload(k0);
-    xload(k0);
-    wstore(0);
-    if (nst > 1) wload(k0 + kZK);
-    __syncthreads();
-  }
-  // stage st: its X in rx, its W in LDS buffer st & 1, the next W in rw
-  for (int64_t st = 0; st < nst; ++st) {
-    stage(int(st & 1), [&] {
-      if (st + 1 < nst) xload(k0 + (st + 1) * kZK);
-    });
-    if (st + 1 < nst) {
-      wstore(int(st & 1) ^ 1);
-      if (st + 2 < nst) wload(k0 + (st + 2) * kZK);
+  // the columns k0 .. k1 - 1 of the split, whose first are ks0, ..
+  auto segment = [&](int64_t k0, int64_t k1) {
+#pragma unroll
+    for (int i = 0; i < QT; ++i) big[i] = small[i] = v16f{};
+    const int64_t nst = (k1 - k0) / kZK;  // whole stages
+    if (nst > 0) {
+      wload(k0);
+      xload(k0);
+      wstore(0);
+      if (nst > 1) wload(k0 + kZK);
+      __syncthreads();
     }
-    __syncthreads();
-  }
-  if (const int left = int(k1 - k0 - nst * kZK); left > 0) {  // the last k: zeros past them
-    const int64_t kb = k0 + nst * kZK;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int k = 8 * (e / 4) + 4 * h + e % 4;
-      const float v = xr[kb + (k < left ? k : 0)];
-      rx[e] = k < left ? v : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < QT; ++i) {
-      const int q = q0 + t / 8 + 32 * i;
-      const float *src = W + int64_t(q < b ? q : b - 1) * d + kb;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = 4 * (t % 8) + e;
-        const float v = src[k < left ? k : 0];
-        rw[i][e] = k < left ? v : 0.f;
+    // stage st: its X in rx, its W in LDS buffer st & 1, the next W in rw
+    for (int64_t st = 0; st < nst; ++st) {
+      stage(int(st & 1), [&] {
+        if (st + 1 < nst) xload(k0 + (st + 1) * kZK);
+      });
+      if (st + 1 < nst) {
+        wstore(int(st & 1) ^ 1);
+        if (st + 2 < nst) wload(k0 + (st + 2) * kZK);
       }
+      __syncthreads();
     }
-    wstore(0);
-    __syncthreads();
-    stage(0, [] {});
-  }
+    if (const int left = int(k1 - k0 - nst * kZK); left > 0) {  // the last k: zeros past them
+      const int64_t kb = k0 + nst * kZK;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int k = 8 * (e / 4) + 4 * h + e % 4;
+        const float v = xr[kb + (k < left ? k : 0)];
+        rx[e] = k < left ? v : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < QT; ++i) {
+        const int q = q0 + t / 8 + 32 * i;
+        const float *src = W + int64_t(q < b ? q : b - 1) * d + kb;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int k = 4 * (t % 8) + e;
+          const float v = src[k < left ? k : 0];
+          rw[i][e] = k < left ? v : 0.f;
+        }
+      }
+      wstore(0);
+      __syncthreads();
+      stage(0, [] {});
+    }
 
-  bool bad = false;
+    bool bad = false;
 #pragma unroll
-  for (int i = 0; i < QT; ++i)
+    for (int i = 0; i < QT; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      big[i][v] += small[i][v];
-      bad = bad || big[i][v] != big[i][v];
-    }
-  if (__any(bad)) {  // the tile on the fp32 matrix instructions
+      for (int v = 0; v < 16; ++v) {
+        big[i][v] += small[i][v];
+        bad = bad || big[i][v] != big[i][v];
+      }
+    if (__any(bad)) {  // the tile on the fp32 matrix instructions
 #pragma unroll
-    for (int i = 0; i < QT; ++i) {
-      const int q = q0 + 32 * i + li;
-      const float *wr = W + int64_t(q < b ? q : b - 1) * d;
-      big[i] = v16f{};
-      for (int64_t k = k0 + h; k - h < k1; k += 2) {
-        const float x = xr[k < k1 ? k : k1 - 1], w = wr[k < k1 ? k : k1 - 1];
-        big[i] = mfma2(k < k1 ? x : 0.f, k < k1 ? w : 0.f, big[i]);
+      for (int i = 0; i < QT; ++i) {
+        const int q = q0 + 32 * i + li;
+        const float *wr = W + int64_t(q < b ? q : b - 1) * d;
+        big[i] = v16f{};
+        for (int64_t k = k0 + h; k - h < k1; k += 2) {
+          const float x = xr[k < k1 ? k : k1 - 1], w = wr[k < k1 ? k : k1 - 1];
+          big[i] = mfma2(k < k1 ? x : 0.f, k < k1 ? w : 0.f, big[i]);
+        }
       }
     }
+    float *Zs = Zp + (int64_t(s) * R + r0 + 32 * wave) * b + q0;
+#pragma unroll
+    for (int i = 0; i < QT; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int r = 8 * (v >> 2) + 4 * h + (v & 3);
+        if (r0 + 32 * wave + r < R && q0 + 32 * i + li < b) {
+          float *dst = Zs + int64_t(r) * b + 32 * i + li;
+          *dst = k0 == ks0 ? big[i][v] : *dst + big[i][v];
+        }
+      }
+  };
+  if constexpr (SEG) {
+    for (int64_t k0 = ks0; k0 < ks1; k0 += kZSeg * kZK) segment(k0, k0 + kZSeg * kZK < ks1 ? k0 + kZSeg * kZK : ks1);
+  } else {
+    segment(ks0, ks1);
   }
-  float *Zs = Zp + (int64_t(s) * R + r0 + 32 * wave) * b + q0;
-#pragma unroll
-  for (int i = 0; i < QT; ++i)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int r = 8 * (v >> 2) + 4 * h + (v & 3);
-      if (r0 + 32 * wave + r < R && q0 + 32 * i + li < b) Zs[int64_t(r) * b + 32 * i + li] = big[i][v];
-    }
 }
 
-// U[r][q] = loss'(sum_s Zp[s][r][q]) - y[r] for the rows r of all chunks, the splits summed in
-// order; in place where there is one.
+// U[r][q] = loss'(sum_s Zp[s][r][q]) - y[r] for the rows r of all chunks, the splits summed in four
+// runs (one long run of 128 splits was off by 1.3e-7 in all, four by 1.2e-7); in place where there is one.
 __global__ __launch_bounds__(256) void resid_kernel(const float *Zp, const float *__restrict__ y, int64_t total,
                                                     int b, int splits, int loss, float *U) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (e >= total) return;
-  float z = 0.f;
-#pragma unroll 8
-  for (int s = 0; s < splits; ++s) z += Zp[int64_t(s) * total + e];
+  float zs[4] = {0.f, 0.f, 0.f, 0.f};
+  int s = 0;
+#pragma unroll 2
+  for (; s + 4 <= splits; s += 4)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) zs[u] += Zp[int64_t(s + u) * total + e];
+  for (; s < splits; ++s) zs[0] += Zp[int64_t(s) * total + e];
+  const float z = (zs[0] + zs[1]) + (zs[2] + zs[3]);
   const float yv = y[e / b];
   U[e] = loss == GC_LOSS_LOGISTIC ? 1.0f / (1.0f + expf(-z)) - yv : z - yv;
 }
@@ -277,9 +300,10 @@ __global__ __launch_bounds__(256) void resid_kernel(const float *Zp, const float
 // G[q][i][x] = sum_r U[i][r][q] * X[i][r][x] for QT point tiles and 4 x 32 PW positions per block.
 //   B (16 rows x 32 positions): lane (h, li) holds rows h, h + 2, .. h + 14 of each 16 at positions
 //   PW li .. + PW - 1, PW separate 32-wide tiles
-template <int QT, int PW>
+//   SEG: the rows in segments of kseg steps of 16, each summed by itself and added to G
+template <int QT, int PW, bool SEG>
 __global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const float *__restrict__ U, const float *__restrict__ X,
-                                                           int N, int n, int64_t d, int b, int ksteps, int qblocks,
+                                                           int N, int n, int64_t d, int b, int kseg, int qblocks,
                                                             int64_t tiles, float *__restrict__ G) {
   using VT = typename Floats<PW>::T;
   __shared__ __align__(16) uint32_t Us[2][QT * 3 * kWave][4];  // U's parts of a stage as the lanes read them
@@ -361,20 +385,10 @@ __global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const float *__restri
   };
 
   v16f big[QT][PW], small[QT][PW];
-#pragma unroll
-  for (int q = 0; q < QT; ++q)
-#pragma unroll
-    for (int w = 0; w < PW; ++w) big[q][w] = small[q][w] = v16f{};
   using Zero = std::integral_constant<int, 0>;
   using One = std::integral_constant<int, 1>;
-  uload(0);
-  xload(Zero{}, 0);
-  if (ksteps > 1) xload(One{}, 1);
-  ustore(0);
-  if (ksteps > 1) uload(1);
-  __syncthreads();
   // stage ks: its X in register set ks & 1, its U in LDS buffer ks & 1, the next U in ru
-  auto stage = [&](int ks, auto setc) {
+  auto stage = [&](int ks, int ksteps, auto setc) {
     constexpr int SET = decltype(setc)::value;
     v8bf xs[PW][3];
 #pragma unroll
@@ -394,58 +408,79 @@ __global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const float *__restri
     }
     __syncthreads();
   };
-  for (int ks = 0; ks < ksteps; ks += 2) {
-    stage(ks, Zero{});
-    if (ks + 1 < ksteps) stage(ks + 1, One{});
-  }
+  // the steps ks0 .. ks1 - 1 of 16 rows, ks0 even
+  auto segment = [&](int ks0, int ks1) {
+#pragma unroll
+    for (int q = 0; q < QT; ++q)
+#pragma unroll
+      for (int w = 0; w < PW; ++w) big[q][w] = small[q][w] = v16f{};
+    uload(ks0);
+    xload(Zero{}, ks0);
+    if (ks0 + 1 < ks1) xload(One{}, ks0 + 1);
+    ustore(0);
+    if (ks0 + 1 < ks1) uload(ks0 + 1);
+    __syncthreads();
+    for (int ks = ks0; ks < ks1; ks += 2) {
+      stage(ks, ks1, Zero{});
+      if (ks + 1 < ks1) stage(ks + 1, ks1, One{});
+    }
 
-  bool bad = false;
+    bool bad = false;
 #pragma unroll
-  for (int q = 0; q < QT; ++q)
+    for (int q = 0; q < QT; ++q)
 #pragma unroll
-    for (int w = 0; w < PW; ++w)
+      for (int w = 0; w < PW; ++w)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        big[q][w][v] += small[q][w][v];
-        bad = bad || big[q][w][v] != big[q][w][v];
-      }
-  if (__any(bad)) {  // the tile on the fp32 matrix instructions
+        for (int v = 0; v < 16; ++v) {
+          big[q][w][v] += small[q][w][v];
+          bad = bad || big[q][w][v] != big[q][w][v];
+        }
+    if (__any(bad)) {  // the tile on the fp32 matrix instructions
 #pragma unroll
-    for (int q = 0; q < QT; ++q) {
+      for (int q = 0; q < QT; ++q) {
 #pragma unroll
-      for (int w = 0; w < PW; ++w) big[q][w] = v16f{};
-      const int qq = (qb * QT + q) * 32 + li;
-      for (int r = h; r - h < n; r += 2) {
-        const bool in = r < n;
-        const float uv = Ui[int64_t(in ? r : n - 1) * b + (qq < b ? qq : b - 1)];
-        const float u = in && qq < b ? uv : 0.f;
-        const float *src = Xi + int64_t(in ? r : n - 1) * d;
+        for (int w = 0; w < PW; ++w) big[q][w] = v16f{};
+        const int qq = (qb * QT + q) * 32 + li;
+        const int r1 = SEG && 16 * ks1 < n ? 16 * ks1 : n;
+        for (int r = 16 * ks0 + h; r - h < r1; r += 2) {
+          const bool in = r < r1;
+          const float uv = Ui[int64_t(in ? r : n - 1) * b + (qq < b ? qq : b - 1)];
+          const float u = in && qq < b ? uv : 0.f;
+          const float *src = Xi + int64_t(in ? r : n - 1) * d;
 #pragma unroll
-        for (int w = 0; w < PW; ++w) {
-          const float v = src[x + w < d ? x + w : d - 1];
-          big[q][w] = mfma2(u, in ? v : 0.f, big[q][w]);
+          for (int w = 0; w < PW; ++w) {
+            const float v = src[x + w < d ? x + w : d - 1];
+            big[q][w] = mfma2(u, in ? v : 0.f, big[q][w]);
+          }
         }
       }
     }
-  }
 #pragma unroll
-  for (int q = 0; q < QT; ++q)
+    for (int q = 0; q < QT; ++q)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int qq = (qb * QT + q) * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-      if (qq >= b) continue;
-      float *dst = G + (int64_t(qq) * N + i) * d + x;
-      if (inside) {
-        VT o;
+      for (int v = 0; v < 16; ++v) {
+        const int qq = (qb * QT + q) * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+        if (qq >= b) continue;
+        float *dst = G + (int64_t(qq) * N + i) * d + x;
+        if (inside) {
+          VT o;
 #pragma unroll
-        for (int w = 0; w < PW; ++w) o[w] = big[q][w][v];
-        *reinterpret_cast<VT *>(dst) = o;
-      } else {
+          for (int w = 0; w < PW; ++w) o[w] = big[q][w][v];
+          if (ks0 > 0) o += *reinterpret_cast<const VT *>(dst);
+          *reinterpret_cast<VT *>(dst) = o;
+        } else {
 #pragma unroll
-        for (int w = 0; w < PW; ++w)
-          if (x + w < d) dst[w] = big[q][w][v];
+          for (int w = 0; w < PW; ++w)
+            if (x + w < d) dst[w] = ks0 > 0 ? dst[w] + big[q][w][v] : big[q][w][v];
+        }
       }
-    }
+  };
+  const int ksteps = (n + 15) / 16;  // n <= 2^30
+  if constexpr (SEG) {
+    for (int ks = 0; ks < ksteps; ks += kseg) segment(ks, ks + kseg < ksteps ? ks + kseg : ksteps);
+  } else {
+    segment(0, ksteps);
+  }
 }
 
 // Launch plan shared by the workspace-size query and the launch.
@@ -454,17 +489,17 @@ struct MfmaPlan {
   int zqblocks, uqblocks;
   int splits;
   int64_t kper, rblocks;
-  int ksteps, qtiles;         // steps of 16 rows, tiles of 32 points
+  int useg, qtiles;           // steps of 16 rows per segment, tiles of 32 points
   int64_t blocks1, tiles, blocks2;
 };
 
-MfmaPlan mfma_plan(int N, int n, int64_t d, int b) {
+MfmaPlan mfma_plan(int N, int n, int64_t d, int b, bool seg) {
   MfmaPlan pl{};
   pl.qtiles = int(ceil_div(b, 32));
   const int64_t R = int64_t(N) * n;
   const int64_t stages = ceil_div(d, kZK);
   pl.rblocks = ceil_div(R, kZRows);
-  pl.zqt = pl.qtiles <= 2 ? pl.qtiles : 4;
+  pl.zqt = pl.qtiles <= 2 ? pl.qtiles : (seg ? 2 : 4);
   // fewer point tiles per block where a few blocks are all there is
   while (pl.zqt > 1 && pl.rblocks * ceil_div(pl.qtiles, pl.zqt) * ceil_div(stages, 4) < 256) pl.zqt /= 2;
   pl.upw = 2;
@@ -472,12 +507,12 @@ MfmaPlan mfma_plan(int N, int n, int64_t d, int b) {
   pl.uqt = pl.qtiles == 1 || pl.tiles * N * ceil_div(pl.qtiles, 2) < 256 ? 1 : 2;
   pl.zqblocks = int(ceil_div(pl.qtiles, pl.zqt));
   pl.uqblocks = int(ceil_div(pl.qtiles, pl.uqt));
-  // K = d split so that the blocks fill whole rounds of the resident ones (four, three or two
-  // per CU by point tiles, on 256 CUs); a block costs about 8 stages beyond its own (its prologue,
+  // K = d split so that the blocks fill whole rounds of the resident ones (two to four per CU
+  // by point tiles, on 256 CUs); a block costs about 8 stages beyond its own (its prologue,
   // its Z partials written and summed again), and the sums about one per split.  At most 64
   // stages per block: 128 additions at a partial's own size (n = 512, d = 16384, 4 points: the
   // gradients' error 1.4e-7, with 103 stages 1.7e-7, on the vector units 1.6e-7).
-  const int64_t resident = 256 * (pl.zqt == 1 ? 4 : (pl.zqt == 2 ? 3 : 2));
+  const int64_t resident = 256 * z_waves(pl.zqt, seg);
   constexpr int64_t kExtra = 8, kMaxStages = 64;
   const int64_t tiles = pl.rblocks * pl.zqblocks;
   // partials of more than one split go to G, which is written after they have been read
@@ -495,7 +530,8 @@ MfmaPlan mfma_plan(int N, int n, int64_t d, int b) {
     }
   }
   pl.blocks1 = tiles * pl.splits;
-  pl.ksteps = int(ceil_div(n, 16));
+  pl.useg = 8;  // about as many segments as two steps of one
+  while (2 * int64_t(pl.useg) * pl.useg < ceil_div(n, 16)) pl.useg *= 2;
   pl.blocks2 = ceil_div(pl.tiles * N, 8) * 8 * pl.uqblocks;
   return pl;
 }
@@ -505,10 +541,10 @@ MfmaPlan mfma_plan(int N, int n, int64_t d, int b) {
 // Two passes over X whatever b is, against one (fused) or two per point: from 4 or 2 points on,
 // but for small calls, where its third launch costs more than the passes saved (X of 111 x 1001
 // at 20 points 13 us against 19, of 256 x 4096 at 4 points 36 against 23).
-bool mfma_eligible(int N, int n, int64_t d, int b, bool fused) {
-  if (b < (fused ? 4 : 2) || d > int64_t(1) << 28) return false;
+bool mfma_eligible(int N, int n, int64_t d, int b, bool fused, bool seg) {
+  if (b < (fused ? 4 : 2) || d > int64_t(1) << 28 || n > 1 << 30) return false;
   if (double(N) * double(n) * double(d) * double(b) < 3e6) return false;
-  const MfmaPlan pl = mfma_plan(N, n, d, b);
+  const MfmaPlan pl = mfma_plan(N, n, d, b, seg);
   // few points keep the vector units where more than 64 stages per block would cost precision
   if (b < 16 && pl.kper > 64 * kZK) return false;
   return grid_ok(pl.blocks1, kZThreads) && grid_ok(pl.blocks2, kMThreads) &&
@@ -517,24 +553,27 @@ bool mfma_eligible(int N, int n, int64_t d, int b, bool fused) {
 
 // workspace: the residuals [N n][b]
 void launch_mfma_grads(const float *X, const float *y, const float *W, int N, int n, int64_t d, int b,
-                       int loss, float *G, void *workspace, hipStream_t st) {
-  const MfmaPlan pl = mfma_plan(N, n, d, b);
+                       int loss, bool seg, float *G, void *workspace, hipStream_t st) {
+  const MfmaPlan pl = mfma_plan(N, n, d, b, seg);
   const int64_t R = int64_t(N) * n;
   float *U = static_cast<float *>(workspace);
   float *Zp = pl.splits > 1 ? G : U;
   const int64_t total = R * b;
-#define GC_ZW(QT)                                                                                         \
-  hipLaunchKernelGGL(zw_kernel<QT>, dim3(unsigned(pl.blocks1)), dim3(kZThreads), 0, st, X, W, R, d, b,    \
-                     pl.splits, pl.kper, pl.zqblocks, Zp)
-  if (pl.zqt == 1) GC_ZW(1);
-  else if (pl.zqt == 2) GC_ZW(2);
-  else GC_ZW(4);
+#define GC_ZW(QT, SEG)                                                                                    \
+  hipLaunchKernelGGL((zw_kernel<QT, SEG>), dim3(unsigned(pl.blocks1)), dim3(kZThreads), 0, st, X, W, R,   \
+                     d, b, pl.splits, pl.kper, pl.zqblocks, Zp)
+  if (pl.zqt == 1 && seg) GC_ZW(1, true);
+  else if (seg) GC_ZW(2, true);
+  else if (pl.zqt == 1) GC_ZW(1, false);
+  else if (pl.zqt == 2) GC_ZW(2, false);
+  else GC_ZW(4, false);
 #undef GC_ZW
   hipLaunchKernelGGL(resid_kernel, dim3(unsigned(ceil_div(total, 256))), dim3(256), 0, st, Zp, y, total, b,
                      pl.splits, loss, U);
 #define GC_UTX(QT, PW)                                                                                     \
-  hipLaunchKernelGGL((utx_kernel<QT, PW>), dim3(unsigned(pl.blocks2)), dim3(kMThreads), 0, st, U, X, N,    \
-                     n, d, b, pl.ksteps, pl.uqblocks, pl.tiles, G)
+  hipLaunchKernelGGL((seg ? utx_kernel<QT, PW, true> : utx_kernel<QT, PW, false>),                        \
+                     dim3(unsigned(pl.blocks2)), dim3(kMThreads), 0, st, U, X, N, n, d, b, pl.useg,        \
+                     pl.uqblocks, pl.tiles, G)
   if (pl.uqt == 1) GC_UTX(1, 2);
   else GC_UTX(2, 2);
 #undef GC_UTX
