@@ -540,9 +540,13 @@ MfmaPlan mfma_plan(int N, int n, int64_t d, int b, bool seg) {
 
 // Two passes over X whatever b is, against one (fused) or two per point: from 4 or 2 points on,
 // but for small calls, where its third launch costs more than the passes saved (X of 111 x 1001
-// at 20 points 13 us against 19, of 256 x 4096 at 4 points 36 against 23).
+// at 20 points 13 us against 19, of 256 x 4096 at 4 points 36 against 23), and for four points of
+// short rows, whose four passes are as fast (us, fused against matrix cores at 4 points: X of 20 x 512 x
+// 1024 51 / 62, 16 x 2048 x 4096 226 / 321, 8 x 8192 x 2048 344 / 749, 20 x 16 x 16384 42 / 45; but 20 x
+// 64 x 4096 31 / 28, 20 x 512 x 8192 224 / 177; at 5 points 20 x 512 x 1024 64 / 61).
 bool mfma_eligible(int N, int n, int64_t d, int b, bool fused, bool seg) {
   if (b < (fused ? 4 : 2) || d > int64_t(1) << 28 || n > 1 << 30) return false;
+  if (fused && b == 4 && (n < 32 || (n > 128 && d < 8192))) return false;
   if (double(N) * double(n) * double(d) * double(b) < 3e6) return false;
   const MfmaPlan pl = mfma_plan(N, n, d, b, seg);
   // few points keep the vector units where more than 64 stages per block would cost precision

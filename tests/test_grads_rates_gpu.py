@@ -1,0 +1,30 @@
+"""The time of chunk gradients at several points against that of the same X at one point, at sizes
+where the plan decides between a good and a bad use of the chip.  Bars: about midway between the
+two ratios measured."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2405_19509_amd import gcx  # noqa: E402
+from test_encode_rates_gpu import fastest  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def points_over_one(N, n, d, b):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randn((N, n, d), generator=g, device="cuda") * d ** -0.5
+    y = (torch.rand((N, n), generator=g, device="cuda") < 0.5).float()
+    W = torch.randn((b, d), generator=g, device="cuda")
+
+    def call(W):
+        G = torch.empty((N, d) if W.dim() == 1 else (W.shape[0], N, d), device="cuda")
+        ws = torch.empty(gcx.gc_chunk_grads_workspace_size(N, n, d, W.shape[0] if W.dim() > 1 else 1),
+                         dtype=torch.uint8, device="cuda")
+        return fastest(lambda: gcx.gc_chunk_grads(X, y, W, gcx.GC_LOSS_LINEAR, G=G, workspace=ws))
+    return call(W) / call(W[0].contiguous())
+
+
+def test_four_points_of_short_rows():
+    """Four passes of the kernel for one point (2.0) against the matrix cores in a long chain (3.9)."""
+    assert points_over_one(8, 8192, 2048, 4) < 3
