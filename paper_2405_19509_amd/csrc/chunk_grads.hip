@@ -34,9 +34,9 @@
 namespace gcx {
 
 // multi-point path on the matrix cores (chunk_grads_mfma.hip)
-bool mfma_eligible(int N, int n, int64_t d, int b, bool fused, bool seg);
+bool mfma_eligible(int N, int n, int64_t d, int b, bool fused, bool seg, int64_t room);
 void launch_mfma_grads(const float *X, const float *y, const float *W, int N, int n, int64_t d, int b,
-                      int loss, bool seg, float *G, void *workspace, hipStream_t st);
+                      int loss, bool seg, int64_t room, float *G, void *workspace, hipStream_t st);
 
 namespace {
 
@@ -388,8 +388,11 @@ extern "C" int gc_chunk_grads(const float *X, const float *y, const float *W, in
   // 16384, 4 points: fused 1.7e-7 in 0.46 ms, matrix cores 2.1e-7 in 0.23, in segments 1.5e-7 in
   // 0.27; 20 x 8192 x 512: 1.3e-7, 4.9e-7, 1.0e-7).  Whole quads from 16 points on had longer ones.
   const bool seg = fused_ok(d) && (b < 16 || b % 4 != 0);
-  if (enough && mfma_eligible(N, n, d, b, fused, seg)) {
-    launch_mfma_grads(X, y, W, N, n, d, b, loss, seg, G, workspace, stream);
+  // partial sums of the first product that a workspace of the size asked for has room for beside the
+  // residuals
+  const int64_t room = int64_t(gc_chunk_grads_workspace_size(N, n, d, b) / (sizeof(float) * size_t(rows))) - 1;
+  if (enough && mfma_eligible(N, n, d, b, fused, seg, room)) {
+    launch_mfma_grads(X, y, W, N, n, d, b, loss, seg, room, G, workspace, stream);
     return launch_status();
   }
   if (fused) {

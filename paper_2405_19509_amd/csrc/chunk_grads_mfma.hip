@@ -51,6 +51,8 @@ typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
 template <int N>
 struct Floats;
 template <>
+struct Floats<1> { typedef float T __attribute__((ext_vector_type(1), aligned(4))); };
+template <>
 struct Floats<2> { typedef float T __attribute__((ext_vector_type(2), aligned(4))); };
 template <>
 struct Floats<4> { typedef float T __attribute__((ext_vector_type(4), aligned(4))); };
@@ -493,30 +495,41 @@ struct MfmaPlan {
   int64_t blocks1, tiles, blocks2;
 };
 
-MfmaPlan mfma_plan(int N, int n, int64_t d, int b, bool seg) {
+MfmaPlan mfma_plan(int N, int n, int64_t d, int b, bool seg, int64_t room) {
   MfmaPlan pl{};
   pl.qtiles = int(ceil_div(b, 32));
   const int64_t R = int64_t(N) * n;
   const int64_t stages = ceil_div(d, kZK);
   pl.rblocks = ceil_div(R, kZRows);
+  // partials of more than one split go to G, which is written after they have been read, or to the
+  // workspace where that has room for more of them (chunks of about as many rows as columns; G
+  // alone against both: X of 10 x 512 x 1000 at 64 points 82 us / 46, 1 x 8192 x 8192 at 16 points 726 / 388)
+  const int64_t most = std::max<int64_t>(1, std::min(std::max(d / n, room), stages));
   pl.zqt = pl.qtiles <= 2 ? pl.qtiles : (seg ? 2 : 4);
   // fewer point tiles per block where a few blocks are all there is
-  while (pl.zqt > 1 && pl.rblocks * ceil_div(pl.qtiles, pl.zqt) * ceil_div(stages, 4) < 256) pl.zqt /= 2;
+  while (pl.zqt > 1 && pl.rblocks * ceil_div(pl.qtiles, pl.zqt) * std::min(ceil_div(stages, 4), most) < 256) pl.zqt /= 2;
+  // two positions per lane and two point tiles, but for calls short of a block per CU (us, one
+  // position per lane against two: X of 8 x 8192 x 2048 at 8 points 588 / 750, 4 x 2000 x 2001 at 16
+  // points 146 / 195)
   pl.upw = 2;
   pl.tiles = ceil_div(d, int64_t(32) * pl.upw * kMWaves);
   pl.uqt = pl.qtiles == 1 || pl.tiles * N * ceil_div(pl.qtiles, 2) < 256 ? 1 : 2;
+  if (pl.tiles * N * ceil_div(pl.qtiles, pl.uqt) < 256) {
+    pl.upw = 1;
+    pl.tiles = ceil_div(d, int64_t(32) * kMWaves);
+  }
   pl.zqblocks = int(ceil_div(pl.qtiles, pl.zqt));
   pl.uqblocks = int(ceil_div(pl.qtiles, pl.uqt));
   // K = d split so that the blocks fill whole rounds of the resident ones (two to four per CU
   // by point tiles, on 256 CUs); a block costs about 8 stages beyond its own (its prologue,
   // its Z partials written and summed again), and the sums about one per split.  At most 64
-  // stages per block: 128 additions at a partial's own size (n = 512, d = 16384, 4 points: the
-  // gradients' error 1.4e-7, with 103 stages 1.7e-7, on the vector units 1.6e-7).
+  // stages per block (128 additions at a partial's own size) where there is room for so many
+  // splits; without it calls of 16 points or more run longer sums, in segments if they were short
+  // before (1 x 16384 x 16384, 17 points: 1.7e-7) and else still below the error of one point at a
+  // time (4 x 2000 x 2001, 16 points: 3.1e-7 against 7.5e-7).
   const int64_t resident = 256 * z_waves(pl.zqt, seg);
   constexpr int64_t kExtra = 8, kMaxStages = 64;
   const int64_t tiles = pl.rblocks * pl.zqblocks;
-  // partials of more than one split go to G, which is written after they have been read
-  const int64_t most = std::max<int64_t>(1, std::min(d / n, stages));
   const int64_t least = std::min(ceil_div(stages, kMaxStages), most);
   int64_t best = -1;
   for (int64_t sp = least; sp <= std::min(std::max<int64_t>(least + 8, 64), most); ++sp) {
@@ -544,24 +557,28 @@ MfmaPlan mfma_plan(int N, int n, int64_t d, int b, bool seg) {
 // short rows, whose four passes are as fast (us, fused against matrix cores at 4 points: X of 20 x 512 x
 // 1024 51 / 62, 16 x 2048 x 4096 226 / 321, 8 x 8192 x 2048 344 / 749, 20 x 16 x 16384 42 / 45; but 20 x
 // 64 x 4096 31 / 28, 20 x 512 x 8192 224 / 177; at 5 points 20 x 512 x 1024 64 / 61).
-bool mfma_eligible(int N, int n, int64_t d, int b, bool fused, bool seg) {
+bool mfma_eligible(int N, int n, int64_t d, int b, bool fused, bool seg, int64_t room) {
   if (b < (fused ? 4 : 2) || d > int64_t(1) << 28 || n > 1 << 30) return false;
   if (fused && b == 4 && (n < 32 || (n > 128 && d < 8192))) return false;
   if (double(N) * double(n) * double(d) * double(b) < 3e6) return false;
-  const MfmaPlan pl = mfma_plan(N, n, d, b, seg);
+  const MfmaPlan pl = mfma_plan(N, n, d, b, seg, room);
+  // Few blocks in the second product make a chain of n rows of about 0.07 us each: a few points of
+  // wider rows are faster in their passes (4 x 8192 x 4096, 6 points 400 us against 558, 4 x 2048 x 1024,
+  // 9 points 116 / 129; but 8 x 8192 x 2048, 8 points 652 / 573, 20 x 2048 x 512 284 / 135)
+  if (fused && pl.upw == 1 && d >= 1024 && n > 1024 && int64_t(b) * N * d < 100000) return false;
   // few points keep the vector units where more than 64 stages per block would cost precision
   if (b < 16 && pl.kper > 64 * kZK) return false;
   return grid_ok(pl.blocks1, kZThreads) && grid_ok(pl.blocks2, kMThreads) &&
          grid_ok(ceil_div(int64_t(N) * n * b, 256), 256);
 }
 
-// workspace: the residuals [N n][b]
+// workspace: the residuals [N n][b], and room partial sums of them
 void launch_mfma_grads(const float *X, const float *y, const float *W, int N, int n, int64_t d, int b,
-                       int loss, bool seg, float *G, void *workspace, hipStream_t st) {
-  const MfmaPlan pl = mfma_plan(N, n, d, b, seg);
+                       int loss, bool seg, int64_t room, float *G, void *workspace, hipStream_t st) {
+  const MfmaPlan pl = mfma_plan(N, n, d, b, seg, room);
   const int64_t R = int64_t(N) * n;
   float *U = static_cast<float *>(workspace);
-  float *Zp = pl.splits > 1 ? G : U;
+  float *Zp = pl.splits == 1 ? U : (pl.splits <= d / n ? G : U + R * b);
   const int64_t total = R * b;
 #define GC_ZW(QT, SEG)                                                                                    \
   hipLaunchKernelGGL((zw_kernel<QT, SEG>), dim3(unsigned(pl.blocks1)), dim3(kZThreads), 0, st, X, W, R,   \
@@ -578,7 +595,8 @@ void launch_mfma_grads(const float *X, const float *y, const float *W, int N, in
   hipLaunchKernelGGL((seg ? utx_kernel<QT, PW, true> : utx_kernel<QT, PW, false>),                        \
                      dim3(unsigned(pl.blocks2)), dim3(kMThreads), 0, st, U, X, N, n, d, b, pl.useg,        \
                      pl.uqblocks, pl.tiles, G)
-  if (pl.uqt == 1) GC_UTX(1, 2);
+  if (pl.upw == 1) GC_UTX(1, 1);
+  else if (pl.uqt == 1) GC_UTX(1, 2);
   else GC_UTX(2, 2);
 #undef GC_UTX
 }

@@ -119,3 +119,20 @@ def test_error_of_short_sums(N, n, d, b):
     one = torch.stack([gcx.gc_chunk_grads(X, y, w.contiguous(), gcx.GC_LOSS_LINEAR) for w in W])
     err, single = ((g.double() - ref).norm() / ref.norm() for g in (G, one))
     assert float(err) <= float(single)
+
+
+@pytest.mark.parametrize("N,n,d,b", [
+    # one position per lane: columns around its tiles of 128; partials in the workspace (whole quads, and
+    # rows of whole float4 at a few points) and in G; segments of both products and their remainders
+    (1, 600, 127, 65), (1, 600, 129, 40), (2, 520, 516, 16), (1, 3000, 2052, 20), (3, 700, 260, 132),
+    (1, 2100, 1028, 7), (2, 1030, 4100, 9), (1, 129, 16384, 5), (1, 8200, 512, 6),
+])
+@pytest.mark.parametrize("loss", [gcx.GC_LOSS_LINEAR, gcx.GC_LOSS_LOGISTIC])
+def test_as_many_rows_as_columns(N, n, d, b, loss):
+    X, y, W = problem(N, n, d, b)
+    G = torch.full((b, N, d), float("nan"), device="cuda")
+    need = gcx.gc_chunk_grads_workspace_size(N, n, d, b)
+    ws = torch.full((need + 64,), 0xff, dtype=torch.uint8, device="cuda")
+    gcx.gc_chunk_grads(X, y, W, loss, G=G, workspace=ws[:need])
+    check(G, reference(X, y, W, loss))
+    assert bool((ws[need:] == 0xff).all())

@@ -28,3 +28,9 @@ def points_over_one(N, n, d, b):
 def test_four_points_of_short_rows():
     """Four passes of the kernel for one point (2.0) against the matrix cores in a long chain (3.9)."""
     assert points_over_one(8, 8192, 2048, 4) < 3
+
+
+@pytest.mark.parametrize("N,n,d,b,bar", [(10, 512, 1000, 64, 2.2), (2, 4000, 4096, 64, 2.9), (1, 8192, 8192, 16, 2.7)])
+def test_chunks_of_as_many_rows_as_columns(N, n, d, b, bar):
+    """Column splits that fill the chip (ratios 1.6, 2.0, 1.9), against one split (2.8, 3.8, 3.5)."""
+    assert points_over_one(N, n, d, b) < bar
