@@ -18,7 +18,8 @@
 // Many points (from 4 on, from 2 where the fused path does not apply): two matrix-core GEMMs
 // per chunk (chunk_grads_mfma.hip), two reads of X in all.
 //
-// General path (any d, any alignment): two streaming kernels
+// General path (any d, any alignment: and the fused one's d off 16-byte boundaries, where the
+// workspace holds the residuals): two streaming kernels
 //   dot_kernel   x.w of 4 rows (few rows: 1) over a segment of the columns by one wave, 16-byte
 //                loads from any float on, w loaded once for the rows; several segments' sums
 //                go to G and seg_residual_kernel adds them -> workspace residuals [b][N][n]
@@ -254,25 +255,25 @@ __global__ __launch_bounds__(kFusedThreads) void fused_grad_kernel(
   const int64_t d4 = d / 4;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
 
-  float4 w[NV], acc[NV];
-  const float4 *w4 = reinterpret_cast<const float4 *>(W + int64_t(q) * d);
+  v4fu w[NV], acc[NV];  // rows start on any float
+  const v4fu *w4 = reinterpret_cast<const v4fu *>(W + int64_t(q) * d);
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     const int64_t c = threadIdx.x + int64_t(kFusedThreads) * v;
-    w[v] = c < d4 ? w4[c] : make_float4(0.f, 0.f, 0.f, 0.f);
-    acc[v] = make_float4(0.f, 0.f, 0.f, 0.f);
+    w[v] = c < d4 ? w4[c] : v4fu{0.f, 0.f, 0.f, 0.f};
+    acc[v] = v4fu{0.f, 0.f, 0.f, 0.f};
   }
   const int64_t c0 = r0 / n;  // first chunk of this block
   int64_t cur = c0;
   float *slot = part + ((int64_t(q) * blocks + b) * 2) * d;
 
   auto flush = [&](int64_t chunk) {
-    float4 *dst = reinterpret_cast<float4 *>(slot + (chunk - c0) * d);
+    v4fu *dst = reinterpret_cast<v4fu *>(slot + (chunk - c0) * d);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       const int64_t c = threadIdx.x + int64_t(kFusedThreads) * v;
       if (c < d4) dst[c] = acc[v];
-      acc[v] = make_float4(0.f, 0.f, 0.f, 0.f);
+      acc[v] = v4fu{0.f, 0.f, 0.f, 0.f};
     }
   };
 
@@ -282,12 +283,12 @@ __global__ __launch_bounds__(kFusedThreads) void fused_grad_kernel(
       flush(cur);
       cur = c;
     }
-    const float4 *x4 = reinterpret_cast<const float4 *>(X + r * d);
-    float4 x[NV];
+    const v4fu *x4 = reinterpret_cast<const v4fu *>(X + r * d);
+    v4fu x[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       const int64_t cc = threadIdx.x + int64_t(kFusedThreads) * v;
-      x[v] = cc < d4 ? x4[cc] : make_float4(0.f, 0.f, 0.f, 0.f);
+      x[v] = cc < d4 ? x4[cc] : v4fu{0.f, 0.f, 0.f, 0.f};
     }
     float s = 0.f;
 #pragma unroll
@@ -325,13 +326,13 @@ __global__ void reduce_partials_kernel(const float *__restrict__ part, int N, in
   if (x4 * 4 >= d) return;
   const int64_t bfirst = (i * n) / rows_per_block;
   const int64_t blast = ((i + 1) * n - 1) / rows_per_block;
-  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  v4fu s = {0.f, 0.f, 0.f, 0.f};
   for (int64_t b = bfirst; b <= blast; ++b) {
     const int64_t c0 = (b * rows_per_block) / n;
-    const float4 v = reinterpret_cast<const float4 *>(part + ((int64_t(q) * blocks + b) * 2 + (i - c0)) * d)[x4];
+    const v4fu v = reinterpret_cast<const v4fu *>(part + ((int64_t(q) * blocks + b) * 2 + (i - c0)) * d)[x4];
     s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
   }
-  reinterpret_cast<float4 *>(G + (int64_t(q) * N + i) * d)[x4] = s;
+  reinterpret_cast<v4fu *>(G + (int64_t(q) * N + i) * d)[x4] = s;
 }
 
 }  // namespace
@@ -381,7 +382,9 @@ extern "C" int gc_chunk_grads(const float *X, const float *y, const float *W, in
   // 16 points or more in whole quads are taken on 16-byte boundaries only
   if (b >= 16 && b % 4 == 0 && d % 4 == 0 && (!vec4 || !aligned16(y) || !aligned16(workspace))) return GC_EINVAL;
   const bool enough = workspace_bytes >= sizeof(float) * size_t(rows);  // the residuals, and below the partials
-  const bool fused = vec4 && fused_ok(d) && aligned16(workspace) &&
+  // the fused kernel on 16-byte boundaries, and on any floats where its partials are all that the
+  // workspace holds (rows of few columns)
+  const bool fused = fused_ok(d) && ((vec4 && aligned16(workspace)) || !enough) &&
                      workspace_bytes >= sizeof(float) * size_t(b) * size_t(fused_plan(N, n).blocks) * 2 * size_t(d);
   // Calls that the fused kernel could take (its sums are short: one row's products spread over a block,
   // a block's rows) are summed in segments on the matrix cores, for no larger an error (X of 20 x 512 x
@@ -414,7 +417,6 @@ extern "C" int gc_chunk_grads(const float *X, const float *y, const float *W, in
                        fp.rows_per_block, fp.blocks, G);
     return launch_status();
   }
-  if (!enough) return GC_EINVAL;  // rows of few columns, off the boundaries that the fused path needs
   float *resid = static_cast<float *>(workspace);
   const DotPlan dp = dot_plan(N, n, d, b);
   float *sums = dp.segs > 1 ? G : resid;

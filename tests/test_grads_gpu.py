@@ -136,3 +136,22 @@ def test_as_many_rows_as_columns(N, n, d, b, loss):
     gcx.gc_chunk_grads(X, y, W, loss, G=G, workspace=ws[:need])
     check(G, reference(X, y, W, loss))
     assert bool((ws[need:] == 0xff).all())
+
+
+@pytest.mark.parametrize("N,n,d,b", [(50, 512, 16, 1), (30, 400, 4, 3), (40, 2100, 32, 9)])
+def test_few_columns_on_any_float(N, n, d, b):
+    """Every array one float past a 16-byte boundary and a workspace of the size asked for, which holds the
+    partials of the kernel for short rows but not the residuals."""
+    X, y, W = problem(N, n, d, b)
+    need = gcx.gc_chunk_grads_workspace_size(N, n, d, b)
+    assert need < 4 * b * N * n
+
+    def shifted(t):
+        s = torch.empty(t.numel() + 1, device="cuda")[1:].view(t.shape)
+        return s.copy_(t)
+
+    G = shifted(torch.full((N, d) if b == 1 else (b, N, d), float("nan"), device="cuda"))
+    ws = torch.full((need + 64,), 0xff, dtype=torch.uint8, device="cuda")
+    gcx.gc_chunk_grads(shifted(X), shifted(y), shifted(W), gcx.GC_LOSS_LOGISTIC, G=G, workspace=ws[4:4 + need])
+    check(G, reference(X, y, W, gcx.GC_LOSS_LOGISTIC))
+    assert bool((ws[4 + need:] == 0xff).all())
