@@ -63,6 +63,7 @@ constexpr int kMThreads = 256;                    // utx_kernel
 constexpr int kMWaves = kMThreads / kWave;
 constexpr int kZK = 32;               // k per stage of zw_kernel
 constexpr int kZSeg = 16;             // stages per segment
+constexpr int kChainRows = 1024;      // rows of a chunk from which a few blocks make a long chain
 
 __device__ __forceinline__ v16f mfma16(v8bf a, v8bf b, v16f c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -523,14 +524,15 @@ MfmaPlan mfma_plan(int N, int n, int64_t d, int b, bool seg, int64_t room) {
   // K = d split so that the blocks fill whole rounds of the resident ones (two to four per CU
   // by point tiles, on 256 CUs); a block costs about 8 stages beyond its own (its prologue,
   // its Z partials written and summed again), and the sums about one per split.  At most 64
-  // stages per block (128 additions at a partial's own size) where there is room for so many
-  // splits; without it calls of 16 points or more run longer sums, in segments if they were short
-  // before (1 x 16384 x 16384, 17 points: 1.7e-7) and else still below the error of one point at a
-  // time (4 x 2000 x 2001, 16 points: 3.1e-7 against 7.5e-7).
-  const int64_t resident = 256 * z_waves(pl.zqt, seg);
-  constexpr int64_t kExtra = 8, kMaxStages = 64;
+  // stages per block (128 additions at a partial's own size), 16 where sums were short before,
+  // as far as there is room for so many splits; without it those sums run in segments (50 x 512 x 16384, 4
+  // points: 750 us, with splits of 16 stages 700) and others stay below the error of one
+  // point at a time (4 x 2000 x 2001, 16 points: 3.1e-7 against 7.5e-7).
+  const int64_t resident = 256 * z_waves(pl.zqt, false);
+  constexpr int64_t kExtra = 8;
+  const int64_t max_stages = seg ? kZSeg : 64;
   const int64_t tiles = pl.rblocks * pl.zqblocks;
-  const int64_t least = std::min(ceil_div(stages, kMaxStages), most);
+  const int64_t least = std::min(ceil_div(stages, max_stages), most);
   int64_t best = -1;
   for (int64_t sp = least; sp <= std::min(std::max<int64_t>(least + 8, 64), most); ++sp) {
     const int64_t nst = ceil_div(stages, sp);
@@ -555,17 +557,18 @@ MfmaPlan mfma_plan(int N, int n, int64_t d, int b, bool seg, int64_t room) {
 // but for small calls, where its third launch costs more than the passes saved (X of 111 x 1001
 // at 20 points 13 us against 19, of 256 x 4096 at 4 points 36 against 23), and for four points of
 // short rows, whose four passes are as fast (us, fused against matrix cores at 4 points: X of 20 x 512 x
-// 1024 51 / 62, 16 x 2048 x 4096 226 / 321, 8 x 8192 x 2048 344 / 749, 20 x 16 x 16384 42 / 45; but 20 x
-// 64 x 4096 31 / 28, 20 x 512 x 8192 224 / 177; at 5 points 20 x 512 x 1024 64 / 61).
+// 1024 51 / 62, 16 x 2048 x 4096 226 / 321, 8 x 8192 x 2048 344 / 749, 100 x 16 x 4096 24 / 32; but 20 x
+// 64 x 4096 31 / 28, 20 x 512 x 8192 224 / 177, 20 x 16 x 16384 42 / 32; at 5 points 20 x 512 x 1024 64 / 61).
 bool mfma_eligible(int N, int n, int64_t d, int b, bool fused, bool seg, int64_t room) {
   if (b < (fused ? 4 : 2) || d > int64_t(1) << 28 || n > 1 << 30) return false;
-  if (fused && b == 4 && (n < 32 || (n > 128 && d < 8192))) return false;
+  if (fused && b == 4 && d < 8192 && (n < 32 || n > 128)) return false;
   if (double(N) * double(n) * double(d) * double(b) < 3e6) return false;
   const MfmaPlan pl = mfma_plan(N, n, d, b, seg, room);
-  // Few blocks in the second product make a chain of n rows of about 0.07 us each: a few points of
-  // wider rows are faster in their passes (4 x 8192 x 4096, 6 points 400 us against 558, 4 x 2048 x 1024,
-  // 9 points 116 / 129; but 8 x 8192 x 2048, 8 points 652 / 573, 20 x 2048 x 512 284 / 135)
-  if (fused && pl.upw == 1 && d >= 1024 && n > 1024 && int64_t(b) * N * d < 100000) return false;
+  // Few blocks in the second product make a chain of n rows of about 0.07 us each; the fused kernel
+  // takes 1 ns per row and point, more past 2000 columns (us, fused / matrix cores: 4 x 8192 x 4096 at 6
+  // points 400 / 558, 4 x 2048 x 1024 at 9 116 / 129; 8 x 8192 x 2048 at 8 652 / 573, 10 x 8192 x 1024 at 8
+  // 657 / 550, 20 x 2048 x 512 at 8 284 / 135).
+  if (fused && pl.upw == 1 && n > kChainRows && int64_t(b) * N * std::max<int64_t>(1000, d / 2) < 60000) return false;
   // few points keep the vector units where more than 64 stages per block would cost precision
   if (b < 16 && pl.kper > 64 * kZK) return false;
   return grid_ok(pl.blocks1, kZThreads) && grid_ok(pl.blocks2, kMThreads) &&
@@ -583,8 +586,9 @@ void launch_mfma_grads(const float *X, const float *y, const float *W, int N, in
 #define GC_ZW(QT, SEG)                                                                                    \
   hipLaunchKernelGGL((zw_kernel<QT, SEG>), dim3(unsigned(pl.blocks1)), dim3(kZThreads), 0, st, X, W, R,   \
                      d, b, pl.splits, pl.kper, pl.zqblocks, Zp)
-  if (pl.zqt == 1 && seg) GC_ZW(1, true);
-  else if (seg) GC_ZW(2, true);
+  const bool zseg = seg && pl.kper > kZSeg * kZK;  // segments within the splits as well
+  if (pl.zqt == 1 && zseg) GC_ZW(1, true);
+  else if (zseg) GC_ZW(2, true);
   else if (pl.zqt == 1) GC_ZW(1, false);
   else if (pl.zqt == 2) GC_ZW(2, false);
   else GC_ZW(4, false);
