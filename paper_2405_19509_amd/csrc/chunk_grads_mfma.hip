@@ -282,20 +282,26 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(z_wav
   }
 }
 
-// U[r][q] = loss'(sum_s Zp[s][r][q]) - y[r] for the rows r of all chunks, the splits summed in four
+// U[r][q] = loss'(sum_s Zp[s][r][q]) - y[r] for the rows r of all chunks, the splits summed in eight
 // runs (one long run of 128 splits was off by 1.3e-7 in all, four by 1.2e-7); in place where there is one.
 __global__ __launch_bounds__(256) void resid_kernel(const float *Zp, const float *__restrict__ y, int64_t total,
                                                     int b, int splits, int loss, float *U) {
   const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (e >= total) return;
-  float zs[4] = {0.f, 0.f, 0.f, 0.f};
+  float zs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   int s = 0;
 #pragma unroll 2
-  for (; s + 4 <= splits; s += 4)
+  for (; s + 8 <= splits; s += 8)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) zs[u] += Zp[int64_t(s + u) * total + e];
-  for (; s < splits; ++s) zs[0] += Zp[int64_t(s) * total + e];
-  const float z = (zs[0] + zs[1]) + (zs[2] + zs[3]);
+    for (int u = 0; u < 8; ++u) zs[u] += Zp[int64_t(s + u) * total + e];
+  if (s < splits) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const float v = Zp[int64_t(s + u < splits ? s + u : s) * total + e];
+      zs[u] += s + u < splits ? v : 0.f;
+    }
+  }
+  const float z = ((zs[0] + zs[1]) + (zs[2] + zs[3])) + ((zs[4] + zs[5]) + (zs[6] + zs[7]));
   const float yv = y[e / b];
   U[e] = loss == GC_LOSS_LOGISTIC ? 1.0f / (1.0f + expf(-z)) - yv : z - yv;
 }
