@@ -132,8 +132,9 @@ int gc_qmax(const int32_t *O, int32_t N, int32_t m, int64_t *Q, int64_t *qmax);
  *                          r = sigmoid(X_i w_q) - y_i (GC_LOSS_LOGISTIC)
  * X [N][n][d], y [N][n], W [b][d], G [b][N][d]: device fp32.  fp32 arithmetic.
  * Many points run on the matrix cores, every operand split into three bf16 parts
- * (at or below the error of fp32 sums); G may hold partial sums until the call is
- * done.  With b >= 16 points in whole quads (b % 4 == 0, d % 4 == 0) X, y, W, G and
+ * (at or below the error of fp32 sums; values of X and W below 2^-108 in magnitude
+ * enter with an absolute error of up to 2^-126); G may hold partial sums until the
+ * call is done.  With b >= 16 points in whole quads (b % 4 == 0, d % 4 == 0) X, y, W, G and
  * the workspace must be 16-byte aligned.
  * workspace: device, at least gc_chunk_grads_workspace_size(N, n, d, b) bytes.
  * Errors: GC_EINVAL for sizes < 1, a null pointer, an unknown loss, or a

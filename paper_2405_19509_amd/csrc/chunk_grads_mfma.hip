@@ -14,9 +14,13 @@
 // per 16 terms rounds at the sum's own size (fp32 matrix instructions: one per 2 terms).
 // The matrix cores round worse than to nearest, so long sums drift: calls whose sums were short before
 // (see gc_chunk_grads) add them up in segments, of 512 columns and of 128 rows or more.
-// A NaN in a tile's sums (an infinity's or a NaN's parts, or values near the largest float
-// that round up) makes its wave compute the tile again with the fp32 matrix instructions, which
-// treat infinities as the vector units do.
+// A sum in a tile that is not finite (an infinity's or a NaN's parts, or values near the largest
+// float that round up) makes its wave compute the tile again with the fp32 matrix instructions,
+// which treat infinities as the vector units do.
+//
+// Magnitudes: parts below 2^-126 are lost, so values below about 2^-108 keep less than 24 bits.  U is
+// scaled up by 2^40 for its parts, since whole chunks can have residuals that small (logistic loss of
+// separated data); X and W are taken as they are.
 //
 //   zw_kernel     Z partials over a split of K = d, for 128 of the N n sample rows and up to
 //                 128 points per block.  A wave loads its 32 rows of X from memory in the
@@ -34,6 +38,7 @@
 // At 64 points the matrix cores and the vector units (splits) are busy a third of the time each and
 // the clock falls under both; registers allow three or two waves per SIMD (four spill).
 #include <algorithm>
+#include <cfloat>
 #include <type_traits>
 
 #include "common.h"
@@ -62,6 +67,7 @@ constexpr int kZRows = 32 * (kZThreads / kWave);  // sample rows per block
 constexpr int kMThreads = 256;                    // utx_kernel
 constexpr int kMWaves = kMThreads / kWave;
 constexpr int kZK = 32;               // k per stage of zw_kernel
+constexpr float kUp = 0x1p40f, kDown = 0x1p-40f;  // what U is scaled by, and its sums back
 constexpr int kZSeg = 16;             // stages per segment
 constexpr int kChainRows = 1024;      // rows of a chunk from which a few blocks make a long chain
 
@@ -249,7 +255,7 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(z_wav
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         big[i][v] += small[i][v];
-        bad = bad || big[i][v] != big[i][v];
+        bad = bad || !(fabsf(big[i][v]) <= FLT_MAX);
       }
     if (__any(bad)) {  // the tile on the fp32 matrix instructions
 #pragma unroll
@@ -387,7 +393,7 @@ __global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const float *__restri
 #pragma unroll
     for (int c = 0; c < QT; ++c) {
       uint32_t p[3];
-      split3_trunc(ru[c][0], ru[c][1], p);
+      split3_trunc(ru[c][0] * kUp, ru[c][1] * kUp, p);
 #pragma unroll
       for (int v = 0; v < 3; ++v) Us[buf][(c * 3 + v) * kWave + 32 * uh + t % 32][uj] = p[v];
     }
@@ -442,7 +448,8 @@ __global__ __launch_bounds__(kMThreads, 2) void utx_kernel(const float *__restri
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           big[q][w][v] += small[q][w][v];
-          bad = bad || big[q][w][v] != big[q][w][v];
+          bad = bad || !(fabsf(big[q][w][v]) <= FLT_MAX);
+          big[q][w][v] *= kDown;
         }
     if (__any(bad)) {  // the tile on the fp32 matrix instructions
 #pragma unroll

@@ -155,3 +155,30 @@ def test_few_columns_on_any_float(N, n, d, b):
     gcx.gc_chunk_grads(shifted(X), shifted(y), shifted(W), gcx.GC_LOSS_LOGISTIC, G=G, workspace=ws[4:4 + need])
     check(G, reference(X, y, W, gcx.GC_LOSS_LOGISTIC))
     assert bool((ws[4 + need:] == 0xff).all())
+
+
+@pytest.mark.parametrize("N,n,d,b", [(4, 100, 4097, 5), (2, 130, 16384, 20), (3, 70, 4100, 64), (1, 600, 129, 40)])
+def test_small_residuals(N, n, d, b):
+    """Residuals of separated data, far below 2^-108: no larger an error than at ordinary size (sums of up to
+    600 products, 2 to 4e-7)."""
+    X, y, W = problem(N, n, d, b)
+    W *= 0
+    y.normal_().mul_(2.0 ** -118)
+    ref = reference(X, y, W, gcx.GC_LOSS_LINEAR)
+    G = gcx.gc_chunk_grads(X, y, W, gcx.GC_LOSS_LINEAR)
+    assert float((G.double() - ref).norm() / ref.norm()) <= 5e-7
+
+
+@pytest.mark.parametrize("b", [5, 20, 64])
+def test_sums_near_the_largest_float(b):
+    """A product whose leading parts round up past the largest float while it does not."""
+    N, n, d = 2, 40, 5000
+    X, y, W = problem(N, n, d, b)
+    W *= 0
+    y[1, 7] = -(2.0 ** 64)
+    X[1, 7, 1234] = 1.998 * 2.0 ** 63
+    G = gcx.gc_chunk_grads(X, y, W, gcx.GC_LOSS_LINEAR)
+    assert bool(G.isfinite().all())
+    check(G, reference(X, y, W, gcx.GC_LOSS_LINEAR))
+    ref = 1.998 * 2.0 ** 127
+    assert float((G[:, 1, 1234].double() - ref).abs().max()) <= 1e-6 * ref
