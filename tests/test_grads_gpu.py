@@ -1,8 +1,8 @@
 """Chunk gradients where their paths change: column counts that no vector width divides, few and
 many rows and points, tile edges, unaligned rows, infinities and NaN.
 
-Reference: the same products in 64 bits.  Bar: relative 2-norm per chunk 1e-5, the repository's
-for G (measured errors are 0.5 to 2e-7)."""
+Reference: the same products in 64 bits.  Bar: relative 2-norm per chunk 1e-6 (measured errors are 0.5
+to 5e-7; a product of bf16 parts left out gives 1.4e-6 and more, test_grads_parts.py)."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -10,6 +10,7 @@ torch = pytest.importorskip("torch")
 from paper_2405_19509_amd import gcx  # noqa: E402
 
 pytestmark = pytest.mark.gpu
+BAR = 1e-6
 
 
 def problem(N, n, d, b, seed=0):
@@ -34,7 +35,7 @@ def reference(X, y, W, loss):
 def check(G, ref):
     G = G.double().view(ref.shape)
     err = (G - ref).norm(dim=-1) / ref.norm(dim=-1).clamp_min(1e-30)
-    assert float(err.max()) <= 1e-5
+    assert float(err.max()) <= BAR
 
 
 @pytest.mark.parametrize("N,n,d,b", [
