@@ -77,21 +77,18 @@ struct Floats<2> { typedef float T __attribute__((ext_vector_type(2), aligned(4)
 template <>
 struct Floats<4> { typedef float T __attribute__((ext_vector_type(4), aligned(4))); };
 
-// round-to-nearest-even bf16 bits of a finite fp32 value
-__device__ __forceinline__ uint32_t bf16_rne(float v) {
-  const uint32_t b = __float_as_uint(v);
-  return (b + 0x7fffu + ((b >> 16) & 1u)) >> 16;
-}
-
-// A coefficient in three bf16 parts: b1 = bf16(v), b2 = bf16(v - b1), b3 = bf16(v - b1 - b2), all exact
-// steps.  What would round past the largest bf16 is cut to its top 16 bits instead; an infinity or a
-// NaN is in the first part alone.
-__device__ __forceinline__ void split_coef(float v, uint32_t (&b)[3]) {
-  const uint32_t bits = __float_as_uint(v), mag = bits & 0x7fffffffu;
-  b[0] = mag < 0x7f7f8000u ? bf16_rne(v) : (mag > 0x7f800000u ? 0x7fc0u : bits >> 16);
-  const float r1 = mag < 0x7f800000u ? v - __uint_as_float(b[0] << 16) : 0.f;
-  b[1] = bf16_rne(r1);
-  b[2] = bf16_rne(r1 - __uint_as_float(b[1] << 16));
+// A coefficient in three bf16 parts, each the rounding of what the earlier ones leave, all exact
+// steps; the first part is at most the largest bf16, so that what would round past it stays finite.
+// An infinity leaves a NaN, as a NaN does.  Two instructions for the limits: v_med3_f32's constant
+// stays in a register over the tile loop, one too many for three waves at 11 steps of bf16.
+__device__ __forceinline__ void split_coef(float v, uint16_t (&b)[3]) {
+  constexpr float most = 0x1.fep127f;
+  const __bf16 b1 = __bf16(fmaxf(fminf(v, most), -most));
+  const float r1 = v - float(b1);
+  const __bf16 b2 = __bf16(r1), b3 = __bf16(r1 - float(b2));
+  b[0] = __builtin_bit_cast(uint16_t, b1);
+  b[1] = __builtin_bit_cast(uint16_t, b2);
+  b[2] = __builtin_bit_cast(uint16_t, b3);
 }
 
 // chk + 0 * (either bf16 half of pair): a NaN once a half is infinite or a NaN
@@ -163,10 +160,13 @@ struct MxLayout {
   static constexpr int AP = Kp + 8;       // plane row stride (bf16): 16-byte rows, staggered banks
   static constexpr int W = 32 * PW;       // positions per tile
   static constexpr bool APART = KS == 1;  // small products in sums of their own
-  // registers: B (4 NP PW KS; fp32 splits take some more), accumulators (16 or 32 PW), one K step
+  // registers: B (4 NP PW KS; fp32 splits take some more), accumulators (16 PW), one K step
   // of A (12), addresses
-  static constexpr int REGS = (F32 ? 15 : 4) * PW * KS + (APART ? 32 : 16) * PW + 12 + 40;
-  static constexpr int WPE = REGS <= 128 ? 4 : (REGS <= 168 ? 3 : 2);
+  static constexpr int REGS = (F32 ? 15 : 4) * PW * KS + 16 * PW + 12 + 40;
+  // waves per SIMD: the most that the compiler fits without scratch, which costs a call 18 us.  Sums
+  // of their own want 16 registers more, 215 in all at four fp32 positions.
+  static constexpr int WPE = APART ? (F32 && PW == 4 ? 2 : 3)
+                                   : (REGS <= 128 || (F32 && KS == 2 && PW == 2) ? 4 : (REGS <= 168 ? 3 : 2));
 };
 
 // The window's rows at the positions of one tile, term by term over the processed prefix in
@@ -361,7 +361,8 @@ encode_mx_kernel(MxArgs a) {
       lim[q] = rem < a.L ? rem : a.L;
     }
     __syncthreads();
-    // three bf16 planes per row tile, one for each part of the coefficients; row kk at column 16 (kk / 16) + 8 (kk % 2) + (kk % 16) / 2
+    // three bf16 planes per row tile, one for each part of the coefficients; row kk at column
+    // 16 (kk / 16) + 8 (kk % 2) + (kk % 16) / 2
     for (int e = tid; e < nsend * a.delta; e += nth) {
       const int c = e / a.delta, t = e - c * a.delta;
       if (t >= cnp[c]) continue;
@@ -374,10 +375,10 @@ encode_mx_kernel(MxArgs a) {
       for (int k = 0; k < ell; ++k) {
         const int kk = s * ell + k;
         const int col = (kk & ~15) + 8 * (kk & 1) + ((kk & 15) >> 1);
-        uint32_t part[3];
+        uint16_t part[3];
         split_coef(src[k], part);
 #pragma unroll
-        for (int i = 0; i < 3; ++i) tp[32 * i * AP + col] = uint16_t(part[i]);
+        for (int i = 0; i < 3; ++i) tp[32 * i * AP + col] = part[i];
       }
     }
     __syncthreads();
@@ -482,38 +483,49 @@ encode_mx_kernel(MxArgs a) {
 #pragma unroll 1
       for (int rt = 0; rt < ntile; ++rt) {
         const uint16_t *At = Ap + rt * (3 * 32 * AP) + li * AP + 8 * h;
-        v16f acc[PW], big[Lay::APART ? PW : 1];
-#pragma unroll
-        for (int w = 0; w < PW; ++w) acc[w] = v16f{};
-        auto mm_to = [&](v16f *sum, const uint16_t *plane, int q, int part) {
+        v16f acc[PW];
+        auto mm = [&](v16f &sum, const uint16_t *plane, int q, int w, int part) {
           const v8bf av = *reinterpret_cast<const v8bf *>(plane + 16 * q);
-#pragma unroll
-          for (int w = 0; w < PW; ++w)
-            sum[w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bf[q][w][part], sum[w], 0, 0, 0);
+          sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bf[q][w][part], sum, 0, 0, 0);
         };
-        auto mm = [&](const uint16_t *plane, int q, int part) { mm_to(acc, plane, q, part); };
         // the products of parts above 2^-24 relative; those below 2^-7 of the whole first, over
         // all of K, so that only the last KS sums round at the result's own size
-#pragma unroll
-        for (int q = 0; q < KS; ++q) {
-          mm(At + 64 * AP, q, 0);
-          if constexpr (F32) {
-            mm(At + 32 * AP, q, 1);
-            mm(At, q, 2);
-          }
-          mm(At + 32 * AP, q, 0);
-          if constexpr (F32) mm(At, q, 1);
-        }
         if constexpr (Lay::APART) {
 #pragma unroll
-          for (int w = 0; w < PW; ++w) big[w] = v16f{};
+          for (int w = 0; w < PW; ++w) {
+            v16f small = v16f{}, big = v16f{};
 #pragma unroll
-          for (int q = 0; q < KS; ++q) mm_to(big, At, q, 0);
-#pragma unroll
-          for (int w = 0; w < PW; ++w) acc[w] += big[w];
+            for (int q = 0; q < KS; ++q) {
+              mm(small, At + 64 * AP, q, w, 0);
+              if constexpr (F32) {
+                mm(small, At + 32 * AP, q, w, 1);
+                mm(small, At, q, w, 2);
+              }
+              mm(small, At + 32 * AP, q, w, 0);
+              if constexpr (F32) mm(small, At, q, w, 1);
+              mm(big, At, q, w, 0);
+            }
+            acc[w] = small + big;
+          }
         } else {
 #pragma unroll
-          for (int q = 0; q < KS; ++q) mm(At, q, 0);
+          for (int w = 0; w < PW; ++w) acc[w] = v16f{};
+          auto each = [&](const uint16_t *plane, int q, int part) {
+#pragma unroll
+            for (int w = 0; w < PW; ++w) mm(acc[w], plane, q, w, part);
+          };
+#pragma unroll
+          for (int q = 0; q < KS; ++q) {
+            each(At + 64 * AP, q, 0);
+            if constexpr (F32) {
+              each(At + 32 * AP, q, 1);
+              each(At, q, 2);
+            }
+            each(At + 32 * AP, q, 0);
+            if constexpr (F32) each(At, q, 1);
+          }
+#pragma unroll
+          for (int q = 0; q < KS; ++q) each(At, q, 0);
         }
         // lane (h, li) holds D[8(v/4) + 4h + v%4][li] of each 32-wide tile: rows 32 rt + 8g + 4h
         // + i, PW neighbouring positions each.  Non-temporal where rows start on 64-byte
@@ -659,8 +671,14 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
     a.CW = (a.J * a.PB + 31) & ~31;
     if (mx_lds(a, KS) <= kMxLds || cw == 32) break;  // 32 rows always fit
   }
-  // positions per lane, as registers allow (fp32: 12 PW per K step, bf16 4 PW; 16 PW sums)
-  const int pw = f32 ? (KS <= 2 ? (small_odd || many ? 4 : 2) : (KS <= 5 ? 2 : 1)) : (KS <= 8 ? 4 : 2);
+  // positions per lane, as registers allow (fp32: 12 PW per K step, bf16 4 PW; 16 PW sums).  On odd rows
+  // at one fp32 step four positions take 215 registers, two waves per SIMD: two positions, four waves
+  // where the grid holds at most four blocks per CU (us, two / four positions: m = 44, delta = 5, d =
+  // 24769, 27 patterns 32.0 / 34.4, m = 30, delta = 11, d = 52503, 8 patterns 19.8 / 22.0; larger, m = 50,
+  // delta = 5, d = 10^6, 8 patterns 525 / 485)
+  const int64_t units = int64_t(a.ngroups) * a.ntp;
+  const bool wide = many || (small_odd && (KS == 2 || ceil_div(a.L, 4 * 128) * units > 4 * int64_t(cu_count())));
+  const int pw = f32 ? (KS <= 2 ? (wide ? 4 : 2) : (KS <= 5 ? 2 : 1)) : (KS <= 8 ? 4 : 2);
   const int threads = KS <= (f32 ? 2 : 3) ? 256 : 512;
   const int nw = threads / kWave;
   a.ntiles = ceil_div(a.L, int64_t(32) * pw);
@@ -669,7 +687,6 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
   // bf16 at two steps and many patterns: m = 200, delta = 20, d = 2^18, 128 patterns 3.94 against 4.40,
   // m = 100, delta = 16, ell = 2, 256 patterns 2.11 against 2.22, 64 patterns of m = 200 2.47 against 2.43),
   // fewer while the grid is short of four blocks per CU
-  const int64_t units = int64_t(a.ngroups) * a.ntp;
   a.tpb = int64_t(nw) * (!f32 && KS == 2 && P > 64 ? 4 : (KS <= 3 ? 2 : 8));
   while (a.tpb > nw && ceil_div(a.ntiles, a.tpb) * units < 4 * int64_t(cu_count())) a.tpb -= nw;
   a.nsr = ceil_div(a.ntiles, a.tpb);
