@@ -185,8 +185,9 @@ __global__ __launch_bounds__(kGradThreads) void xtr_kernel(const float *__restri
 }
 
 // Rows per wave, row groups and column segments of dot_kernel per point.  Segments of at least
-// 1024 columns (four rounds of a wave's 16-byte loads), as many as give every CU 32 waves; one row
-// per wave where four would leave the CUs short of 8 waves.  The segments' sums go to G, which is
+// 4096 columns, whose sums' launch costs what shorter ones save (us, 1024 / 4096: X of 9 x 131 x 2101
+// 16.4 / 14.2, 9 x 131 x 4101 17.2 / 15.0, 3 x 20 x 400001 56 / 42; one segment of 16385 40), as many
+// as give every CU 32 waves; one row per wave where four would leave the CUs short of 8 waves.  The segments' sums go to G, which is
 // written after they have been read: at most d / n segments.
 struct DotPlan {
   int rows;
@@ -196,7 +197,7 @@ struct DotPlan {
 
 inline DotPlan dot_plan(int N, int n, int64_t d, int b) {
   DotPlan dp{};
-  const int64_t R = int64_t(N) * n, most = std::max<int64_t>(1, std::min(d / 1024, d / n));
+  const int64_t R = int64_t(N) * n, most = std::max<int64_t>(1, std::min(d / 4096, d / n));
   dp.rows = ceil_div(R, 4) * b * most < 2048 ? 1 : 4;
   dp.groups = ceil_div(R, dp.rows);
   const int64_t segs = std::max<int64_t>(1, std::min(ceil_div(8192, dp.groups * b), most));

@@ -575,8 +575,17 @@ MfmaPlan mfma_plan(int N, int n, int64_t d, int b, bool seg, int64_t room) {
 bool mfma_eligible(int N, int n, int64_t d, int b, bool fused, bool seg, int64_t room) {
   if (b < (fused ? 4 : 2) || d > int64_t(1) << 28 || n > 1 << 30) return false;
   if (fused && b == 4 && d < 8192 && (n < 32 || n > 128)) return false;
-  if (double(N) * double(n) * double(d) * double(b) < 3e6) return false;
+  const double volume = double(N) * double(n) * double(d) * double(b);
+  if (fused && volume < 3e6) return false;
   const MfmaPlan pl = mfma_plan(N, n, d, b, seg, room);
+  // Against two passes per point the third launch, the chain of n rows and that of a split's stages have
+  // to pay: both times in us, measured at 1 to 60 chunks of 17 x 815 to 12 x 100001 and 1 to 64 points.
+  // One point at a time reads X from a cache the more the points (us, vector units / matrix cores: 1 x 1000
+  // x 333 at 17 points 21 / 64, 5 x 200 x 1001 at 8 15 / 26, 2 x 12 x 100001 at 4 20 / 61; above the line 12
+  // x 500 x 8193 at 2 133 / 91, 23 x 131 x 4099 at 8 122 / 36, 12 x 60 x 2101 at 64 57 / 25).
+  const double vector_us = 13 + 0.014 * n + 1.15e-6 * volume / (1 + std::min(b, 128) / 64.0);
+  const double matrix_us = 17 + 0.04 * n + 0.6 * double(pl.kper / kZK) + 0.9e-6 * volume / b;
+  if (!fused && vector_us < matrix_us) return false;
   // Few blocks in the second product make a chain of n rows of about 0.07 us each; the fused kernel
   // takes 1 ns per row and point, more past 2000 columns (us, fused / matrix cores: 4 x 8192 x 4096 at 6
   // points 400 / 558, 4 x 2048 x 1024 at 9 116 / 129; 8 x 8192 x 2048 at 8 652 / 573, 10 x 8192 x 1024 at 8

@@ -47,6 +47,8 @@ def check(G, ref):
     # 64, 256, one and several splits of the columns, one to four point tiles per block
     (4, 64, 4096, 4), (3, 33, 8191, 31), (2, 130, 16385, 33), (7, 17, 20001, 64), (1, 128, 32771, 65),
     (5, 100, 2049, 97), (2, 31, 33000, 129), (30, 300, 70, 60), (60, 15, 33, 256), (1, 7, 200003, 5),
+    # enough work for the matrix cores where one point at a time takes the smaller calls above
+    (20, 33, 8191, 31), (240, 15, 33, 256), (24, 7, 200003, 5),
 ])
 @pytest.mark.parametrize("loss", [gcx.GC_LOSS_LINEAR, gcx.GC_LOSS_LOGISTIC])
 def test_shapes(N, n, d, b, loss):
@@ -80,7 +82,7 @@ def test_whole_quads_off_their_boundary_are_refused(n):
         gcx.gc_chunk_grads(off.copy_(X), y, W, gcx.GC_LOSS_LINEAR)
 
 
-@pytest.mark.parametrize("b", [1, 20, 64, 128])
+@pytest.mark.parametrize("b", [1, 20, 33, 64, 128])
 @pytest.mark.parametrize("kind", ["inf in X", "inf in W", "NaN in X", "NaN in W", "near the largest float"])
 def test_values_that_are_not_finite(kind, b):
     """They reach the outputs that they reach in 64 bits, and no others."""
@@ -127,6 +129,7 @@ def test_error_of_short_sums(N, n, d, b):
     # rows of whole float4 at a few points) and in G; segments of both products and their remainders
     (1, 600, 127, 65), (1, 600, 129, 40), (2, 520, 516, 16), (1, 3000, 2052, 20), (3, 700, 260, 132),
     (1, 2100, 1028, 7), (2, 1030, 4100, 9), (1, 129, 16384, 5), (1, 8200, 512, 6),
+    (12, 600, 127, 65), (16, 600, 129, 40), (16, 520, 516, 16), (3, 3000, 2052, 20), (9, 700, 260, 132),
 ])
 @pytest.mark.parametrize("loss", [gcx.GC_LOSS_LINEAR, gcx.GC_LOSS_LOGISTIC])
 def test_as_many_rows_as_columns(N, n, d, b, loss):
@@ -158,7 +161,8 @@ def test_few_columns_on_any_float(N, n, d, b):
     assert bool((ws[4 + need:] == 0xff).all())
 
 
-@pytest.mark.parametrize("N,n,d,b", [(4, 100, 4097, 5), (2, 130, 16384, 20), (3, 70, 4100, 64), (1, 600, 129, 40)])
+@pytest.mark.parametrize("N,n,d,b", [(4, 100, 4097, 5), (2, 130, 16384, 20), (3, 70, 4100, 64), (1, 600, 129, 40),
+                                     (40, 100, 4097, 5), (16, 600, 129, 40)])
 def test_small_residuals(N, n, d, b):
     """Residuals of separated data, far below 2^-108: no larger an error than at ordinary size (sums of up to
     600 products, 2 to 4e-7)."""

@@ -34,3 +34,10 @@ def test_four_points_of_short_rows():
 def test_chunks_of_as_many_rows_as_columns(N, n, d, b, bar):
     """Column splits that fill the chip (ratios 1.6, 2.0, 1.9), against one split (2.8, 3.8, 3.5)."""
     assert points_over_one(N, n, d, b) < bar
+
+
+@pytest.mark.parametrize("N,n,d,b,bar", [(5, 200, 1001, 8, 1.7), (1, 1000, 333, 17, 2.7), (2, 12, 100001, 4, 2.2)])
+def test_small_calls_at_several_points(N, n, d, b, bar):
+    """Rows off float4, one point at a time (ratios 1.2, 1.1, 1.1), against three launches and their
+    chains (2.3, 4.4, 3.3)."""
+    assert points_over_one(N, n, d, b) < bar
