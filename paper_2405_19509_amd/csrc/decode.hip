@@ -1,6 +1,7 @@
 // gc_decode_coeffs: coverage, decodability, coefficient error and the
 // encoding coefficients of Algorithm 1 (Find-Encoding-Coeff), batched over
-// straggler patterns.  One wavefront per pattern, one lane per chunk.
+// straggler patterns.  One wavefront per pattern, or a block's wavefronts where patterns are few or
+// their regions large; one lane per chunk, then in most kernels one per coefficient row.
 //
 // For chunk i with processed holders S_i (Delta = |S_i|) and X = R[:, S_i]
 // (ell x Delta), Algorithm 1's minimum-norm least-squares coefficients are
@@ -11,7 +12,9 @@
 //   Delta <  ell:  H = X^T X (Delta x Delta, padded with the identity to
 //                  ell x ell),  pinv(X) = H^-1 X^T
 // with a Cholesky factorisation of M or H.  ell = 1 reduces to Remark 1:
-// coefficient R_j / sum_{S_i} R^2.  Coverage and decodability are integer
+// coefficient R_j / sum_{S_i} R^2; its fp64 sum runs in the holder table's order, in the cyclic
+// kernel in ascending cyclic order, so that the last bit of a coefficient may differ between a
+// call of at most as many patterns as CUs (the block kernel) and a larger one.  Coverage and decodability are integer
 // decisions and never depend on the floating-point solve.
 #include <algorithm>
 
@@ -251,8 +254,10 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_kernel(
 //     K^T (K x_j), written contiguously.  There are delta times more rows than chunks, so the
 //     divisions stay in phase 1 (m = 200, delta = 20, ell = 2, 20,000 patterns, 640 MB of Bc:
 //     350 us with them in phase 2, 199 us without).
-// Both phases read psi from the wave's LDS copy.  Results equal decode_kernel's up to the fp64
-// rounding of reciprocals in place of divisions, before the one rounding to fp32.
+// Both phases read psi from the wave's LDS copy.  Results equal decode_kernel's up to fp64
+// rounding before the one rounding to fp32: of a reciprocal in place of divisions at ell = 1, of
+// products with the factor's inverse in place of triangular solves at ell >= 2, which grows with
+// the condition of X X^T as the factor's own does (the Gram matrix squares it in both).
 template <int ELL>
 struct DecodeLayout {
   static constexpr int NF = ELL * (ELL + 1) / 2;  // packed lower triangle
