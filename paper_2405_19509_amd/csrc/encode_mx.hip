@@ -39,7 +39,7 @@
 //
 // Rows of workers that transmit nothing (psi = 0) are not written.  The blocks of a position
 // range run back to back on one XCD (round-robin dispatch), so its L2 serves the windows'
-// overlapping chunks.  If a window's workers hold more distinct chunks than its slots (orders
+// overlapping chunks; those of the ranges past whole eights are spread over all XCDs.  If a window's workers hold more distinct chunks than its slots (orders
 // other than the cyclic one), the block takes as many of its workers at a time as fit.
 #include <algorithm>
 #include <type_traits>
@@ -636,11 +636,13 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
   // 128 / 192 rows 2.4 / 2.1 / 2.05 ms).  With few K steps on rows that start anywhere 128 rows
   // and four positions per lane (0.62 ms against 0.65 with 256 rows, 0.68 with two positions).
   const bool small_odd = f32 && !a.nt && steps(delta) <= 2;
-  // The same on rows at 64 bytes with many patterns: at most 64 patterns per K step and window, so
+  // The same on rows at 64 bytes with many patterns: at most 32 patterns per K step and window, so
   // that a window takes several workers, and four positions per lane.  Windows of 256 patterns of one
   // worker wrote 256-byte pieces m rows apart, below the worker groups' rate (ms, one worker / this /
   // worker groups: m = 100, delta = 10, d = 2^20, ell = 1, 256 patterns 21.4 / 16.1 / 15.8, ell = 2, 512
-  // patterns 24.3 / 17.7 / 22.8; m = 200, delta = 20, d = 2^18, 512 patterns 27.6 / 19.2 / 22.9).
+  // patterns 24.3 / 17.7 / 22.8; m = 200, delta = 20, d = 2^18, 512 patterns 27.6 / 19.2 / 22.9; 64 patterns
+  // per step / 32 / worker groups: m = 50, delta = 5, d = 2^14, ell = 2, 1000 patterns 0.276 / 0.251 / 0.417,
+  // 10,000 2.39 / 2.32 / 2.19).
   const bool many = f32 && a.nt && steps(delta) <= 2 && P > 64;
   int KS = 0;
   for (int cw = small_odd ? 128 : (f32 ? kMxMaxCW : 192);; cw -= 32) {
@@ -649,7 +651,7 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
     // K steps the most workers it holds, and of these the one with the least work per row: KS
     // products per row tile, and for each K step loads and splits that cost about as much as
     // 2.5 row tiles' products
-    a.PB = int(ceil_div(P, ceil_div(P, many ? std::min<int64_t>(cw, 64 * steps(delta)) : cw)));
+    a.PB = int(ceil_div(P, ceil_div(P, many ? std::min<int64_t>(cw, 32 * steps(delta)) : cw)));
     a.ntp = ceil_div(P, a.PB);
     const int64_t most = N <= kMxMapChunks ? std::min<int64_t>(cw / a.PB, m) : 1;
     double best = 0;
