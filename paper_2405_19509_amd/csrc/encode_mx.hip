@@ -160,13 +160,17 @@ struct MxLayout {
   static constexpr int AP = Kp + 8;       // plane row stride (bf16): 16-byte rows, staggered banks
   static constexpr int W = 32 * PW;       // positions per tile
   static constexpr bool APART = KS == 1;  // small products in sums of their own
+  // Nothing that only the tables' construction needs kept in registers over the tile loop, and one
+  // position's sums formed at a time: at one fp32 step and four positions 168 registers, three waves per
+  // SIMD, instead of 214 (m = 37, delta = 8, d = 3261045, 2 patterns 399 -> 307 us, m = 90, delta = 7, d =
+  // 349517, 3 patterns 99 -> 88).  Elsewhere the waves stay as many and calls lost up to 7% by it.
+  static constexpr bool LEAN = F32 && APART;
   // registers: B (4 NP PW KS; fp32 splits take some more), accumulators (16 PW), one K step
   // of A (12), addresses
   static constexpr int REGS = (F32 ? 15 : 4) * PW * KS + 16 * PW + 12 + 40;
-  // waves per SIMD: the most that the compiler fits without scratch, which costs a call 18 us.  Sums
-  // of their own want 16 registers more, 215 in all at four fp32 positions.
-  static constexpr int WPE = APART ? (F32 && PW == 4 ? 2 : 3)
-                                   : (REGS <= 128 || (F32 && KS == 2 && PW == 2) ? 4 : (REGS <= 168 ? 3 : 2));
+  // waves per SIMD asked for: the most that the compiler fits without scratch, which costs a call 18 us
+  static constexpr int WPE =
+      APART ? 3 : (REGS <= 128 || (F32 && KS == 2 && PW == 2) ? 4 : (REGS <= 168 ? 3 : 2));
 };
 
 // The window's rows at the positions of one tile, term by term over the processed prefix in
@@ -251,6 +255,8 @@ encode_mx_kernel(MxArgs a) {
   const int nj = a.m - j0 < a.J ? a.m - j0 : a.J;
   const int ell = a.ell;
   float *const Tw = a.T + (p0 * a.m + j0) * a.L;  // row (pattern p0, worker j0) of T
+  // a block's value in a scalar register
+  auto uniform = [](int v) { return Lay::LEAN ? __builtin_amdgcn_readfirstlane(v) : v; };
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), nw = nth / kWave;
   const int lane = tid % kWave, h = lane >> 5, li = lane & 31;
@@ -293,18 +299,20 @@ encode_mx_kernel(MxArgs a) {
       if (tid == 0) nuni_s = cnt;
     }
     __syncthreads();
-    nuni = nuni_s;
+    nuni = uniform(nuni_s);
   }
   for (int ja = 0, jn = nj; ja < nj; ja = jn) {  // workers ja .. jn - 1 of the group
+    int tp = tid;
+    if constexpr (Lay::LEAN) asm volatile("" : "+v"(tp));  // opaque: formed anew in each pass
     int nslot = nuni;
     __syncthreads();  // the previous pass is done with every table
     if (a.J == 1) {
       nslot = a.delta;
-      for (int t = tid; t < a.delta; t += nth) slotc[t] = code[t] >= 0 ? code[t] : 0;
+      for (int t = tp; t < a.delta; t += nth) slotc[t] = code[t] >= 0 ? code[t] : 0;
     } else if (nuni > a.slots) {
-      for (int c = tid; c < a.N; c += nth) map[c] = -1;
+      for (int c = tp; c < a.N; c += nth) map[c] = -1;
       __syncthreads();
-      if (tid < kWave) {
+      if (tp < kWave) {
         int cnt = 0, j = ja;
         for (; j < nj; ++j) {
           const int c = lane < a.delta ? code[j * a.delta + lane] : -1;  // delta <= 64
@@ -321,19 +329,20 @@ encode_mx_kernel(MxArgs a) {
           __builtin_amdgcn_wave_barrier();
           __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
-        if (tid == 0) {
+        if (tp == 0) {
           nuni_s = cnt;
           jn_s = j;
         }
       }
       __syncthreads();
-      nslot = nuni_s;
-      jn = jn_s;
+      nslot = uniform(nuni_s);
+      jn = uniform(jn_s);
     }
     const int K = nslot * ell;  // rows of B
-    for (int e = tid; e < (a.CW / 32) * (3 * 32 * AP / 8); e += nth)
+    for (int e = tp; e < (a.CW / 32) * (3 * 32 * AP / 8); e += nth)
       reinterpret_cast<uint4 *>(Ap)[e] = make_uint4(0u, 0u, 0u, 0u);
     // the transmitting candidates, compacted in order
+    const int rpb = tp / a.J, rjb = tp - rpb * a.J;
     const bool on = npr > 0 && rjb >= ja && rjb < jn;
     const unsigned long long mk = __ballot(on);
     if (lane == 0) wcnt[wave] = __popcll(mk);
@@ -343,16 +352,17 @@ encode_mx_kernel(MxArgs a) {
       if (w < wave) c0 += wcnt[w];
       nsend += wcnt[w];
     }
+    nsend = uniform(nsend);
     if (on) {
       const int c = c0 + __popcll(mk & ((1ull << lane) - 1));
-      crow[c] = int16_t(tid);
+      crow[c] = int16_t(tp);
       cnp[c] = int16_t(npr);
       rowoff[c] = (int64_t(rpb) * a.m + rjb) * a.L;
     }
     const int ntile = (nsend + 31) / 32;
     // row kk of B: half kk % 2, place kk / 2 (a place past K repeats row 0, with zero
     // coefficients): its element offset in G and the end of its valid positions
-    for (int e = tid; e < Kp; e += nth) {
+    for (int e = tp; e < Kp; e += nth) {
       const int kk = e < K ? e : 0;
       const int s = kk / ell, k = kk - s * ell;
       const int64_t rem = a.d - int64_t(k) * a.L;
@@ -363,7 +373,7 @@ encode_mx_kernel(MxArgs a) {
     __syncthreads();
     // three bf16 planes per row tile, one for each part of the coefficients; row kk at column
     // 16 (kk / 16) + 8 (kk % 2) + (kk % 16) / 2
-    for (int e = tid; e < nsend * a.delta; e += nth) {
+    for (int e = tp; e < nsend * a.delta; e += nth) {
       const int c = e / a.delta, t = e - c * a.delta;
       if (t >= cnp[c]) continue;
       const int pb = crow[c] / a.J, jb = crow[c] - pb * a.J;
@@ -371,14 +381,14 @@ encode_mx_kernel(MxArgs a) {
       if (ch < 0) continue;
       const int s = a.J == 1 ? t : map[ch];
       const float *src = a.Bc + (((p0 + pb) * a.m + j0 + jb) * a.delta + t) * ell;
-      uint16_t *tp = Ap + (c / 32) * (3 * 32 * AP) + (c % 32) * AP;
+      uint16_t *row = Ap + (c / 32) * (3 * 32 * AP) + (c % 32) * AP;
       for (int k = 0; k < ell; ++k) {
         const int kk = s * ell + k;
         const int col = (kk & ~15) + 8 * (kk & 1) + ((kk & 15) >> 1);
         uint16_t part[3];
         split_coef(src[k], part);
 #pragma unroll
-        for (int i = 0; i < 3; ++i) tp[32 * i * AP + col] = part[i];
+        for (int i = 0; i < 3; ++i) row[32 * i * AP + col] = part[i];
       }
     }
     __syncthreads();
@@ -493,19 +503,20 @@ encode_mx_kernel(MxArgs a) {
         if constexpr (Lay::APART) {
 #pragma unroll
           for (int w = 0; w < PW; ++w) {
-            v16f small = v16f{}, big = v16f{};
-#pragma unroll
-            for (int q = 0; q < KS; ++q) {
-              mm(small, At + 64 * AP, q, w, 0);
-              if constexpr (F32) {
-                mm(small, At + 32 * AP, q, w, 1);
-                mm(small, At, q, w, 2);
-              }
-              mm(small, At + 32 * AP, q, w, 0);
-              if constexpr (F32) mm(small, At, q, w, 1);
-              mm(big, At, q, w, 0);
+            v16f sum = v16f{};
+            mm(sum, At + 64 * AP, 0, w, 0);
+            if constexpr (F32) {
+              mm(sum, At + 32 * AP, 0, w, 1);
+              mm(sum, At, 0, w, 2);
             }
-            acc[w] = small + big;
+            mm(sum, At + 32 * AP, 0, w, 0);
+            if constexpr (F32) mm(sum, At, 0, w, 1);
+            acc[w] = sum;
+            if constexpr (Lay::LEAN) __builtin_amdgcn_sched_barrier(0);
+            v16f big = v16f{};
+            mm(big, At, 0, w, 0);
+            acc[w] = acc[w] + big;
+            if constexpr (Lay::LEAN) __builtin_amdgcn_sched_barrier(0);
           }
         } else {
 #pragma unroll
@@ -673,14 +684,9 @@ int encode_mx(const void *G, bool f32, int32_t N, int64_t d, const int32_t *psi,
     a.CW = (a.J * a.PB + 31) & ~31;
     if (mx_lds(a, KS) <= kMxLds || cw == 32) break;  // 32 rows always fit
   }
-  // positions per lane, as registers allow (fp32: 12 PW per K step, bf16 4 PW; 16 PW sums).  On odd rows
-  // at one fp32 step four positions take 215 registers, two waves per SIMD: two positions, four waves
-  // where the grid holds at most four blocks per CU (us, two / four positions: m = 44, delta = 5, d =
-  // 24769, 27 patterns 32.0 / 34.4, m = 30, delta = 11, d = 52503, 8 patterns 19.8 / 22.0; larger, m = 50,
-  // delta = 5, d = 10^6, 8 patterns 525 / 485)
+  // positions per lane, as registers allow (fp32: 12 PW per K step, bf16 4 PW; 16 PW sums)
   const int64_t units = int64_t(a.ngroups) * a.ntp;
-  const bool wide = many || (small_odd && (KS == 2 || ceil_div(a.L, 4 * 128) * units > 4 * int64_t(cu_count())));
-  const int pw = f32 ? (KS <= 2 ? (wide ? 4 : 2) : (KS <= 5 ? 2 : 1)) : (KS <= 8 ? 4 : 2);
+  const int pw = f32 ? (KS <= 2 ? (small_odd || many ? 4 : 2) : (KS <= 5 ? 2 : 1)) : (KS <= 8 ? 4 : 2);
   const int threads = KS <= (f32 ? 2 : 3) ? 256 : 512;
   const int nw = threads / kWave;
   a.ntiles = ceil_div(a.L, int64_t(32) * pw);
